@@ -1782,6 +1782,596 @@ __global__ __launch_bounds__(1024) void k_align(GridArgs g, SearchArgs sa, LibAr
     }
 }
 
+// ---------------------------------------------------------------------------
+// Batched rigid alignment by score bounds.
+//
+// As for the shells, every alignment sample of an atom lies on the sphere of its
+// radius r about the grid centre.  On that sphere a sample is (polar position,
+// azimuth phi about the y axis), and the y rotations of a strip (restart, x
+// rotation i) only turn phi by 12 degrees each: its 30 samples share the polar
+// position and take phi0 + 12 j degrees.  At pocket load k_bounds stores, per
+// atom type and radius band, an upper bound of the interpolated grid over each
+// (band, polar row, azimuth sub-bin of a 12 degree sector), the 30 sectors of a
+// sub-bin side by side: a strip then reads the bounds of all its samples of an
+// atom as one run of 30 16-bit integers.
+//
+// Their sum over the atoms bounds an orientation's score from above.  The
+// orientation of the largest bound is scored first; every orientation whose
+// bound does not reach that score (less a margin above all roundings) cannot be
+// the best one, and the others -- about 2% with bins of a quarter cell -- are
+// scored in FP32 as in align_pose: same transform, samples and atom order, so
+// the chosen orientation is the same one.
+//
+// Bound by the texture unit (busy 0.90): reading a record costs its cache line, and a
+// line from L2 takes about 2 CU-clocks whatever part of it is used; records and the
+// exact scores' cubes are half of it each.  Alignment of 2,500 ligands of 20-80 atoms
+// (256 restarts): 13.1 ms, from 30.9 ms in k_align, which samples every orientation
+// from LDS.  16,000 ligands of 20-100 atoms: 118 ms from 234 ms.
+struct BoundRow {
+    float ylo, yhi, rlo, rhi;  // |y| range and range of the distance to the y axis
+};
+
+__device__ __forceinline__ float band_top(const BoundArgs &bd, int b) { return bd.edge[b + 1]; }
+
+// Rows are uniform in t = sqrt(1 - |y|/r), which is near the polar angle over the
+// whole half sphere (dtheta/dt in [sqrt 2, 2]).  kBoundRowPad covers t's rounding,
+// largest at the pole, where 1 - |y|/r cancels.
+constexpr float kBoundRowPad = 2e-3f;
+constexpr float kBoundPhiPad = 2e-4f;  // radians: bound_sector's error (1e-5) and roundings
+
+__device__ __forceinline__ BoundRow bound_row(float r0, float r1, int row, int rows, float pad) {
+    BoundRow q;
+    const float t0 = fmaxf((float)row / (float)rows - kBoundRowPad, 0.0f);
+    const float t1 = fminf((float)(row + 1) / (float)rows + kBoundRowPad, 1.0f);
+    const float u1 = 1.0f - t0 * t0, u0 = 1.0f - t1 * t1;  // |y|/r in [u0, u1]
+    const float ra = fmaxf(r0 - pad, 0.0f), rb = r1 + pad;
+    q.ylo = u0 * ra - pad;
+    q.yhi = u1 * rb + pad;
+    q.rlo = fmaxf(ra * sqrtf(fmaxf(1.0f - u1 * u1, 0.0f)) - pad, 0.0f);
+    q.rhi = rb * sqrtf(fmaxf(1.0f - u0 * u0, 0.0f)) + pad;
+    return q;
+}
+
+// Range of the sine over [a, b] (b - a below a turn, a > -2 pi).
+__device__ __forceinline__ void sin_range(float a, float b, float &lo, float &hi) {
+    const float pi = 3.14159265358979f;
+    const float sa = sinf(a), sb = sinf(b);
+    lo = fminf(sa, sb);
+    hi = fmaxf(sa, sb);
+    // peaks at pi/2 + 2 pi k, troughs at -pi/2 + 2 pi k
+    if (floorf((b - 0.5f * pi) / (2.0f * pi)) > floorf((a - 0.5f * pi) / (2.0f * pi))) hi = 1.0f;
+    if (floorf((b + 0.5f * pi) / (2.0f * pi)) > floorf((a + 0.5f * pi) / (2.0f * pi))) lo = -1.0f;
+}
+
+// Largest value of the interpolated grid (edge values beyond the box, as the
+// clamps of tri_u give) over the box [lo, hi] in grid units, plus the rounding of
+// a sample there.  In a cell the interpolant is linear along each axis, so its
+// largest value over the box's part of the cell is at one of that part's corners.
+__device__ float box_max(const GridArgs &g, int t, const float (&lo)[3], const float (&hi)[3]) {
+    const int dim[3] = {g.nx, g.ny, g.nz};
+    float a[3], b[3];
+    int c0[3], c1[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const float top = (float)(dim[k] - 1);
+        a[k] = fminf(fmaxf(lo[k], 0.0f), top);
+        b[k] = fminf(fmaxf(hi[k], 0.0f), top);
+        c0[k] = min((int)a[k], dim[k] - 2);
+        c1[k] = min((int)b[k], dim[k] - 2);
+    }
+    float best = -3.4e38f;
+    for (int iz = c0[2]; iz <= c1[2]; ++iz)
+        for (int iy = c0[1]; iy <= c1[1]; ++iy)
+            for (int ix = c0[0]; ix <= c1[0]; ++ix) {
+                const size_t e = ((size_t)t * g.nz * g.ny + (size_t)iz * g.ny + iy) * g.nx + ix;
+                const float4 q0 = g.cubes[2 * e], q1 = g.cubes[2 * e + 1];
+                const float mag = fmaxf(fabsf(q0.x) + fabsf(q0.y) + fabsf(q0.z) + fabsf(q0.w),
+                                        fabsf(q1.x) + fabsf(q1.y) + fabsf(q1.z) + fabsf(q1.w));
+                float m = -3.4e38f;
+#pragma unroll
+                for (int v = 0; v < 8; ++v) {
+                    const float x = (v & 1 ? fminf(b[0], (float)(ix + 1)) : fmaxf(a[0], (float)ix)) - (float)ix;
+                    const float y = (v & 2 ? fminf(b[1], (float)(iy + 1)) : fmaxf(a[1], (float)iy)) - (float)iy;
+                    const float z = (v & 4 ? fminf(b[2], (float)(iz + 1)) : fmaxf(a[2], (float)iz)) - (float)iz;
+                    m = fmaxf(m, tri_blend(q0, q1, x, y, z));
+                }
+                best = fmaxf(best, fmaf(mag, 4e-6f, m));
+            }
+    return best;
+}
+
+// One workgroup column per (type, band); threads over the band's entries.
+__global__ __launch_bounds__(256) void k_bounds(GridArgs g, BoundArgs bd,
+                                                unsigned short *__restrict__ tab) {
+    const int t = blockIdx.y / bd.nb, b = blockIdx.y - t * bd.nb;
+    const int4 q = bd.band[b];
+    const int rows = q.x, m = q.y, total = 2 * rows * m * kBoundRec;
+    unsigned short *out = tab + ((size_t)t * bd.type_bytes + (size_t)q.z) / 2;
+    const bool last = b == bd.nb - 1;
+    const float r0 = bd.edge[b], r1 = last ? r0 : band_top(bd, b);
+    const float sector = 6.28318530717959f / (float)kBoundSteps;
+    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
+        int v = kBoundMax;
+        if (!last) {
+            const int rec = e / kBoundRec, k = e - rec * kBoundRec;
+            const int row2 = rec / m, f = rec - row2 * m;
+            const bool south = row2 >= rows;
+            const BoundRow br = bound_row(r0, r1, south ? row2 - rows : row2, rows, bd.pad);
+            const float p0 = sector * ((float)(k % kBoundSteps) + (float)f / (float)m) - kBoundPhiPad;
+            const float p1 = sector * ((float)(k % kBoundSteps) + (float)(f + 1) / (float)m) + kBoundPhiPad;
+            float sl, sh, cl, ch;
+            sin_range(p0, p1, sl, sh);
+            sin_range(p0 + 1.57079632679490f, p1 + 1.57079632679490f, cl, ch);
+            const float e7 = 1e-6f;  // of the sine itself
+            const float lo[3] = {g.acx + fminf(br.rlo * sl, br.rhi * sl) - br.rhi * e7,
+                                 g.acy + (south ? -br.yhi : br.ylo),
+                                 g.acz + fminf(br.rlo * cl, br.rhi * cl) - br.rhi * e7};
+            const float hi[3] = {g.acx + fmaxf(br.rlo * sh, br.rhi * sh) + br.rhi * e7,
+                                 g.acy + (south ? -br.ylo : br.yhi),
+                                 g.acz + fmaxf(br.rlo * ch, br.rhi * ch) + br.rhi * e7};
+            const float u = (box_max(g, t, lo, hi) - bd.vlow) / bd.step;
+            // the integer above u, so that vlow + step * v is not below the maximum
+            v = u > 0.0f ? (u < (float)kBoundMax ? (int)u + 1 : kBoundMax) : 1;
+        }
+        out[e] = (unsigned short)v;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_value_range(const float *__restrict__ v, long long n,
+                                                     uint32_t *mm) {
+    uint32_t hi = 0u, nlo = 0u, bad = 0u;
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (long long)gridDim.x * blockDim.x) {
+        const float x = v[i];
+        const uint32_t o = ord_f32(x);
+        hi = max(hi, o);
+        nlo = max(nlo, ~o);
+        bad |= !(fabsf(x) <= 1e30f);
+    }
+    atomicMax(&mm[0], hi);
+    atomicMax(&mm[1], nlo);
+    if (bad) atomicOr(&mm[2], 1u);
+}
+
+// Azimuth of (x, z) = rho (sin phi, cos phi) in sectors of 12 degrees, in [0, 30).
+// The arc tangent is the polynomial of Abramowitz and Stegun 4.4.47 (1e-5
+// radians); the scale is a few ulps short of a full turn so that the sector
+// index stays below 30.
+__device__ __forceinline__ float bound_sector(float x, float z) {
+    constexpr float kTurn = (float)kBoundSteps * (1.0f - 1e-6f);
+    constexpr float kRad = kTurn / 6.28318530717959f;
+    const float ax = fabsf(x), az = fabsf(z);
+    const float mn = fminf(ax, az), mx = fmaxf(fmaxf(ax, az), 1e-20f);
+    const float a = mn * __builtin_amdgcn_rcpf(mx), s = a * a;
+    float p = fmaf(s, 0.0208351f * kRad, -0.0851330f * kRad);
+    p = fmaf(s, p, 0.1801410f * kRad);
+    p = fmaf(s, p, -0.3302995f * kRad);
+    p = fmaf(s, p, 0.9998660f * kRad);
+    p *= a;
+    p = ax > az ? 0.25f * kTurn - p : p;
+    p = z < 0.0f ? 0.5f * kTurn - p : p;
+    return x < 0.0f ? kTurn - p : p;
+}
+
+// Low 24 bits of x, plus c.
+__device__ __forceinline__ uint32_t add_low24(uint32_t x, int c) {
+    uint32_t r;
+    asm("v_mad_u32_u24 %0, %1, 1, %2" : "=v"(r) : "v"(x), "v"(c));
+    return r;
+}
+
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+    v = max(v, (uint32_t)dpp_read<0x111, 0xF>((int)v));
+    v = max(v, (uint32_t)dpp_read<0x112, 0xF>((int)v));
+    v = max(v, (uint32_t)dpp_read<0x114, 0xF>((int)v));
+    v = max(v, (uint32_t)dpp_read<0x118, 0xF>((int)v));
+    v = max(v, (uint32_t)dpp_read<0x142, 0xA>((int)v));
+    v = max(v, (uint32_t)dpp_read<0x143, 0xC>((int)v));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Shared memory of k_align_bound (bytes).
+constexpr int kBoundWaves = 4;                     // waves per workgroup
+constexpr int kBoundPerWave = 2;                   // restarts per wave: 60 strips in 64 lanes
+constexpr int kBoundCand = kBoundPerWave * kBoundSteps * kBoundSteps;
+struct BoundLds {
+    static __host__ __device__ size_t xyzt() { return 0; }                     // [nmax] x,y,z,toff
+    static __host__ __device__ size_t dxyz(int nmax) { return (size_t)nmax * 16; }  // X - c0, toff
+    static __host__ __device__ size_t unit(int nmax) { return (size_t)nmax * 32; }  // grid units, 1/r
+    static __host__ __device__ size_t band(int nmax) { return (size_t)nmax * 48; }  // rows, sub-bins, offset
+    static __host__ __device__ size_t misc(int nmax) { return (size_t)nmax * 64; }
+    static __host__ __device__ size_t cand(int nmax) { return misc(nmax) + 16; }
+    static __host__ __device__ size_t total(int nmax) {
+        return cand(nmax) + (size_t)kBoundWaves * kBoundCand * 2;
+    }
+};
+
+typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+// Restart slot, x and y rotation of a bound's place e = lane << 5 | 4 s + c in the
+// wave: strip (lane & ~7) + s, y rotation 4 (lane & 7) + c.
+__device__ __forceinline__ int bound_slot(uint32_t e, int &oi, int &oj) {
+    const int strip = (int)((e >> 5) & 56u) + (int)((e >> 2) & 7u);
+    oj = 4 * (int)((e >> 5) & 7u) + (int)(e & 3u);
+    const int k = strip >= kBoundSteps ? 1 : 0;
+    oi = strip - k * kBoundSteps;
+    return k;
+}
+
+// Exact scores of the listed orientations (see bound_slot), 64 at a time, lane per orientation: align_pose's samples in its atom order.  best[k] is
+// raised to the best key of restart slot k.
+template <bool Inside>
+__device__ __forceinline__ void score_listed(const uint16_t *cand, int nc, const float4 *dxyz, int n,
+                                             const int (&r)[kBoundPerWave],
+                                             const float4 (&cw)[kBoundPerWave],
+                                             const float4 (&ce)[kBoundPerWave], const Tri &tr,
+                                             const GridArgs &g, const SearchArgs &sa,
+                                             u64 (&best)[kBoundPerWave]) {
+    const int lane = lane_id();
+    // lanes past the list leave the loop: a load costs by its active lanes
+    for (int c = lane; c < nc; c += 64) {
+        int oi, oj;
+        const int k = bound_slot(cand[c], oi, oj);
+        const int rr = k ? r[1] : r[0];
+        const float cwx = k ? cw[1].x : cw[0].x, cwy = k ? cw[1].y : cw[0].y,
+                    cwz = k ? cw[1].z : cw[0].z;
+        const float ex = k ? ce[1].x : ce[0].x, ey = k ? ce[1].y : ce[0].y,
+                    ez = k ? ce[1].z : ce[0].z;
+        const float4 m0 = sa.smat[3 * rr + 0], m1 = sa.smat[3 * rr + 1], m2 = sa.smat[3 * rr + 2];
+        const float2 ci = sa.acs[oi], cj = sa.acs[oj];
+        float acc = 0.0f;
+        auto place = [&](const float4 d, float &gx, float &gy, float &gz) {
+            const float yx = fmaf(m0.x, d.x, fmaf(m0.y, d.y, fmaf(m0.z, d.z, g.cx)));
+            const float yy = fmaf(m1.x, d.x, fmaf(m1.y, d.y, fmaf(m1.z, d.z, g.cy)));
+            const float yz = fmaf(m2.x, d.x, fmaf(m2.y, d.y, fmaf(m2.z, d.z, g.cz)));
+            const XStage xs = align_x((yx - cwx) * g.inv_h, (yy - cwy) * g.inv_h,
+                                      (yz - cwz) * g.inv_h, ci, ey);
+            gx = align_gx(xs, cj, ex);
+            gy = xs.gy;
+            gz = align_gz(xs, cj, ez);
+        };
+        constexpr int U = 4;  // atoms whose cube loads are in flight together
+        int a = 0;
+        for (; a + U - 1 < n; a += U) {
+            float fx[U], fy[U], fz[U];
+            float4 q0[U], q1[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float4 d = dxyz[a + u];
+                const int to = uniform_int(__float_as_int(d.w));
+                float gx, gy, gz;
+                place(d, gx, gy, gz);
+                uint32_t off;
+                if (Inside) {
+                    fx[u] = __builtin_amdgcn_fractf(gx);
+                    fy[u] = __builtin_amdgcn_fractf(gy);
+                    fz[u] = __builtin_amdgcn_fractf(gz);
+                    off = in_cell(tr, gx, gy, gz);
+                } else {
+                    off = tri_cell(tr, gx, gy, gz, fx[u], fy[u], fz[u]);
+                }
+                q0[u] = ldq(tr.rs, off, to);
+                q1[u] = ldq(tr.rs, off, to + 16);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < U; ++u) acc += tri_blend(q0[u], q1[u], fx[u], fy[u], fz[u]);
+        }
+        for (; a < n; ++a) {
+            const float4 d = dxyz[a];
+            const int to = uniform_int(__float_as_int(d.w));
+            float gx, gy, gz;
+            place(d, gx, gy, gz);
+            acc += Inside ? tri_in(tr, gx, gy, gz, to) : tri_u(tr, gx, gy, gz, to);
+        }
+        const u64 key = make_key(acc, (uint32_t)(oi * kBoundSteps + oj));
+        if (k == 0) best[0] = key > best[0] ? key : best[0];
+        else best[1] = key > best[1] ? key : best[1];
+    }
+}
+
+// Persistent workgroups pop (ligand, group of kBoundWaves * kBoundPerWave restarts)
+// items (queues as in k_align).  A wave holds two restarts' 60 strips, one per
+// lane.  Per atom each lane finds its strip's record; then eight lanes at a time
+// read one record (a lane 4 of its 32 entries, 8 bytes), so a load covers eight
+// strips with 64 contiguous bytes each, and add them as packed 16-bit integers
+// (ligands of more than kBoundRun atoms: every kBoundRun into 32 bits).
+template <int NS>
+__global__ __launch_bounds__(64 * kBoundWaves, 4) void k_align_bound(GridArgs g, SearchArgs sa,
+                                                                     LibArgs lib, WorkArgs ws,
+                                                                     BoundArgs bd, int bin, int lst) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int nmax = bin_nmax(bin);
+    const int tid = threadIdx.x, wave = uniform_int(tid >> 6), lane = lane_id();
+    float4 *xyzt = (float4 *)(smem + BoundLds::xyzt());
+    float4 *dxyz = (float4 *)(smem + BoundLds::dxyz(nmax));
+    float4 *unit = (float4 *)(smem + BoundLds::unit(nmax));
+    float4 *band = (float4 *)(smem + BoundLds::band(nmax));
+    int *misc = (int *)(smem + BoundLds::misc(nmax));
+    uint16_t *cand = (uint16_t *)(smem + BoundLds::cand(nmax)) + (size_t)wave * kBoundCand;
+    const Tri tr = make_tri(g);
+    const __amdgpu_buffer_rsrc_t brs =
+        __builtin_amdgcn_make_buffer_rsrc((void *)bd.tab, (short)0, (int)bd.bytes, 0x00020000);
+    constexpr int GR = kBoundWaves * kBoundPerWave;
+    const int groups = (sa.R + GR - 1) / GR;
+    // the lane's strip, its 8-lane group and place in it
+    const int q8 = lane & 7;
+    const int slot = lane >= kBoundSteps && lane < 2 * kBoundSteps ? 1 : 0;
+    const int si = lane < 2 * kBoundSteps ? lane - kBoundSteps * slot : 0;
+    const float2 ci = sa.acs[si];
+    const uint32_t wrap_at = (uint32_t)(q8 + 1) << 24;
+    const int c_in = 8 * q8, c_wrap = 8 * q8 - 2 * kBoundSteps;
+    const long long nl = ws.counters[lst];
+    int *qc = ws.counters + 4 * kMaxLists + lst * kXcds;
+    int qcur = (int)(blockIdx.x % kXcds), qleft = kXcds;
+    for (;;) {
+        if (tid == 0) {
+            int qli = -1, qgrp = 0;
+            while (qleft > 0) {
+                const long long l0 = nl * qcur / kXcds, l1 = nl * (qcur + 1) / kXcds;
+                const long long items = (l1 - l0) * groups;
+                const int got = items > 0 ? atomicAdd(&qc[qcur], 1) : 0;
+                if ((long long)got < items) {
+                    qli = (int)(l0 + got / groups);
+                    qgrp = got % groups;
+                    break;
+                }
+                qcur = qcur + 1 == kXcds ? 0 : qcur + 1;
+                --qleft;
+            }
+            misc[0] = qli;
+            misc[1] = qgrp;
+        }
+        __syncthreads();
+        const int li = uniform_int(misc[0]), grp = uniform_int(misc[1]);
+        if (li < 0) break;
+        const int l = ws.bin_list[(size_t)lst * lib.L + li];
+        const int a0 = lib.atom_off[l], n = lib.atom_off[l + 1] - a0;
+        const int B = lib.rot_off[l + 1] - lib.rot_off[l];
+        for (int i = tid; i < n; i += 64 * kBoundWaves) {
+            const float *p = lib.xyz + 3 * (size_t)(a0 + i);
+            const uint32_t toff = (uint32_t)lib.type[a0 + i] * g.type_bytes;
+            xyzt[i] = make_float4(p[0], p[1], p[2], __uint_as_float(toff));
+        }
+        __syncthreads();
+        if (wave == 0) {
+            // ligand-centred coordinates X - c0, with the c0 of start_pose, and each
+            // atom's radius band
+            Pose<NS> X;
+#pragma unroll
+            for (int q = 0; q < NS; ++q) {
+                const int i = lane + 64 * q;
+                const float4 v = i < n ? xyzt[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+                X.x[q] = v.x;
+                X.y[q] = v.y;
+                X.z[q] = v.z;
+            }
+            float c0x, c0y, c0z;
+            centroid(X, n, c0x, c0y, c0z);
+#pragma unroll
+            for (int q = 0; q < NS; ++q) {
+                const int i = lane + 64 * q;
+                if (i >= n) continue;
+                const float dx = X.x[q] - c0x, dy = X.y[q] - c0y, dz = X.z[q] - c0z;
+                const float ux = dx * g.inv_h, uy = dy * g.inv_h, uz = dz * g.inv_h;
+                const float rad = sqrtf(fmaf(ux, ux, fmaf(uy, uy, uz * uz)));
+                int lo = 0, hi = bd.nb - 1;  // last band whose lower radius is not above rad
+                while (lo < hi) {
+                    const int mid = (lo + hi + 1) >> 1;
+                    if (bd.edge[mid] <= rad) lo = mid;
+                    else hi = mid - 1;
+                }
+                const int4 bq = bd.band[lo];
+                const uint32_t off = (uint32_t)lib.type[a0 + i] * bd.type_bytes + (uint32_t)bq.z;
+                dxyz[i] = make_float4(dx, dy, dz, xyzt[i].w);
+                unit[i] = make_float4(ux, uy, uz, rad > 1e-6f ? 1.0f / rad : 0.0f);
+                band[i] = make_float4((float)bq.x, (float)bq.y, __uint_as_float(off), 0.0f);
+            }
+        }
+        int r[kBoundPerWave];
+        float4 cw[kBoundPerWave], ce[kBoundPerWave];
+        bool out_any = false;
+        const int rbase = grp * GR + wave * kBoundPerWave;
+#pragma unroll
+        for (int k = 0; k < kBoundPerWave; ++k) {
+            r[k] = min(rbase + k, sa.R - 1);  // restarts past R repeat the last one
+            Pose<NS> Y;
+            start_pose(Y, xyzt, n, r[k], g, sa);
+            float cx, cy, cz;
+            centroid(Y, n, cx, cy, cz);
+            cw[k] = make_float4(cx, cy, cz, 0.f);
+            ce[k] = make_float4((cx - g.ox) * g.inv_h, (cy - g.oy) * g.inv_h,
+                                (cz - g.oz) * g.inv_h, 0.f);
+#pragma unroll
+            for (int q = 0; q < NS; ++q) {
+                const float rx = (Y.x[q] - cx) * g.inv_h, ry = (Y.y[q] - cy) * g.inv_h,
+                            rz = (Y.z[q] - cz) * g.inv_h;
+                if (lane + 64 * q < n)
+                    out_any = out_any ||
+                              !ball_inside(tr, ce[k].x, ce[k].y, ce[k].z,
+                                           ball_radius(fmaf(rx, rx, fmaf(ry, ry, rz * rz))));
+            }
+        }
+        const bool all_in = __ballot(out_any) == 0ull;
+        __syncthreads();
+        if (rbase < sa.R) {
+            // rows of R_x(i) S_r of the lane's strip
+            const int rs = slot ? r[1] : r[0];
+            const float4 s0 = sa.smat[3 * rs + 0], s1 = sa.smat[3 * rs + 1], s2 = sa.smat[3 * rs + 2];
+            const float ax = fmaf(ci.x, s1.x, -ci.y * s2.x), ay = fmaf(ci.x, s1.y, -ci.y * s2.y),
+                        az = fmaf(ci.x, s1.z, -ci.y * s2.z);
+            const float bx = fmaf(ci.y, s1.x, ci.x * s2.x), by = fmaf(ci.y, s1.y, ci.x * s2.y),
+                        bz = fmaf(ci.y, s1.z, ci.x * s2.z);
+            us2 acc[8][2];
+            constexpr bool kWide = NS * 64 > kBoundRun;
+            uint32_t sum[kWide ? 8 : 1][4];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                acc[s][0] = acc[s][1] = (us2)(0);
+                if constexpr (kWide) sum[s][0] = sum[s][1] = sum[s][2] = sum[s][3] = 0u;
+            }
+            // The record of the lane's strip for atom a: byte offset of its entry k0 in the
+            // band (below 2^24) and, in the top byte, the first lane of an 8-lane group
+            // whose 4 entries start past the turn.
+            auto record = [&](int a, int &soff) -> uint32_t {
+                const float4 u = unit[a], bq = band[a];
+                const float rx = fmaf(s0.x, u.x, fmaf(s0.y, u.y, s0.z * u.z));
+                const float gy = fmaf(ax, u.x, fmaf(ay, u.y, az * u.z));
+                const float qz = fmaf(bx, u.x, fmaf(by, u.y, bz * u.z));
+                // t and the sector fraction are below 1 by an ulp at least, so their rows
+                // and sub-bins are in range
+                const float t = __builtin_amdgcn_sqrtf(fmaxf(fmaf(-fabsf(gy), u.w, 0.99999988f), 0.0f));
+                const float rowf = floorf(t * bq.x) + (gy < 0.0f ? bq.x : 0.0f);
+                const float p = bound_sector(rx, qz);
+                const float k0 = floorf(p);
+                const float rec = fmaf(rowf, bq.y, floorf((p - k0) * bq.y));
+                const uint32_t ki = (uint32_t)k0;
+                const uint32_t at = (uint32_t)(rec * (2.0f * (float)kBoundRec)) + 2u * ki;
+                soff = uniform_int(__float_as_int(bq.z));
+                return at | ((((uint32_t)(kBoundSteps + 3) << 22) - (ki << 22)) & 0xFF000000u);
+            };
+            int soff;
+            uint32_t v = record(0, soff);
+            for (int a = 0; a < n; ++a) {
+                u32x2 w[8];
+#define DOCK_BOUND_LOAD(S)                                                                      \
+    {                                                                                           \
+        const uint32_t x = (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (S << 5) | 0x18);      \
+        w[S] = __builtin_amdgcn_raw_buffer_load_b64(                                            \
+            brs, (int)add_low24(x, x < wrap_at ? c_wrap : c_in), soff, 0);                      \
+    }
+                DOCK_BOUND_LOAD(0) DOCK_BOUND_LOAD(1) DOCK_BOUND_LOAD(2) DOCK_BOUND_LOAD(3)
+                DOCK_BOUND_LOAD(4) DOCK_BOUND_LOAD(5) DOCK_BOUND_LOAD(6) DOCK_BOUND_LOAD(7)
+#undef DOCK_BOUND_LOAD
+                // the next atom's record while the loads are in flight
+                v = record(a + 1 < n ? a + 1 : a, soff);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int s = 0; s < 8; ++s) {
+                    acc[s][0] += __builtin_bit_cast(us2, (uint32_t)w[s].x);
+                    acc[s][1] += __builtin_bit_cast(us2, (uint32_t)w[s].y);
+                }
+                if constexpr (kWide) {
+                    if ((a & (kBoundRun - 1)) == kBoundRun - 1) {
+#pragma unroll
+                        for (int s = 0; s < 8; ++s) {
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) sum[s][c] += acc[s][c >> 1][c & 1];
+                            acc[s][0] = acc[s][1] = (us2)(0);
+                        }
+                    }
+                }
+            }
+            // no bound for strips past the second restart's and y rotations past the turn
+            // (every real one is at least 1 per atom)
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                const bool no_strip = s >= 4 && lane >= 56;
+                if (no_strip) acc[s][0] = (us2)(0);
+                if (no_strip || q8 == 7) acc[s][1] = (us2)(0);
+                if constexpr (kWide) {
+                    if (no_strip) sum[s][0] = sum[s][1] = 0u;
+                    if (no_strip || q8 == 7) sum[s][2] = sum[s][3] = 0u;
+                }
+            }
+            auto bound = [&](int s, int c) -> uint32_t {
+                uint32_t v = acc[s][c >> 1][c & 1];
+                if constexpr (kWide) v += sum[s][c];
+                return v;
+            };
+            const bool second = lane >= 32;  // strips of lane & ~7 + s >= 30: or lanes 24..31, s >= 6
+            const bool split = lane >= 24 && lane < 32;
+            // slot of the largest bound of each restart: key = bound << 11 | lane << 5 | 4 s + c
+            uint32_t top[kBoundPerWave] = {0u, 0u};
+            {
+                uint32_t lo = 0u, hi = 0u;  // slots s < 6 and s >= 6
+#pragma unroll
+                for (int s = 0; s < 8; ++s)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const uint32_t key = (bound(s, c) << 11) | (uint32_t)(4 * s + c);
+                        if (s < 6) lo = max(lo, key);
+                        else hi = max(hi, key);
+                    }
+                const uint32_t at = (uint32_t)lane << 5;
+                lo |= at;
+                hi |= at;
+                top[0] = second ? 0u : (split ? lo : max(lo, hi));
+                top[1] = second ? max(lo, hi) : (split ? hi : 0u);
+            }
+            // (the bounds again below: keeping all 32 unpacked would fill the registers)
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+                asm volatile("" : "+v"(acc[s][0]), "+v"(acc[s][1]));
+            uint32_t least[kBoundPerWave];  // smallest bound that can be the best score
+#pragma unroll
+            for (int k = 0; k < kBoundPerWave; ++k) {
+                int oi, oj;
+                bound_slot(wave_max_u32(top[k]) & 2047u, oi, oj);
+                const float2 xi = sa.acs[oi], xj = sa.acs[oj];
+                const float4 m0 = sa.smat[3 * r[k] + 0], m1 = sa.smat[3 * r[k] + 1],
+                             m2 = sa.smat[3 * r[k] + 2];
+                float v = 0.0f;
+#pragma unroll
+                for (int q = 0; q < NS; ++q) {
+                    const int i = lane + 64 * q;
+                    if (i < n) {
+                        const float4 d = dxyz[i];
+                        const float yx = fmaf(m0.x, d.x, fmaf(m0.y, d.y, fmaf(m0.z, d.z, g.cx)));
+                        const float yy = fmaf(m1.x, d.x, fmaf(m1.y, d.y, fmaf(m1.z, d.z, g.cy)));
+                        const float yz = fmaf(m2.x, d.x, fmaf(m2.y, d.y, fmaf(m2.z, d.z, g.cz)));
+                        const XStage xs = align_x((yx - cw[k].x) * g.inv_h, (yy - cw[k].y) * g.inv_h,
+                                                  (yz - cw[k].z) * g.inv_h, xi, ce[k].y);
+                        v += tri_v(tr, align_gx(xs, xj, ce[k].x), xs.gy, align_gz(xs, xj, ce[k].z),
+                                   (uint32_t)__float_as_int(d.w));
+                    }
+                }
+                const float got = wave_sum(v);
+                // roundings: of the two sums of n terms (n^2 2^-24 of the largest term
+                // each, and relative to the score), and of the bound's quantisation
+                const float nf = (float)n;
+                const float low = got - fabsf(got) * 1e-5f - nf * nf * 5e-7f * bd.mag -
+                                  nf * 2e-3f * bd.step;
+                const float x = (low - nf * bd.vlow) / bd.step;
+                // not above 2, or NaN: every orientation stays
+                least[k] = x > 2.0f ? (uint32_t)fminf(x, 1e9f) - 1u : 1u;
+            }
+            // the orientations that stay
+            int nc = 0;
+            const uint32_t lim_lo = second ? least[1] : least[0];
+            const uint32_t lim_hi = second || split ? least[1] : least[0];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const bool ok = bound(s, c) >= (s < 6 ? lim_lo : lim_hi);
+                    const u64 bm = __ballot(ok);
+                    if (bm == 0ull) continue;
+                    if (ok)
+                        cand[nc + (int)__builtin_amdgcn_mbcnt_hi(
+                                      (uint32_t)(bm >> 32),
+                                      __builtin_amdgcn_mbcnt_lo((uint32_t)bm, 0u))] =
+                            (uint16_t)((lane << 5) | (4 * s + c));
+                    nc += __popcll(bm);
+                }
+            }
+            wave_lds_sync();
+            u64 best[kBoundPerWave] = {0ull, 0ull};
+            if (all_in) score_listed<true>(cand, nc, dxyz, n, r, cw, ce, tr, g, sa, best);
+            else score_listed<false>(cand, nc, dxyz, n, r, cw, ce, tr, g, sa, best);
+#pragma unroll
+            for (int k = 0; k < kBoundPerWave; ++k) {
+                const u64 bk = wave_max_u64(best[k]);
+                if (lane == 0 && rbase + k < sa.R)
+                    ws.rtrace[trace_base(lib, sa, l) + (size_t)(rbase + k) * (1 + sa.P * B)] =
+                        (uint16_t)key_index(bk);
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // Plain (latency) form: one ligand per launch sequence.  Workgroup r docks
 // restart r; its waves split the orientations and the torsion candidates and
 // agree on every decision through LDS and workgroup barriers.
@@ -2896,6 +3486,56 @@ int align_blocks_per_cu(int bin, int R, int A, int arena) {
         case 2: return align_occ_t<2>(waves, arena);
         case 3: return align_occ_t<3>(waves, arena);
         default: return align_occ_t<4>(waves, arena);
+    }
+}
+
+hipError_t launch_value_range(const float *v, long long n, uint32_t *mm, hipStream_t s) {
+    hipLaunchKernelGGL(k_value_range, dim3(512), dim3(256), 0, s, v, n, mm);
+    return hipGetLastError();
+}
+
+hipError_t launch_bounds(const GridArgs &g, const BoundArgs &bd, unsigned short *tab,
+                         hipStream_t s) {
+    if (bd.nb <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_bounds, dim3(32, bd.nb * g.ntypes), dim3(256), 0, s, g, bd, tab);
+    return hipGetLastError();
+}
+
+template <int NS>
+static hipError_t launch_align_bound_t(int bin, int lst, int blocks, const GridArgs &g,
+                                       const SearchArgs &sa, const LibArgs &lib, const WorkArgs &ws,
+                                       const BoundArgs &bd, hipStream_t s) {
+    hipLaunchKernelGGL((k_align_bound<NS>), dim3(blocks), dim3(64 * kBoundWaves),
+                       BoundLds::total(bin_nmax(bin)), s, g, sa, lib, ws, bd, bin, lst);
+    return hipGetLastError();
+}
+
+hipError_t launch_align_bound(int bin, int lst, int blocks, const GridArgs &g,
+                              const SearchArgs &sa, const LibArgs &lib, const WorkArgs &ws,
+                              const BoundArgs &bd, hipStream_t s) {
+    switch (bin_slots(bin)) {
+        case 1: return launch_align_bound_t<1>(bin, lst, blocks, g, sa, lib, ws, bd, s);
+        case 2: return launch_align_bound_t<2>(bin, lst, blocks, g, sa, lib, ws, bd, s);
+        case 3: return launch_align_bound_t<3>(bin, lst, blocks, g, sa, lib, ws, bd, s);
+        default: return launch_align_bound_t<4>(bin, lst, blocks, g, sa, lib, ws, bd, s);
+    }
+}
+
+template <int NS>
+static int align_bound_occ(int bin) {
+    int nb = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_align_bound<NS>, 64 * kBoundWaves,
+                                                     BoundLds::total(bin_nmax(bin))) != hipSuccess)
+        return 1;
+    return nb > 0 ? nb : 1;
+}
+
+int align_bound_blocks_per_cu(int bin) {
+    switch (bin_slots(bin)) {
+        case 1: return align_bound_occ<1>(bin);
+        case 2: return align_bound_occ<2>(bin);
+        case 3: return align_bound_occ<3>(bin);
+        default: return align_bound_occ<4>(bin);
     }
 }
 

@@ -53,6 +53,26 @@ struct GridArgs {
     float acx, acy, acz;   // grid centre in grid units
 };
 
+// Score bounds of the alignment (see k_align_bound): per atom type and radius band
+// b, records of kBoundSteps + 3 16-bit bounds, one record per (polar row, azimuth
+// sub-bin).  A sample's value is at most vlow + step * bound.
+constexpr int kBoundSteps = 30;    // alignment steps the records are laid out for (12 degrees)
+constexpr int kBoundRec = kBoundSteps + 3;  // entries: a turn and 3 repeated
+constexpr int kMaxBoundBands = 1024;
+constexpr int kBoundMax = 511;     // entries are in [1, kBoundMax]
+constexpr int kBoundRun = 128;     // atoms whose bounds sum in 16 bits
+struct BoundArgs {
+    const unsigned short *tab;  // [ntypes][type_bytes / 2]
+    const float *edge;          // [nb] lower radius of each band (grid units), edge[0] = 0
+    const int4 *band;           // [nb] (rows per half sphere, azimuth sub-bins, byte offset, 0)
+    uint32_t bytes, type_bytes;
+    int nb;                     // bands; 0: no bounds (every orientation is scored).  The
+                                // last band has no upper radius and holds kBoundMax.
+    float step, vlow;
+    float mag;                  // max(|vlow|, |largest value|)
+    float pad;                  // bin padding, grid units
+};
+
 struct SearchArgs {
     int R, T, P, A, K, final_align, bmin;
     int prune;             // 1: prune the bump check and score only bump-free candidates
@@ -154,6 +174,19 @@ hipError_t launch_atlas_fill(const GridArgs &g, int4 *info, const int *blob16, f
 hipError_t launch_align(int bin, int lst, int blocks, int arena, const GridArgs &g,
                         const SearchArgs &sa, const LibArgs &lib, const WorkArgs &ws,
                         hipStream_t s);
+// Alignment with score bounds (k_align_bound), for searches of kBoundSteps steps on
+// a pocket that has them; the same results as launch_align.
+hipError_t launch_align_bound(int bin, int lst, int blocks, const GridArgs &g,
+                              const SearchArgs &sa, const LibArgs &lib, const WorkArgs &ws,
+                              const BoundArgs &bd, hipStream_t s);
+int align_bound_blocks_per_cu(int bin);
+// Extremes of n grid values as order-preserving integers: mm[0] = largest, mm[1] =
+// complement of the smallest, mm[2] = 1 when a value is not finite or beyond 1e30
+// (mm zeroed by the caller).
+hipError_t launch_value_range(const float *v, long long n, uint32_t *mm, hipStream_t s);
+// Fills the bound tables of every type.
+hipError_t launch_bounds(const GridArgs &g, const BoundArgs &bd, unsigned short *tab,
+                         hipStream_t s);
 // Smallest arena k_align accepts for the bin (fixed part plus a minimal region).
 size_t align_lds_min(int bin, int A, int R);
 int align_blocks_per_cu(int bin, int R, int A, int arena);

@@ -77,7 +77,9 @@ struct Pocket {
     int4 *d_bands = nullptr;
     int *d_blob16 = nullptr;
     void *d_contacts = nullptr;  // pocket atoms, cell starts and weights (rescoring)
+    void *d_bounds = nullptr;    // score bounds of the alignment: bands, edges, tables
     GridArgs g{};
+    BoundArgs bd{};
     ContactArgs ca{};
     bool has_atoms = false;
     int busy = 0;
@@ -92,6 +94,8 @@ struct Pocket {
         hipFree(d_atlas);
         hipFree(d_bands);
         hipFree(d_blob16);
+        hipFree(d_bounds);
+        d_bounds = nullptr;
         release_atoms();
         d_cubes = d_atlas = nullptr;
         d_bands = nullptr;
@@ -553,6 +557,7 @@ struct Launch {
     WorkArgs wa;
     OutArgs oa;
     ContactArgs ca;
+    BoundArgs bd;  // nb = 0: the alignment runs from the shell atlas (k_align)
 };
 
 // Tables, workspace and kernel arguments of a call on a device-resident library
@@ -654,6 +659,7 @@ int prepare_launch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const
     oa.ftrace = o->final_trace;
     oa.pcontacts = o->pose_contacts;
     if (pk.has_atoms) std::memcpy((void *)&L->ca, (const void *)&pk.ca, sizeof(ContactArgs));
+    if (sa.A == kBoundSteps) std::memcpy((void *)&L->bd, (const void *)&pk.bd, sizeof(BoundArgs));
     return DOCK_OK;
 }
 
@@ -678,10 +684,15 @@ int make_shapes(dock_ctx *c, const Launch &L, const BinShape *tile, Shapes *sh) 
         sh->tile[bin] = t;
         if ((size_t)c->lds_arena < align_lds_min(bin, sa.A, sa.R))
             return fail(DOCK_EDEVICE, "device LDS per workgroup too small for the alignment kernel");
-        const std::string a = "a" + std::to_string(bin) + "/" + std::to_string(sa.R) + "/" +
-                              std::to_string(sa.A) + "/" + std::to_string(c->lds_arena);
-        sh->align_blocks[bin] =
-            occupancy(c, a, align_blocks_per_cu(bin, sa.R, sa.A, c->lds_arena)) * c->num_cu;
+        if (L.bd.nb > 0) {
+            const std::string a = "ab" + std::to_string(bin);
+            sh->align_blocks[bin] = occupancy(c, a, align_bound_blocks_per_cu(bin)) * c->num_cu;
+        } else {
+            const std::string a = "a" + std::to_string(bin) + "/" + std::to_string(sa.R) + "/" +
+                                  std::to_string(sa.A) + "/" + std::to_string(c->lds_arena);
+            sh->align_blocks[bin] =
+                occupancy(c, a, align_blocks_per_cu(bin, sa.R, sa.A, c->lds_arena)) * c->num_cu;
+        }
         const std::string k = "d" + std::to_string(bin) + "/" + std::to_string(t.dock_waves) + "/" +
                               std::to_string((sa.T + 63) / 64);
         sh->dock_blocks[bin] =
@@ -720,8 +731,10 @@ int run_sequence(dock_ctx *c, const Launch &L, const Shapes &sh, hipStream_t s,
     // each stage: one launch per work list (atom bin, or atom bin x bond group)
     for (int bin = 0; bin < kNumBins; ++bin)
         for (int q = 0; q < G; ++q)
-            HIP_TRY(launch_align(bin, bin * G + q, sh.align_blocks[bin], c->lds_arena, g, sa, la,
-                                 wa, s));
+            HIP_TRY(L.bd.nb > 0 ? launch_align_bound(bin, bin * G + q, sh.align_blocks[bin], g, sa,
+                                                     la, wa, L.bd, s)
+                                : launch_align(bin, bin * G + q, sh.align_blocks[bin],
+                                               c->lds_arena, g, sa, la, wa, s));
     if (marks) HIP_TRY(hipEventRecord((*marks)[2], s));
     for (int bin = 0; bin < kNumBins; ++bin)
         for (int q = 0; q < G; ++q)
@@ -861,6 +874,92 @@ int build_atlas(dock_ctx *c, Pocket &pk) {
     return DOCK_OK;
 }
 
+// Score bounds of the alignment (k_align_bound), from the plain grid on the device:
+// bins of a quarter cell up to 16 cells from the centre, of 1/64 of the radius beyond
+// (so that every farther band has as many bins), up to 40 cells; atoms farther out
+// get the grid's largest value.  Half that in radius, which costs memory only: an
+// atom's radius picks one band.  (A CPU count over random trees of 60 atoms: 14 of 900
+// orientations are left with these bins, 19 with a quarter cell in radius too.)
+// Values below -1/2 times the largest one count as that: the best orientation has few
+// of them, and forbidden regions would leave no resolution for the others.  Without
+// a finite grid, or where coordinates this far from the origin round by more than a hundredth
+// of a cell, or where the tables would pass 1 GiB, the pocket has no bounds.
+constexpr float kBoundBin = 0.25f;
+constexpr float kBoundRadial = 0.5f;
+constexpr float kBoundTop = 40.0f;
+
+int build_bounds(Pocket &pk, const float *d_vals) {
+    const GridArgs &g = pk.g;
+    BoundArgs bd{};
+    const int nmax = std::max(g.nx, std::max(g.ny, g.nz));
+    const float o[3] = {g.ox, g.oy, g.oz};
+    const int dim[3] = {g.nx, g.ny, g.nz};
+    double far = 0;
+    for (int a = 0; a < 3; ++a)
+        far = std::max(far, std::fabs((double)o[a] * g.inv_h) + dim[a]);
+    const double rounding = far * std::ldexp(1.0, -20);
+    if (rounding > 0.01) return DOCK_OK;
+    bd.pad = 0.01f + (float)rounding;
+    std::vector<float> edge;
+    std::vector<int4> band;
+    size_t off = 0;
+    float r = 0.f;
+    const float top = std::min(kBoundTop, 0.5f * (float)nmax + 4.0f);
+    while (r < top && (int)edge.size() < kMaxBoundBands - 1) {
+        const float d = std::max(kBoundBin, r / 64.0f), r1 = r + d * kBoundRadial;
+        const int rows = (int)std::ceil(r1 * 1.5708f / d),
+                  m = (int)std::ceil(r1 * 6.2832f / (kBoundSteps * d));
+        edge.push_back(r);
+        band.push_back(make_int4(rows, m, (int)off, 0));
+        off += align256((size_t)2 * rows * m * kBoundRec * 2);
+        r = r1;
+    }
+    edge.push_back(r);  // no upper radius: every bound is the largest
+    band.push_back(make_int4(1, 1, (int)off, 0));
+    off += align256((size_t)2 * kBoundRec * 2);
+    if (off * g.ntypes > ((size_t)1 << 30)) return DOCK_OK;
+    bd.nb = (int)edge.size();
+    bd.type_bytes = (uint32_t)off;
+    bd.bytes = (uint32_t)(off * g.ntypes);
+    const size_t b_band = align256(bd.nb * sizeof(int4)), b_edge = align256(bd.nb * sizeof(float));
+    char *d = nullptr;
+    if (hipMalloc((void **)&d, b_band + b_edge + 256 + bd.bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return DOCK_OK;
+    }
+    pk.d_bounds = d;
+    uint32_t *mm = (uint32_t *)(d + b_band + b_edge);
+    unsigned short *tab = (unsigned short *)(d + b_band + b_edge + 256);
+    uint32_t h[3] = {0, 0, 0};
+    HIP_TRY(hipMemcpy(d, band.data(), bd.nb * sizeof(int4), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(d + b_band, edge.data(), bd.nb * sizeof(float), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(mm, h, sizeof(h), hipMemcpyHostToDevice));
+    HIP_TRY(launch_value_range(d_vals, (long long)g.ncells, mm, nullptr));
+    HIP_TRY(hipMemcpy(h, mm, sizeof(h), hipMemcpyDeviceToHost));
+    auto value = [](uint32_t u) {  // inverse of ord_f32
+        const uint32_t b = (u & 0x80000000u) ? (u & 0x7fffffffu) : ~u;
+        float f;
+        std::memcpy(&f, &b, sizeof(f));
+        return f;
+    };
+    if (h[2]) {
+        (void)hipFree(d);
+        pk.d_bounds = nullptr;
+        return DOCK_OK;
+    }
+    const float vmax = value(h[0]), vmin = value(~h[1]);
+        bd.vlow = vmax > 0.f ? std::max(vmin, -0.5f * vmax) : vmin;
+    bd.mag = std::max(std::fabs(vmax), std::fabs(bd.vlow));
+    bd.step = std::max((vmax - bd.vlow + 1e-5f * bd.mag) / (float)(kBoundMax - 2), 1e-30f);
+    bd.tab = tab;
+    bd.band = (const int4 *)d;
+    bd.edge = (const float *)(d + b_band);
+    HIP_TRY(launch_bounds(g, bd, tab, nullptr));
+    HIP_TRY(hipDeviceSynchronize());
+    pk.bd = bd;
+    return DOCK_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -957,8 +1056,8 @@ int dock_pocket_load(dock_ctx *c, const dock_grid_desc *gd, int32_t *pocket_id) 
     hipError_t e = hipMemcpy(d_vals, gd->values, (size_t)bytes, hipMemcpyHostToDevice);
     if (!e) e = launch_build_cubes(d_vals, pk.d_cubes, gd->ntypes, gd->nx, gd->ny, gd->nz, nullptr);
     if (!e) e = hipDeviceSynchronize();
-    hipFree(d_vals);
     if (e) {
+        hipFree(d_vals);
         hipFree(pk.d_cubes);
         return fail(DOCK_EDEVICE, std::string("pocket upload failed: ") + hipGetErrorString(e));
     }
@@ -988,7 +1087,9 @@ int dock_pocket_load(dock_ctx *c, const dock_grid_desc *gd, int32_t *pocket_id) 
     g.acx = (g.cx - g.ox) * g.inv_h;
     g.acy = (g.cy - g.oy) * g.inv_h;
     g.acz = (g.cz - g.oz) * g.inv_h;
-    const int rc = build_atlas(c, pk);
+    int rc = build_atlas(c, pk);
+    if (!rc) rc = build_bounds(pk, d_vals);
+    hipFree(d_vals);
     if (rc) {
         pk.release();
         return rc;

@@ -1,0 +1,65 @@
+"""The alignment by score bounds (30 alignment steps) against the FP64 oracle, at the
+sizes and pockets where a bound, a list or a record could go wrong."""
+import numpy as np
+import pytest
+
+import synth
+from tests.test_gpu_parity import D, check_all, ctx, run_batch  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def _pocket(kind, seed):
+    pk = synth.pocket_gaussians(seed, 4, 32, 0.5, 40, 4.0)
+    if kind == "flat":  # every orientation ties: all of them are scored
+        pk.values[:] = 0.25
+    elif kind == "walls":  # forbidden regions
+        pk.values[pk.values < -0.2] = -1e6
+    elif kind == "negative":  # no positive value
+        pk.values -= 3.0
+    elif kind == "far":  # coordinates far from the origin
+        o = tuple(x + s for x, s in zip(pk.origin, (310.0, -145.0, 78.0)))
+        pk = synth.Pocket(pk.values, pk.spacing, o)
+    return pk
+
+
+@pytest.mark.parametrize("kind,atoms,restarts", [
+    ("plain", [1, 2, 3, 31, 32, 33], 1),
+    ("plain", [63, 64, 65, 127, 128], 3),
+    ("plain", [129, 192, 193, 256], 21),
+    ("plain", [20, 40], 17),
+    ("flat", [7, 40], 3),
+    ("walls", [12, 66], 9),
+    ("negative", [12, 66], 8),
+])
+def test_bounded_alignment_is_the_oracles(D, ctx, kind, atoms, restarts):  # noqa: F811
+    pk = _pocket(kind, 71)
+    lib = synth.library_from_sizes(72, atoms, [0] * len(atoms))
+    q = synth.start_quats(73, restarts)
+    print(f"[case] bounds {kind} {atoms} R={restarts}", flush=True)
+    h, params = run_batch(D, ctx, pk, lib, q, torsion_steps=16, sweep_passes=1, top_k=2,
+                          dedup_rmsd=0.0)
+    check_all(D, pk, lib, q, h, params, label=f"bounds-{kind}")
+
+
+@pytest.mark.parametrize("kind,atoms,rot,restarts", [
+    ("plain", [5, 33, 70], [1, 3, 5], 11),
+    # FP32 coordinates this far from the origin are off by more than the oracle's
+    # tolerance on either path
+    ("far", [12, 66], [0, 0], 7),
+])
+def test_pocket_without_bounds_takes_the_same_orientations(D, ctx, kind, atoms, rot,  # noqa: F811
+                                                           restarts):
+    # one value beyond the range the bounds are kept for, in a corner no ligand
+    # reaches: every decision is that of the pocket with bounds
+    pk = _pocket(kind, 71)
+    lib = synth.library_from_sizes(72, atoms, rot)
+    q = synth.start_quats(73, restarts)
+    kw = dict(torsion_steps=32, sweep_passes=1, top_k=4, dedup_rmsd=0.0)
+    print(f"[case] bounds on and off, {kind}", flush=True)
+    a, _ = run_batch(D, ctx, pk, lib, q, **kw)
+    off = pk.values.copy()
+    off[:, 0, 0, 0] = 2e30
+    b, _ = run_batch(D, ctx, synth.Pocket(off, pk.spacing, pk.origin), lib, q, **kw)
+    for k in ("trace", "restart_score", "pose_score", "pose_xyz", "final_trace"):
+        np.testing.assert_array_equal(a[k], b[k], err_msg=k)
