@@ -29,6 +29,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cmath>
+
 #include "dock_internal.h"
 
 namespace dockgpu {
@@ -83,6 +85,29 @@ __device__ __forceinline__ u64 wave_max_u64(u64 v) {
     return read_lane64(v, 63);
 }
 
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+    v = max(v, (uint32_t)dpp_read<0x111, 0xF>((int)v));
+    v = max(v, (uint32_t)dpp_read<0x112, 0xF>((int)v));
+    v = max(v, (uint32_t)dpp_read<0x114, 0xF>((int)v));
+    v = max(v, (uint32_t)dpp_read<0x118, 0xF>((int)v));
+    v = max(v, (uint32_t)dpp_read<0x142, 0xA>((int)v));
+    v = max(v, (uint32_t)dpp_read<0x143, 0xC>((int)v));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Largest key of the wave in two 32-bit steps: the largest upper half, then the
+// largest lower half among its lanes (most often one lane).
+__device__ __forceinline__ u64 wave_max_key(u64 v) {
+    const uint32_t hi = (uint32_t)(v >> 32), top = wave_max_u32(hi);
+    const u64 at = __builtin_amdgcn_ballot_w64(hi == top);
+    uint32_t lo;
+    if ((at & (at - 1ull)) == 0ull)
+        lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, __ffsll((long long)at) - 1);
+    else
+        lo = wave_max_u32(hi == top ? (uint32_t)v : 0u);
+    return ((u64)top << 32) | lo;
+}
+
 __device__ __forceinline__ u64 wave_or_u64(u64 v) {
 #define DOCK_OR_STEP(C, R) v |= dpp_read64<C, R>(v);
     DOCK_DPP_STEPS(DOCK_OR_STEP)
@@ -92,6 +117,14 @@ __device__ __forceinline__ u64 wave_or_u64(u64 v) {
 #undef DOCK_DPP_STEPS
 
 __device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// A wave-uniform value read from memory or LDS, as a scalar: masks, counts and loop
+// bounds derived from it then stay in scalar registers.
+__device__ __forceinline__ u64 uniform_u64(u64 v) {
+    const uint32_t lo = (uint32_t)uniform_int((int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)uniform_int((int)(uint32_t)(v >> 32));
+    return ((u64)hi << 32) | lo;
+}
 
 __device__ __forceinline__ float read_lane(float v, int lane) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
@@ -229,10 +262,12 @@ __device__ __forceinline__ float ball_radius(float r2) { return __builtin_amdgcn
 
 // Whether the ball of radius rad (grid units) about (cx,cy,cz), widened by
 // kInsideMargin, stays inside [0, n-2] on every axis.
-__device__ __forceinline__ bool ball_inside(const Tri &t, float cx, float cy, float cz, float rad) {
+template <class G>  // Tri or GridArgs
+__device__ __forceinline__ bool ball_inside(const G &t, float cx, float cy, float cz, float rad) {
     const float r = rad + kInsideMargin;
-    return cx - r >= 0.0f && cy - r >= 0.0f && cz - r >= 0.0f && cx + r <= t.m2x &&
-           cy + r <= t.m2y && cz + r <= t.m2z;
+    // (all six at once, no branches)
+    return (cx - r >= 0.0f) & (cy - r >= 0.0f) & (cz - r >= 0.0f) & (cx + r <= t.m2x) &
+           (cy + r <= t.m2y) & (cz + r <= t.m2z);
 }
 
 // Bilinear coefficients of the (y,z) face at x vertex i of cell (j,k): from
@@ -358,7 +393,7 @@ __device__ __forceinline__ void apply_align(Pose<NS> &Y, int n, int o, const Sea
 struct WaveSplit {
     __device__ __forceinline__ int first() const { return 0; }
     __device__ __forceinline__ int stride() const { return 64; }
-    __device__ __forceinline__ u64 reduce(u64 k) const { return wave_max_u64(k); }
+    __device__ __forceinline__ u64 reduce(u64 k) const { return wave_max_key(k); }
 };
 
 struct BlockSplit {
@@ -367,7 +402,7 @@ struct BlockSplit {
     __device__ __forceinline__ int first() const { return 64 * wave; }
     __device__ __forceinline__ int stride() const { return 64 * waves; }
     __device__ __forceinline__ u64 reduce(u64 k) const {
-        k = wave_max_u64(k);
+        k = wave_max_key(k);
         if (lane_id() == 0) slots[wave] = k;
         __syncthreads();
         u64 r = slots[0];
@@ -618,116 +653,313 @@ __device__ __forceinline__ u64 score_free_any(int nfree, const uint16_t *cand, c
     return score_free<C, Inside>(nfree, cand, rec, m, tors, tr);
 }
 
+// The kernel's arguments, to be loaded again: read through this reference a value
+// is live from its first to its last use in the phase that took the reference.
+// (Kept from the kernel's start, the arguments of all phases together overflow the
+// scalar registers and are spilled to vector lanes, a VALU instruction each way.)
+__device__ __forceinline__ const DockArgs &fresh_args() {
+    auto p = (const __attribute__((address_space(4))) DockArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const DockArgs *)p;
+}
+
+__device__ __forceinline__ u64 ballot(bool v) { return __builtin_amdgcn_ballot_w64(v); }
+// The lane's bit of a wave-uniform mask, and the number of lower lanes set in it.
+__device__ __forceinline__ bool inverse_ballot(u64 m) {
+    return __builtin_amdgcn_inverse_ballot_w64(m);
+}
+__device__ __forceinline__ int mbcnt(u64 m) {
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                          __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Scratch of the bump check, in the LDS of the candidate list that follows it.
+// Pairs of a slot up to which their terms are read from their lanes (7 VALU a pair)
+// rather than through LDS (3 a pair and 10 to lay them out).
+#ifndef KFEW
+#define KFEW 3
+#endif
+constexpr int kBumpFew = KFEW;
+// Moving atoms up to which a decision tests each row's pairs as they are found.  More
+// rows are listed first: finding a pair then costs less (10 VALU a row instead of 25),
+// a list costs about 120 more.  Torsion sweep of 2,500 ligands of 20-80 atoms and of
+// 6,000 of 16 atoms: 22.8 and 11.4 ms with every decision direct, 22.0 and 12.2 ms with
+// every decision listed, 21.3 and 11.4 ms with the line at 4 (21.5 and 11.8 ms at 2,
+// 21.3 and 11.4 ms at 8).
+constexpr int kBumpDirect = 4;
+struct BumpLds {
+    float4 coef[64];                // (Cq, Aq, Bq, 0) of pairs
+    uint16_t pair[64 + kMaxAtoms];  // pairs: moving row << 8 | static atom
+};
+static_assert(sizeof(BumpLds) <= kMaxTorsionSteps * 2, "bump scratch fits the candidate list");
+
+// Tests up to 64 listed pairs (lane p: pair p of np) against the candidates.  For
+// moving atom i (frame P0, V, W) and static atom j, the squared distance after a
+// turn by theta is
+//   d2(theta) = Cq + Aq cos(theta) + Bq sin(theta),
+//   Cq = |P0 - Y_j|^2 + |V|^2, Aq = 2 (P0 - Y_j).V, Bq = 2 (P0 - Y_j).W
+// (V and W are orthogonal with |V| = |W|).  Its minimum over theta is
+// Cq - sqrt(Aq^2 + Bq^2); pairs that cannot come closer than the bump distance are
+// dropped.  Over a slot's arc the extremes of Aq cos + Bq sin are +-sqrt(Aq^2 +
+// Bq^2) inside the arc or the values at its ends: a slot that some pair bumps from
+// end to end is done, and only pairs that reach into a slot are tested against its
+// candidates, with two FMAs each.  (mg: above the roundings of both.)  On random trees
+// of 20-100 atoms 18 pairs a decision are listed and 21 (pair, slot) tests are left of
+// 73, 0.46 slots being done without one.  Sweep of 16,000 such ligands: 225 ms with
+// every pair tested against every candidate, 198 ms so; bound by issue (VALU 0.8 busy,
+// SALU 0.5).  Without pruning (300 ligands of 64 atoms): 38.2 -> 22.0 ms, since a pair's
+// terms are read through LDS (no VALU) instead of lane by lane.
+template <int NS, int C>
+__device__ __forceinline__ void bump_pairs(int np, const uint16_t *pair, BumpLds *bl,
+                                           const float4 *rec,
+                                           const float (&sgx)[NS], const float (&sgy)[NS],
+                                           const float (&sgz)[NS], const float2 (&cs)[C],
+                                           int first, int stride, const TorsionArgs &k,
+                                           u64 (&bumped)[C]) {
+    const float lim = k.lim;
+    const int lane = lane_id();
+    const int e = pair[lane < np ? lane : 0];
+    const int q = e >> 8, j = e & 255;
+    const float4 r0 = rec[3 * q + 0], r1 = rec[3 * q + 1], r2 = rec[3 * q + 2];
+    auto pick = [&](const float (&v)[NS]) -> float {
+        float x = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (j & 63), __float_as_int(v[0])));
+#pragma unroll
+        for (int s = 1; s < NS; ++s) {
+            const float y =
+                __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (j & 63), __float_as_int(v[s])));
+            x = (j >> 6) == s ? y : x;
+        }
+        return x;
+    };
+    const float dx = r0.x - pick(sgx), dy = r0.y - pick(sgy), dz = r0.z - pick(sgz);
+    const float vv = fmaf(r1.x, r1.x, fmaf(r1.y, r1.y, r1.z * r1.z));
+    const float cq = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, vv)));
+    const float aq = 2.0f * fmaf(dx, r1.x, fmaf(dy, r1.y, dz * r1.z));
+    const float bq = 2.0f * fmaf(dx, r2.x, fmaf(dy, r2.y, dz * r2.z));
+    const u64 live = np >= 64 ? ~0ull : (1ull << np) - 1ull;
+    if (!k.prune) {
+        bl->coef[lane] = make_float4(cq, aq, bq, 0.0f);
+        wave_lds_sync();
+        for (int p = 0; p < np; p += 4) {  // (lanes past np hold the first pair again)
+            const float4 *t = bl->coef + p;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    bumped[c] |= ballot(fmaf(t[u].z, cs[c].y, fmaf(t[u].y, cs[c].x, t[u].x)) < lim);
+        }
+        wave_lds_sync();
+        return;
+    }
+    const float lim_in = lim * (1.0f + 1e-4f);  // filter margin: keeps borderline pairs
+    const float d = cq - lim_in;
+    const u64 in = live & (ballot(d < 0.0f) | ballot(d * d < fmaf(aq, aq, bq * bq)));
+    const float mg = 4e-6f * (cq + fabsf(aq) + fabsf(bq));
+    const float room = cq - lim;  // d2 < lim where Aq cos + Bq sin < -room
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const float2 mid = k.mid[(first + stride * c) >> 6];
+        const float v = fmaf(aq, mid.x, bq * mid.y);            // at the middle
+        const float s = fabsf(fmaf(bq, mid.x, -(aq * mid.y)));  // |slope| there
+        const float vt = v * k.tw, ends = fmaf(v, k.cw, room), lift = fmaf(s, k.sw, k.sb);
+        const u64 peak = ballot(s <= vt), dip = ballot(s <= -vt);  // inside the arc
+        const u64 whole = in & ~peak & ballot(ends + lift < -mg);
+        const u64 hit = in & (dip | ballot(ends - lift < mg));
+        if (whole != 0ull) bumped[c] = ~0ull;
+        if (bumped[c] == ~0ull) continue;
+        // the pairs that reach into the slot first, the others' places with one that
+        // bumps nothing; then four at a time
+        const int cnt = __popcll(hit);
+        const bool mine = inverse_ballot(hit);
+        const int at = mine ? mbcnt(hit) : cnt + mbcnt(~hit);
+        bl->coef[at] = make_float4(mine ? cq : 3e38f, mine ? aq : 0.0f, mine ? bq : 0.0f, 0.0f);
+        wave_lds_sync();
+        for (int p = 0; p < cnt; p += 4) {
+            const float4 *t = bl->coef + p;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                bumped[c] |= ballot(fmaf(t[u].z, cs[c].y, fmaf(t[u].y, cs[c].x, t[u].x)) < lim);
+        }
+        wave_lds_sync();
+    }
+}
+
 template <int NS, int C, class Split>
 __device__ int torsion_decide(Pose<NS> &Y, int n, const u64 *mrow, int a, int b,
                               const u64 *far, const int (&toff)[NS], float4 *rec,
-                              uint16_t *cand, const float2 (&cs)[C], const Tri &tr,
-                              const GridArgs &g, const SearchArgs &sa, const Split &sp,
+                              uint16_t *cand, const float2 (&cs)[C], const Split &sp,
                               long long &nscored) {
     const int lane = lane_id();
+    const TorsionArgs &g = fresh_args().t;
     const Axis A = bond_axis(Y, a, b);
     u64 mw[NS];
     int m = 0;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-        mw[s] = mrow[s];
+        mw[s] = uniform_u64(mrow[s]);
         m += __popcll(mw[s]);
     }
     // moving-atom frames -> LDS (grid units), static atoms -> registers
     float sgx[NS], sgy[NS], sgz[NS];
-    bool st[NS];
-    bool out_any = false;  // a moving atom's circle leaves [0, n-2]
+    float hgt[NS], rad[NS];  // height along the axis and distance from it, grid units
+    u64 stm[NS];             // static atoms of each slot as wave masks (bit = lane)
+    bool out_any = false;    // a moving atom's circle leaves [0, n-2]
     int before = 0;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         const int i = lane + 64 * s;
-        const bool mv = (mw[s] >> lane) & 1ull;
-        st[s] = !mv && i < n;
+        const bool mv = inverse_ballot(mw[s]);
+        const int left = n - 64 * s;  // atoms of this slot
+        stm[s] = ~mw[s] & (left >= 64 ? ~0ull : left > 0 ? (1ull << left) - 1ull : 0ull);
         sgx[s] = (Y.x[s] - g.ox) * g.inv_h;
         sgy[s] = (Y.y[s] - g.oy) * g.inv_h;
         sgz[s] = (Y.z[s] - g.oz) * g.inv_h;
+        float px, py, pz, vx, vy, vz, wx, wy, wz;
+        torsion_frame(A, Y.x[s], Y.y[s], Y.z[s], px, py, pz, vx, vy, vz, wx, wy, wz);
+        rad[s] = ball_radius(fmaf(vx, vx, fmaf(vy, vy, vz * vz))) * g.inv_h;
+        hgt[s] = fmaf(A.ux, Y.x[s] - A.ax, fmaf(A.uy, Y.y[s] - A.ay, A.uz * (Y.z[s] - A.az))) * g.inv_h;
+        const int q = before + mbcnt(mw[s]);
         if (mv) {
-            float px, py, pz, vx, vy, vz, wx, wy, wz;
-            torsion_frame(A, Y.x[s], Y.y[s], Y.z[s], px, py, pz, vx, vy, vz, wx, wy, wz);
-            const int q = before + (int)__builtin_amdgcn_mbcnt_hi(
-                                       (uint32_t)(mw[s] >> 32),
-                                       __builtin_amdgcn_mbcnt_lo((uint32_t)mw[s], 0u));
             rec[3 * q + 0] = make_float4((px - g.ox) * g.inv_h, (py - g.oy) * g.inv_h,
                                          (pz - g.oz) * g.inv_h, __int_as_float(toff[s]));
             rec[3 * q + 1] = make_float4(vx * g.inv_h, vy * g.inv_h, vz * g.inv_h,
                                          __int_as_float(i));
             // every candidate of this atom lies on the circle of radius |V| about P0
-            const bool in = ball_inside(tr, (px - g.ox) * g.inv_h, (py - g.oy) * g.inv_h,
-                                        (pz - g.oz) * g.inv_h,
-                                        ball_radius(fmaf(vx, vx, fmaf(vy, vy, vz * vz))) * g.inv_h);
+            const bool in = ball_inside(g, (px - g.ox) * g.inv_h, (py - g.oy) * g.inv_h,
+                                        (pz - g.oz) * g.inv_h, rad[s]);
             rec[3 * q + 2] = make_float4(wx * g.inv_h, wy * g.inv_h, wz * g.inv_h, 0.f);
             out_any = out_any || !in;
         }
         before += __popcll(mw[s]);
     }
-    const bool all_in = __ballot(out_any) == 0ull;
-    wave_lds_sync();
+    const bool all_in = ballot(out_any) == 0ull;
 
-    // Bump Check of every candidate at once.  For moving atom i (frame P0, V, W)
-    // and static atom j, the squared distance after a turn by theta is
-    //   d2(theta) = Cq + Aq cos(theta) + Bq sin(theta),
-    //   Cq = |P0 - Y_j|^2 + |V|^2, Aq = 2 (P0 - Y_j).V, Bq = 2 (P0 - Y_j).W
-    // (V and W are orthogonal with |V| = |W|).  Its minimum over theta is
-    // Cq - sqrt(Aq^2 + Bq^2); pairs that cannot come closer than the bump distance
-    // are skipped, and each remaining pair is tested against every candidate of
-    // the lane with two FMAs.  Distances are in grid units.
-    // bumped candidates as wave masks (bit = lane) per candidate slot c
+    // Bump Check of every candidate at once: bumped candidates as wave masks (bit =
+    // lane) per candidate slot c.  A moving and a static atom come closest to
+    // each other at (height difference, radius difference) about the axis; pairs that
+    // may come within the bump distance are listed, and the list is tested 64 pairs
+    // at a time, a lane per pair (bump_pairs).  The filter's limit is above what
+    // the roundings of both forms of the distance can differ by (Cq is up to about
+    // (2 |V|)^2, its terms round at 2^-24 of that).
     u64 bumped[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) bumped[c] = 0ull;
-    const float lim = sa.bump2g;
-    const float lim_in = lim * (1.0f + 1e-4f);  // filter margin: keeps borderline pairs
-    // static atoms of each slot as wave masks (bit = lane)
-    u64 stm[NS];
+    const float lim = g.lim;
+    const u64 every = g.prune ? 0ull : ~0ull;
+    BumpLds *bl = (BumpLds *)cand;
+    // (a moving atom within the bump distance of the lane's is at most twice as far
+    // from the axis atom, and a bump distance)
+    float reach[NS];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) stm[s] = __ballot(st[s]);
-    for (int q = 0; q < m; ++q) {
-        const float4 r0 = rec[3 * q + 0], r1 = rec[3 * q + 1], r2 = rec[3 * q + 2];
-        const int i = uniform_int(__float_as_int(r1.w));
-        const float vv = fmaf(r1.x, r1.x, fmaf(r1.y, r1.y, r1.z * r1.z));
+    for (int s = 0; s < NS; ++s)
+        reach[s] = fmaf(lim, 1.0f + 2e-3f,
+                        fmaf(fmaf(rad[s], rad[s], hgt[s] * hgt[s]), 1e-4f, 1e-3f));
+    wave_lds_sync();  // the frames
+    // the moving atoms in order: their bits, and each one's far row a step ahead
+    int q = 0, sw = 0;
+    u64 bits = mw[0];
+    auto next_atom = [&]() -> int {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            // static atoms of slot s at least bmin bonds from moving atom i
-            const u64 elm = far[i * NS + s] & stm[s];
-            if (elm == 0ull) continue;
-            const float dx = r0.x - sgx[s], dy = r0.y - sgy[s], dz = r0.z - sgz[s];
-            const float cq = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, vv)));
-            const float aq = 2.0f * fmaf(dx, r1.x, fmaf(dy, r1.y, dz * r1.z));
-            const float bq = 2.0f * fmaf(dx, r2.x, fmaf(dy, r2.y, dz * r2.z));
-            const float e = cq - lim_in;
-            u64 bal = sa.prune ? elm & (__builtin_amdgcn_ballot_w64(e < 0.0f) |
-                                        __builtin_amdgcn_ballot_w64(e * e < fmaf(aq, aq, bq * bq)))
-                               : elm;
-            while (bal != 0ull) {
-                const int src = __ffsll((long long)bal) - 1;
-                bal &= bal - 1ull;
-                const float c0 = read_lane(cq, src), a0 = read_lane(aq, src),
-                            b0 = read_lane(bq, src);
-#pragma unroll
-                for (int c = 0; c < C; ++c)
-                    bumped[c] |= __ballot(fmaf(b0, cs[c].y, fmaf(a0, cs[c].x, c0)) < lim);
+        for (int s = 1; s < NS; ++s)
+            if (bits == 0ull && sw < s) {
+                sw = s;
+                bits = mw[s];
             }
+        const int l = bits != 0ull ? __ffsll((long long)bits) - 1 : 0;
+        bits &= bits - 1ull;
+        return l + 64 * sw;
+    };
+    int i = next_atom();
+    u64 fw[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) fw[s] = far[i * NS + s];
+    if (m <= kBumpDirect && every == 0ull) {
+        for (; q < m; ++q) {
+            const float4 r0 = rec[3 * q + 0], r1 = rec[3 * q + 1], r2 = rec[3 * q + 2];
+            u64 fi[NS];
+            i = next_atom();
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                fi[s] = fw[s];
+                fw[s] = far[i * NS + s];
+            }
+            const float vv = fmaf(r1.x, r1.x, fmaf(r1.y, r1.y, r1.z * r1.z));
+            const float lim_in = lim * (1.0f + 1e-4f);
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const u64 elm = uniform_u64(fi[s]) & stm[s];
+                if (elm == 0ull) continue;
+                const float dx = r0.x - sgx[s], dy = r0.y - sgy[s], dz = r0.z - sgz[s];
+                const float cq = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, vv)));
+                const float aq = 2.0f * fmaf(dx, r1.x, fmaf(dy, r1.y, dz * r1.z));
+                const float bq = 2.0f * fmaf(dx, r2.x, fmaf(dy, r2.y, dz * r2.z));
+                const float e = cq - lim_in;
+                u64 bal = elm & (ballot(e < 0.0f) | ballot(e * e < fmaf(aq, aq, bq * bq)));
+                while (bal != 0ull) {
+                    const int p = __ffsll((long long)bal) - 1;
+                    bal &= bal - 1ull;
+                    const float c0 = read_lane(cq, p), a0 = read_lane(aq, p), b0 = read_lane(bq, p);
+#pragma unroll
+                    for (int c = 0; c < C; ++c)
+                        bumped[c] |= ballot(fmaf(b0, cs[c].y, fmaf(a0, cs[c].x, c0)) < lim);
+                }
+            }
+        }
+    }
+    int np = 0;
+    while (q < m || np > 0) {
+        while (q < m && np < 64) {
+            float hi = read_lane(hgt[0], i & 63), ri = read_lane(rad[0], i & 63);
+#pragma unroll
+            for (int s = 1; s < NS; ++s)
+                if ((i >> 6) == s) {
+                    hi = read_lane(hgt[s], i & 63);
+                    ri = read_lane(rad[s], i & 63);
+                }
+            u64 fi[NS];
+            i = next_atom();
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                fi[s] = fw[s];
+                fw[s] = far[i * NS + s];
+            }
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                // static atoms of slot s at least bmin bonds from the moving atom
+                const float dh = hgt[s] - hi, dr = rad[s] - ri;
+                const u64 near = every | ballot(fmaf(dh, dh, dr * dr) < reach[s]);
+                const u64 bal = uniform_u64(fi[s]) & stm[s] & near;
+                if (bal == 0ull) continue;
+                if (inverse_ballot(bal))
+                    bl->pair[np + mbcnt(bal)] = (uint16_t)((q << 8) | (lane + 64 * s));
+                np += __popcll(bal);
+            }
+            ++q;
+        }
+        if (np > 0) {
+            const int cnt = np < 64 ? np : 64;
+            np -= cnt;
+            wave_lds_sync();
+            bump_pairs<NS, C>(cnt, bl->pair + np, bl, rec, sgx, sgy, sgz, cs, sp.first(),
+                              sp.stride(), g, bumped);
         }
     }
     // Only the bump-free candidates are scored (on the paper's workloads more than
     // half are bumped): list them for this wave, then score the list.  Without
     // pruning every candidate is listed and scored, the bumped ones flagged.
+    const DockArgs &ks = fresh_args();
+    const TorsionArgs &sa = ks.t;
+    const Tri tr = make_tri(ks.g);
     int nfree = 0;
+    const u64 flagged = sa.prune ? 0ull : ~0ull;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-        const int k = sp.first() + lane + sp.stride() * c;
-        const bool bmp = (bumped[c] >> lane) & 1ull;
-        const bool listed = k < sa.T && (!sa.prune || !bmp);
-        const u64 bm = __ballot(listed);
-        if (listed)
-            cand[nfree + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bm >> 32),
-                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)bm, 0u))] =
-                (uint16_t)(bmp ? k | kCandBumped : k);
+        const int k0 = sp.first() + sp.stride() * c, left = sa.T - k0;
+        const u64 real = left >= 64 ? ~0ull : left > 0 ? (1ull << left) - 1ull : 0ull;
+        const u64 bm = real & (~bumped[c] | flagged);
+        if (inverse_ballot(bm))
+            cand[nfree + mbcnt(bm)] =
+                (uint16_t)(k0 + lane + (inverse_ballot(bumped[c]) ? kCandBumped : 0));
         nfree += __popcll(bm);
     }
     wave_lds_sync();
@@ -740,7 +972,7 @@ __device__ int torsion_decide(Pose<NS> &Y, int n, const u64 *mrow, int a, int b,
     const int kstar = best == 0ull ? (int)kTraceNone : (int)key_index(best);
     wave_lds_sync();  // rec is rewritten next
     if (kstar != (int)kTraceNone) {
-        const float2 t = sa.tors[kstar];
+        const float2 t = ld_cs((cfloat2_p)sa.tors, uniform_int(kstar));
         apply_torsion(Y, mrow, A, t.x, t.y);  // the pose is unchanged since A was taken
     }
     return kstar;
@@ -844,10 +1076,9 @@ static __device__ __forceinline__ size_t trace_base(const LibArgs &lib, const Se
 // Docking kernel: persistent workgroups pop (ligand, restart-group) items of one
 // size bin; each wave docks one restart from the orientation k_align chose.
 template <int NS, int C>
-__global__ __launch_bounds__(512) void k_dock(GridArgs g, SearchArgs sa, LibArgs lib, WorkArgs ws,
-                                              int bin, int lst) {
+__global__ __launch_bounds__(512, C <= 4 ? (NS == 1 ? 5 : 4) : 2) void k_dock(DockArgs args) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int nmax = bin_nmax(bin);
+    const int nmax = bin_nmax(args.bin), lst = args.lst;
     const int W = blockDim.x >> 6, wave = threadIdx.x >> 6, lane = lane_id();
     float4 *xyzt = (float4 *)(smem + Lds::xyzt(nmax));
     const u64 *far = (const u64 *)(smem + Lds::far(nmax));
@@ -856,21 +1087,24 @@ __global__ __launch_bounds__(512) void k_dock(GridArgs g, SearchArgs sa, LibArgs
     int *misc = (int *)(smem + Lds::misc(nmax, NS));
     float4 *rec = (float4 *)(smem + Lds::rec(nmax, NS) + (size_t)wave * Lds::rec_stride(nmax));
     uint16_t *cand = (uint16_t *)((unsigned char *)rec + Lds::cand(nmax));
-    const Tri tr = make_tri(g);
-
     float2 cs[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         const int k = lane + 64 * c;
-        cs[c] = k < sa.T ? sa.tors[k] : make_float2(1.f, 0.f);
+        cs[c] = k < args.sa.T ? args.sa.tors[k] : make_float2(1.f, 0.f);
     }
-    const int groups = (sa.R + W - 1) / W;
-    const long long total = (long long)ws.counters[lst] * groups;
+    const int groups = (args.sa.R + W - 1) / W;
+    const long long total = (long long)args.ws.counters[lst] * groups;
     int cur = -1;
     for (;;) {
+        const DockArgs &k = fresh_args();
+        const GridArgs &g = k.g;
+        const SearchArgs &sa = k.sa;
+        const LibArgs &lib = k.lib;
+        const WorkArgs &ws = k.ws;
         if (threadIdx.x == 0) misc[0] = atomicAdd(&ws.counters[kMaxLists + lst], 1);
         __syncthreads();
-        const int item = misc[0];
+        const int item = uniform_int(misc[0]);
         if ((long long)item >= total) break;
         const int li = item / groups, grp = item - li * groups;
         const int l = ws.bin_list[(size_t)lst * lib.L + li];
@@ -879,9 +1113,9 @@ __global__ __launch_bounds__(512) void k_dock(GridArgs g, SearchArgs sa, LibArgs
             cur = l;
         }
         __syncthreads();
-        const int r = grp * W + wave;
+        const int r = grp * W + uniform_int(wave);
         if (r < sa.R) {
-            const int n = misc[1], B = misc[2];
+            const int n = uniform_int(misc[1]), B = uniform_int(misc[2]);
             int toff[NS];
             lane_toff(xyzt, n, toff);
             Pose<NS> Y;
@@ -896,14 +1130,15 @@ __global__ __launch_bounds__(512) void k_dock(GridArgs g, SearchArgs sa, LibArgs
                 for (int b = 0; b < B; ++b, ++d) {
                     const int2 ab = rot[b];
                     const int k = torsion_decide<NS, C>(Y, n, mask + b * NS, uniform_int(ab.x),
-                                                        uniform_int(ab.y), far, toff, rec, cand,
-                                                        cs, tr, g, sa, WaveSplit(), nsc);
+                                                        uniform_int(ab.y), far, toff, rec,
+                                                        cand, cs, WaveSplit(), nsc);
                     if (lane == 0) tr_out[d] = (uint16_t)k;
                 }
             }
-            if (ws.scored && lane == 0) atomicAdd(ws.scored, (unsigned long long)nsc);
-            const float sc = pose_score(Y, n, toff, tr, g);
-            if (lane == 0) ws.rscore[(size_t)l * sa.R + r] = sc;
+            const DockArgs &ke = fresh_args();
+            if (ke.ws.scored && lane == 0) atomicAdd(ke.ws.scored, (unsigned long long)nsc);
+            const float sc = pose_score(Y, n, toff, make_tri(ke.g), ke.g);
+            if (lane == 0) ke.ws.rscore[(size_t)l * ke.sa.R + r] = sc;
         }
         __syncthreads();
     }
@@ -1960,16 +2195,6 @@ __device__ __forceinline__ uint32_t add_low24(uint32_t x, int c) {
     return r;
 }
 
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-    v = max(v, (uint32_t)dpp_read<0x111, 0xF>((int)v));
-    v = max(v, (uint32_t)dpp_read<0x112, 0xF>((int)v));
-    v = max(v, (uint32_t)dpp_read<0x114, 0xF>((int)v));
-    v = max(v, (uint32_t)dpp_read<0x118, 0xF>((int)v));
-    v = max(v, (uint32_t)dpp_read<0x142, 0xA>((int)v));
-    v = max(v, (uint32_t)dpp_read<0x143, 0xC>((int)v));
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
-
 // Shared memory of k_align_bound (bytes).
 constexpr int kBoundWaves = 4;                     // waves per workgroup
 constexpr int kBoundPerWave = 2;                   // restarts per wave: 60 strips in 64 lanes
@@ -2362,7 +2587,7 @@ __global__ __launch_bounds__(64 * kBoundWaves, 4) void k_align_bound(GridArgs g,
             else score_listed<false>(cand, nc, dxyz, n, r, cw, ce, tr, g, sa, best);
 #pragma unroll
             for (int k = 0; k < kBoundPerWave; ++k) {
-                const u64 bk = wave_max_u64(best[k]);
+                const u64 bk = wave_max_key(best[k]);
                 if (lane == 0 && rbase + k < sa.R)
                     ws.rtrace[trace_base(lib, sa, l) + (size_t)(rbase + k) * (1 + sa.P * B)] =
                         (uint16_t)key_index(bk);
@@ -2376,12 +2601,15 @@ __global__ __launch_bounds__(64 * kBoundWaves, 4) void k_align_bound(GridArgs g,
 // restart r; its waves split the orientations and the torsion candidates and
 // agree on every decision through LDS and workgroup barriers.
 template <int NS, int C>
-__global__ __launch_bounds__(256) void k_plain(GridArgs g, SearchArgs sa, LibArgs lib, WorkArgs ws,
-                                               const int *__restrict__ status, int l, int bin) {
+__global__ __launch_bounds__(256) void k_plain(DockArgs args) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int nmax = bin_nmax(bin);
-    const int W = blockDim.x >> 6, wave = threadIdx.x >> 6, lane = lane_id();
-    if (status[l] != 0) return;
+    const GridArgs &g = args.g;
+    const SearchArgs &sa = args.sa;
+    const LibArgs &lib = args.lib;
+    const WorkArgs &ws = args.ws;
+    const int l = args.lig, nmax = bin_nmax(args.bin);
+    const int W = blockDim.x >> 6, wave = uniform_int((int)(threadIdx.x >> 6)), lane = lane_id();
+    if (args.status[l] != 0) return;
     float4 *xyzt = (float4 *)(smem + Lds::xyzt(nmax));
     const u64 *far = (const u64 *)(smem + Lds::far(nmax));
     const u64 *mask = (const u64 *)(smem + Lds::mask(nmax, NS));
@@ -2401,7 +2629,7 @@ __global__ __launch_bounds__(256) void k_plain(GridArgs g, SearchArgs sa, LibArg
     stage_ligand<NS>(smem, nmax, l, lib, ws, g, true);
     __syncthreads();
     const int r = blockIdx.x;
-    const int n = misc[1], B = misc[2];
+    const int n = uniform_int(misc[1]), B = uniform_int(misc[2]);
     int toff[NS];
     lane_toff(xyzt, n, toff);
     Pose<NS> Y;
@@ -2416,8 +2644,8 @@ __global__ __launch_bounds__(256) void k_plain(GridArgs g, SearchArgs sa, LibArg
         for (int b = 0; b < B; ++b, ++d) {
             const int2 ab = rot[b];
             const int k = torsion_decide<NS, C>(Y, n, mask + b * NS, uniform_int(ab.x),
-                                                uniform_int(ab.y), far, toff, rec, cand, cs, tr,
-                                                g, sa, sp, nsc);
+                                                uniform_int(ab.y), far, toff, rec, cand, cs,
+                                                sp, nsc);
             if (writer) tr_out[d] = (uint16_t)k;
         }
     }
@@ -3294,6 +3522,30 @@ hipError_t launch_prep_one(const GridArgs &g, const SearchArgs &sa, const LibArg
 
 size_t plain_lds_bytes(int nmax, int waves) { return dock_lds_bytes(nmax, waves) + (size_t)waves * 8; }
 
+static TorsionArgs torsion_args(const GridArgs &g, const SearchArgs &sa) {
+    TorsionArgs t{};
+    t.inv_h = g.inv_h;
+    t.ox = g.ox; t.oy = g.oy; t.oz = g.oz;
+    t.m2x = g.m2x; t.m2y = g.m2y; t.m2z = g.m2z;
+    t.lim = sa.bump2g;
+    t.T = sa.T;
+    t.prune = sa.prune;
+    t.tors = sa.tors;
+    // a slot's candidates lie within 32 steps of its 33rd, and a step more
+    const double step = 2.0 * M_PI / sa.T, w = 33.0 * step;
+    if (w < 0.99 * M_PI / 2.0) {
+        t.cw = (float)std::cos(w);
+        t.sw = (float)std::sin(w);
+        t.tw = (float)std::tan(w);
+    } else {
+        t.sb = 3e38f;
+    }
+    for (int q = 0; q < kMaxTorsionSteps / 64; ++q)
+        t.mid[q] = make_float2((float)std::cos((64.0 * q + 32.0) * step),
+                               (float)std::sin((64.0 * q + 32.0) * step));
+    return t;
+}
+
 template <int NS, int C>
 static hipError_t launch_plain_t(int l, int bin, int waves, const GridArgs &g,
                                  const SearchArgs &sa, const LibArgs &lib, const WorkArgs &ws,
@@ -3301,8 +3553,8 @@ static hipError_t launch_plain_t(int l, int bin, int waves, const GridArgs &g,
     const size_t lds = plain_lds_bytes(bin_nmax(bin), waves);
     hipFuncSetAttribute((const void *)k_plain<NS, C>, hipFuncAttributeMaxDynamicSharedMemorySize,
                         (int)lds);
-    hipLaunchKernelGGL((k_plain<NS, C>), dim3(sa.R), dim3(64 * waves), lds, s, g, sa, lib, ws,
-                       (const int *)out.status, l, bin);
+    const DockArgs a{torsion_args(g, sa), g, sa, lib, ws, (const int *)out.status, bin, 0, l};
+    hipLaunchKernelGGL((k_plain<NS, C>), dim3(sa.R), dim3(64 * waves), lds, s, a);
     return hipGetLastError();
 }
 
@@ -3334,8 +3586,8 @@ static hipError_t launch_dock_t(int bin, int lst, int blocks, int waves, const G
     const size_t lds = dock_lds_bytes(bin_nmax(bin), waves);
     hipFuncSetAttribute((const void *)k_dock<NS, C>, hipFuncAttributeMaxDynamicSharedMemorySize,
                         (int)lds);
-    hipLaunchKernelGGL((k_dock<NS, C>), dim3(blocks), dim3(64 * waves), lds, s, g, sa, lib, ws, bin,
-                       lst);
+    const DockArgs a{torsion_args(g, sa), g, sa, lib, ws, nullptr, bin, lst, 0};
+    hipLaunchKernelGGL((k_dock<NS, C>), dim3(blocks), dim3(64 * waves), lds, s, a);
     return hipGetLastError();
 }
 

@@ -129,6 +129,33 @@ struct ContactArgs {
     float dc2;               // contact distance squared
 };
 
+// What a torsion decision reads of the grid and the search, side by side: a few wide
+// scalar loads (see fresh_args in dock_device.hip).  A slot of 64 consecutive
+// candidates is an arc about its 33rd of half width w (a step of margin); arcs of
+// half a turn and more have cw = sw = tw = 0 and sb so large that nothing is told
+// of them (see bump_pairs).
+struct TorsionArgs {
+    float inv_h, ox, oy, oz;
+    float m2x, m2y, m2z, lim;  // lim: (bump_dist / spacing)^2
+    float cw, sw, tw, sb;      // cos w, sin w, tan w, 0
+    int T, prune;
+    const float2 *tors;
+    float2 mid[kMaxTorsionSteps / 64];  // (cos, sin) of each slot's middle
+};
+
+// Arguments of the docking kernels (k_dock, k_plain), as they lie in the kernel's
+// argument segment.
+struct DockArgs {
+    TorsionArgs t;
+    GridArgs g;
+    SearchArgs sa;
+    LibArgs lib;
+    WorkArgs ws;
+    const int *status;  // k_plain
+    int bin, lst;       // k_dock: atom bin, work list
+    int lig;            // k_plain: the ligand
+};
+
 struct OutArgs {
     float *best;
     int *npose;
