@@ -1107,7 +1107,7 @@ __global__ __launch_bounds__(512, C <= 4 ? (NS == 1 ? 5 : 4) : 2) void k_dock(Do
         const int item = uniform_int(misc[0]);
         if ((long long)item >= total) break;
         const int li = item / groups, grp = item - li * groups;
-        const int l = ws.bin_list[(size_t)lst * lib.L + li];
+        const int l = ws.bin_list[li];
         if (l != cur) {
             stage_ligand<NS>(smem, nmax, l, lib, ws, g, true);
             cur = l;
@@ -1773,7 +1773,7 @@ __global__ __launch_bounds__(1024) void k_align(GridArgs g, SearchArgs sa, LibAr
         __syncthreads();
         const int li = misc[0], grp = misc[1];
         if (li < 0) break;
-        const int l = ws.bin_list[(size_t)lst * lib.L + li];
+        const int l = ws.bin_list[li];
         const int a0 = lib.atom_off[l], n = lib.atom_off[l + 1] - a0;
         const int B = lib.rot_off[l + 1] - lib.rot_off[l];
         const int rbase = grp * GR;
@@ -2351,7 +2351,7 @@ __global__ __launch_bounds__(64 * kBoundWaves, 4) void k_align_bound(GridArgs g,
         __syncthreads();
         const int li = uniform_int(misc[0]), grp = uniform_int(misc[1]);
         if (li < 0) break;
-        const int l = ws.bin_list[(size_t)lst * lib.L + li];
+        const int l = ws.bin_list[li];
         const int a0 = lib.atom_off[l], n = lib.atom_off[l + 1] - a0;
         const int B = lib.rot_off[l + 1] - lib.rot_off[l];
         for (int i = tid; i < n; i += 64 * kBoundWaves) {
@@ -2754,7 +2754,7 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
             __syncthreads();
             const int li = misc[0];
             if (li >= ws.counters[lst]) break;
-            l = ws.bin_list[(size_t)lst * lib.L + li];
+            l = ws.bin_list[li];
         }
         stage_ligand<NS>(smem, nmax, l, lib, ws, g, false);
         for (int r = threadIdx.x; r < R; r += blockDim.x) {
@@ -3136,7 +3136,7 @@ __global__ __launch_bounds__(512) void k_falign(GridArgs g, SearchArgs sa, LibAr
     const long long nwaves = (long long)nbx * W;
     for (long long item = (long long)bx * W + wave; item < total; item += nwaves) {
         const int li = (int)(li0 + item / pairs), s0 = 2 * (int)(item % pairs);
-        const int l = ws.bin_list[(size_t)lst * lib.L + li];
+        const int l = ws.bin_list[li];
         const int ns = ws.nsel[l];
         if (s0 >= ns) continue;
         if (strips) {
@@ -3165,7 +3165,7 @@ __global__ __launch_bounds__(256) void k_out(SearchArgs sa, LibArgs lib, WorkArg
             l = single;
         } else {
             if (li >= ws.counters[lst]) break;
-            l = ws.bin_list[(size_t)lst * lib.L + li];
+            l = ws.bin_list[li];
         }
         const int a0 = lib.atom_off[l], n = lib.atom_off[l + 1] - a0;
         const int ns = ws.nsel[l];
@@ -3440,13 +3440,15 @@ __global__ __launch_bounds__(64) void k_prep(GridArgs g, SearchArgs sa, LibArgs 
             }
         }
         if (lane == 0 && do_bin) {
-            // work list: the atom bin, or with sa.groups > 1 the paper's bucket of
-            // (atom bin, group of 4 rotatable bonds; the last group takes the rest)
+            // work list: the atom bin and the library's part of ws.chunk ligands, or with
+            // sa.groups > 1 the paper's bucket of (atom bin, group of 4 rotatable bonds;
+            // the last group takes the rest)
             const int bin = (n - 1) >> 5;
             const int grp = B / 4 < sa.groups - 1 ? B / 4 : sa.groups - 1;
-            const int lst = bin * sa.groups + grp;
+            const int part = l / ws.chunk;
+            const int lst = sa.groups > 1 ? bin * sa.groups + grp : part * kNumBins + bin;
             const int pos = atomicAdd(&ws.counters[lst], 1);
-            ws.bin_list[(size_t)lst * lib.L + pos] = l;
+            ws.bin_list[list_offset(sa.groups, lst, lib.L, ws.chunk) + pos] = l;
         }
     } else {
         for (int s = lane; s < sa.K; s += 64) {

@@ -98,12 +98,22 @@ struct LibArgs {
     const unsigned long long *rot_mask;
 };
 
+// Work list lst starts at this entry of the list area [bins or buckets][L].  Paper
+// buckets (groups > 1): lst = bin * groups + group, L entries each.  Else lst =
+// part * kNumBins + bin: a bin's L entries hold the parts' lists at the parts' own
+// places (a part has at most `chunk` ligands), so splitting takes no memory.
+__host__ __device__ inline size_t list_offset(int groups, int lst, int L, int chunk) {
+    return groups > 1 ? (size_t)lst * L
+                      : (size_t)(lst % kNumBins) * L + (size_t)(lst / kNumBins) * chunk;
+}
+
 struct WorkArgs {
     unsigned long long *far;  // [A_total][kFarWords]
     int *counters;            // [kNumCounters]: [4][kMaxLists] count, dock_next, select_next,
                               // (unused) of each work list, then [kMaxLists][kXcds] the
                               // alignment queues of each list
-    int *bin_list;            // [lists][L] ligands of each work list
+    int *bin_list;            // ligands of the launch's work list (k_prep: of all lists)
+    int chunk;                // ligands of a part of the library (k_prep; L: one part)
     float *rscore;            // [L][R]
     uint16_t *rtrace;         // [R*(L + P*Nr_total)]
     float *acc_pose;          // [A_total*K*3] kept poses (aligned by the final step in place)

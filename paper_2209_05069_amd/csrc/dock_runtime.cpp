@@ -163,7 +163,7 @@ struct dock_ctx {
     // scratch array, kept until destroy so no asynchronous copy outlives its source
     std::map<std::string, TableBlob> noalloc_tables;
     char *scratch = nullptr;  // this device's copy of the scratch array
-    std::map<std::string, int> occ;
+    std::map<std::array<int, 5>, int> occ;  // see occupancy()
     // per-bin tile choices of dock_autotune, by (R, T, A, K, P)
     std::map<std::string, std::array<BinShape, kNumBins>> tuned;
     std::vector<hipStream_t> submit_streams;  // dock_submit: requests round-robin over these
@@ -182,6 +182,9 @@ struct dock_ctx {
     // repeat with identical arguments.
     std::map<std::string, int> seen_keys;
     std::map<std::string, hipGraphExec_t> graphs;
+    std::vector<hipStream_t> side_streams;  // batched form: work lists side by side
+    std::vector<hipEvent_t> side_events;
+    hipEvent_t fork_event = nullptr;
     std::vector<hipStream_t> plain_streams;  // plain form: ligands round-robin over these
     std::vector<hipEvent_t> plain_events;
     // per call: start, after prep, after the alignment kernels, after dock, end
@@ -439,11 +442,16 @@ SubmitLayout submit_layout(const dock_library *lib, const dock_params *p, const 
     return sl;
 }
 
-int occupancy(dock_ctx *c, const std::string &key, int v) {
+// Workgroups per CU of a launch shape, queried once (a query costs some
+// microseconds of host time).
+enum { kOccAlign, kOccAlignBound, kOccDock, kOccSelect, kOccFalign };
+
+template <class Query>
+int occupancy(dock_ctx *c, int kernel, int bin, int waves, int a, int b, Query &&query) {
+    const std::array<int, 5> key{kernel, bin, waves, a, b};
     auto it = c->occ.find(key);
-    if (it != c->occ.end()) return it->second;
-    c->occ[key] = v;
-    return v;
+    if (it == c->occ.end()) it = c->occ.emplace(key, query()).first;
+    return it->second;
 }
 
 constexpr int kOutBlocksPerCu = 4;
@@ -639,6 +647,7 @@ int prepare_launch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const
     wa.far = (unsigned long long *)(base + wl.far);
     wa.counters = (int *)(base + wl.counters);
     wa.bin_list = (int *)(base + wl.bin_list);
+    wa.chunk = lib->n_ligands;
     wa.rscore = (float *)(base + wl.rscore);
     wa.rtrace = user_trace ? o->trace : (uint16_t *)(base + wl.rtrace);
     wa.acc_pose = (float *)(base + wl.acc);
@@ -677,33 +686,37 @@ std::string tune_key(const SearchArgs &sa) {
            std::to_string(sa.K) + "/" + std::to_string(sa.P);
 }
 
+// Atom bins a ligand of the library can be in: atoms are limited by the mask words
+// (k_prep refuses the others) and by the atoms that all ligands have together.
+int used_bins(const LibArgs &la) {
+    const long long most = std::min<long long>({64LL * la.mask_words, la.A_total, kMaxAtoms});
+    return most < 1 ? 0 : (int)((most - 1) >> 5) + 1;
+}
+
 int make_shapes(dock_ctx *c, const Launch &L, const BinShape *tile, Shapes *sh) {
     const SearchArgs &sa = L.sa;
-    for (int bin = 0; bin < kNumBins; ++bin) {
+    std::memset((void *)sh, 0, sizeof(*sh));  // the graph key holds its bytes
+    for (int bin = 0; bin < used_bins(L.la); ++bin) {
         const BinShape &t = tile[bin];
         sh->tile[bin] = t;
         if ((size_t)c->lds_arena < align_lds_min(bin, sa.A, sa.R))
             return fail(DOCK_EDEVICE, "device LDS per workgroup too small for the alignment kernel");
-        if (L.bd.nb > 0) {
-            const std::string a = "ab" + std::to_string(bin);
-            sh->align_blocks[bin] = occupancy(c, a, align_bound_blocks_per_cu(bin)) * c->num_cu;
-        } else {
-            const std::string a = "a" + std::to_string(bin) + "/" + std::to_string(sa.R) + "/" +
-                                  std::to_string(sa.A) + "/" + std::to_string(c->lds_arena);
-            sh->align_blocks[bin] =
-                occupancy(c, a, align_blocks_per_cu(bin, sa.R, sa.A, c->lds_arena)) * c->num_cu;
-        }
-        const std::string k = "d" + std::to_string(bin) + "/" + std::to_string(t.dock_waves) + "/" +
-                              std::to_string((sa.T + 63) / 64);
+        sh->align_blocks[bin] =
+            c->num_cu *
+            (L.bd.nb > 0 ? occupancy(c, kOccAlignBound, bin, 0, 0, 0,
+                                     [&] { return align_bound_blocks_per_cu(bin); })
+                         : occupancy(c, kOccAlign, bin, 0, sa.R, sa.A, [&] {
+                               return align_blocks_per_cu(bin, sa.R, sa.A, c->lds_arena);
+                           }));
         sh->dock_blocks[bin] =
-            occupancy(c, k, dock_blocks_per_cu(bin, t.dock_waves, sa.T)) * c->num_cu;
-        const std::string f = "s" + std::to_string(bin) + "/" + std::to_string(t.select_waves) +
-                              "/" + std::to_string(sa.R) + "/" + std::to_string(sa.K);
-        const int sb =
-            occupancy(c, f, select_blocks_per_cu(bin, t.select_waves, sa.R, sa.K)) * c->num_cu;
+            c->num_cu * occupancy(c, kOccDock, bin, t.dock_waves, (sa.T + 63) / 64, 0,
+                                  [&] { return dock_blocks_per_cu(bin, t.dock_waves, sa.T); });
+        const int sb = c->num_cu * occupancy(c, kOccSelect, bin, t.select_waves, sa.R, sa.K, [&] {
+                           return select_blocks_per_cu(bin, t.select_waves, sa.R, sa.K);
+                       });
         sh->select_blocks[bin] = sb > L.la.L ? L.la.L : sb;
-        const std::string fa = "fa" + std::to_string(bin) + "/" + std::to_string(t.falign_waves);
-        int per_cu = occupancy(c, fa, falign_blocks_per_cu(bin, t.falign_waves));
+        int per_cu = occupancy(c, kOccFalign, bin, t.falign_waves, 0, 0,
+                               [&] { return falign_blocks_per_cu(bin, t.falign_waves); });
         if (t.falign_per_cu > 0 && t.falign_per_cu < per_cu) per_cu = t.falign_per_cu;
         sh->falign_blocks[bin] = per_cu * c->num_cu;
     }
@@ -714,55 +727,153 @@ int make_shapes(dock_ctx *c, const Launch &L, const BinShape *tile, Shapes *sh) 
     return DOCK_OK;
 }
 
-// The batched launch sequence: reset, prep, then per stage its launch per bin.
-// marks (optional): events recorded at the phase boundaries.
+// One stage (or all, in order) of work list `lst` of atom bin `bin`, with `share` per
+// cent of the workgroups that fill the GPU.
+enum { kStageAlign = 1, kStageDock = 2, kStageSelect = 4, kStageFalign = 8, kStageOut = 16,
+       kStageAll = 31 };
+
+int run_list(dock_ctx *c, const Launch &L, const Shapes &sh, int stages, int bin, int lst,
+             int share, hipStream_t s) {
+    const GridArgs &g = L.g;
+    const SearchArgs &sa = L.sa;
+    const LibArgs &la = L.la;
+    const OutArgs &oa = L.oa;
+    WorkArgs wa = L.wa;
+    wa.bin_list += list_offset(sa.groups, lst, la.L, wa.chunk);
+    auto part = [&](int blocks) { return std::max(1, (blocks * share + 99) / 100); };
+    if (stages & kStageAlign)
+        HIP_TRY(L.bd.nb > 0 ? launch_align_bound(bin, lst, part(sh.align_blocks[bin]), g, sa, la, wa,
+                                                 L.bd, s)
+                            : launch_align(bin, lst, part(sh.align_blocks[bin]), c->lds_arena, g,
+                                           sa, la, wa, s));
+    if (stages & kStageDock)
+        HIP_TRY(launch_dock(bin, lst, part(sh.dock_blocks[bin]), sh.tile[bin].dock_waves, g, sa, la,
+                            wa, s));
+    if (stages & kStageSelect)
+        HIP_TRY(launch_select(bin, lst, part(sh.select_blocks[bin]), sh.tile[bin].select_waves, g,
+                              sa, la, wa, oa, -1, s));
+    if (stages & kStageFalign)
+        HIP_TRY(launch_falign(bin, lst, part(sh.falign_blocks[bin]), sh.tile[bin].falign_waves, g,
+                              sa, la, wa, oa, -1, sh.tile[bin].falign_xcd ? kXcds : 0, s));
+    if (stages & kStageOut) HIP_TRY(launch_out(bin, lst, part(sh.out_blocks), sa, la, wa, oa, -1, s));
+    return DOCK_OK;
+}
+
+// The batched launch sequence on one stream: reset, prep, then per stage its launch per
+// bin.  marks (optional): events recorded at the phase boundaries.
 int run_sequence(dock_ctx *c, const Launch &L, const Shapes &sh, hipStream_t s,
                  const std::array<hipEvent_t, 5> *marks) {
-    const GridArgs &g = L.g;
     const SearchArgs &sa = L.sa;
     const LibArgs &la = L.la;
     const WorkArgs &wa = L.wa;
     const OutArgs &oa = L.oa;
-    const int G = sa.groups;
+    const int G = sa.groups, bins = used_bins(la);
     HIP_TRY(launch_reset(wa.counters, 0, kNumCounters, s));
     if (marks) HIP_TRY(hipEventRecord((*marks)[0], s));
-    HIP_TRY(launch_prep(g, sa, la, wa, oa, s));
+    HIP_TRY(launch_prep(L.g, sa, la, wa, oa, s));
     if (marks) HIP_TRY(hipEventRecord((*marks)[1], s));
     // each stage: one launch per work list (atom bin, or atom bin x bond group)
-    for (int bin = 0; bin < kNumBins; ++bin)
-        for (int q = 0; q < G; ++q)
-            HIP_TRY(L.bd.nb > 0 ? launch_align_bound(bin, bin * G + q, sh.align_blocks[bin], g, sa,
-                                                     la, wa, L.bd, s)
-                                : launch_align(bin, bin * G + q, sh.align_blocks[bin],
-                                               c->lds_arena, g, sa, la, wa, s));
+    auto stage = [&](int which) -> int {
+        for (int bin = 0; bin < bins; ++bin)
+            for (int q = 0; q < G; ++q) {
+                const int rc = run_list(c, L, sh, which, bin, bin * G + q, 100, s);
+                if (rc) return rc;
+            }
+        return DOCK_OK;
+    };
+    int rc = stage(kStageAlign);
+    if (rc) return rc;
     if (marks) HIP_TRY(hipEventRecord((*marks)[2], s));
-    for (int bin = 0; bin < kNumBins; ++bin)
-        for (int q = 0; q < G; ++q)
-            HIP_TRY(launch_dock(bin, bin * G + q, sh.dock_blocks[bin], sh.tile[bin].dock_waves, g,
-                                sa, la, wa, s));
+    rc = stage(kStageDock);
+    if (rc) return rc;
     if (marks) HIP_TRY(hipEventRecord((*marks)[3], s));
-    for (int bin = 0; bin < kNumBins; ++bin)
-        for (int q = 0; q < G; ++q)
-            HIP_TRY(launch_select(bin, bin * G + q, sh.select_blocks[bin],
-                                  sh.tile[bin].select_waves, g, sa, la, wa, oa, -1, s));
-    for (int bin = 0; bin < kNumBins; ++bin)
-        for (int q = 0; q < G; ++q)
-            HIP_TRY(launch_falign(bin, bin * G + q, sh.falign_blocks[bin],
-                                  sh.tile[bin].falign_waves, g, sa, la, wa, oa, -1,
-                                  sh.tile[bin].falign_xcd ? kXcds : 0, s));
-    for (int bin = 0; bin < kNumBins; ++bin)
-        for (int q = 0; q < G; ++q)
-            HIP_TRY(launch_out(bin, bin * G + q, sh.out_blocks, sa, la, wa, oa, -1, s));
+    rc = stage(kStageSelect);
+    if (!rc) rc = stage(kStageFalign);
+    if (!rc) rc = stage(kStageOut);
+    if (rc) return rc;
     if (oa.pcontacts) HIP_TRY(launch_rescore(L.ca, sa, la, oa, -1, sh.rescore_blocks, s));
     if (marks) HIP_TRY(hipEventRecord((*marks)[4], s));
     return DOCK_OK;
 }
 
-// The tile choice for these search settings: the autotuner's, else the defaults.
-const BinShape *bin_tiles(dock_ctx *c, const SearchArgs &sa) {
-    static const BinShape defaults[kNumBins] = {};
+// Streams the batched form's work lists run on, the library size from which every
+// stream gets its own third of the library, and the share of the GPU (per cent) a
+// launch then takes.
+// Chains of short kernels (few ligands in a bin) leave the GPU idle one after the
+// other; side by side 200 ligands of 100-256 atoms take 38.4 ms instead of 53.8 (43.1
+// on four streams), 32 ligands of 12-150 atoms 2.7 ms instead of 5.3.  A large
+// library's kernels fill the GPU each, but with different units: on half the
+// workgroups each, an alignment or final step (texture unit) of one third of the
+// library runs beside the sweep (VALU) of another: 16,000 ligands 379 ms instead of
+// 418, 2,500 ligands 43.3 instead of 47.9 (45.2 with lists side by side but unsplit);
+// in halves 393 and 45.3, in quarters 423 and 50.5, on 40 or 60 per cent of the
+// workgroups 390 and 389.
+constexpr int kWays = 3;
+constexpr int kSplitLigands = 2048;
+constexpr int kSplitShare = 50;
+
+bool split_library(const Launch &L) { return L.sa.groups == 1 && L.la.L >= kSplitLigands; }
+
+// The batched launch sequence over several streams: after prep the work lists are
+// independent of each other, each a chain of its own (alignment, sweep, selection,
+// final step, outputs).  The side streams start after prep and are joined before
+// the call's end on `s`.  They are all the context's own, made one after the other, so
+// that each has a hardware queue of its own (`s` may share one with a side stream, and
+// chains of one queue run one after the other).
+int run_overlapped(dock_ctx *c, const Launch &L0, const Shapes &sh, hipStream_t s) {
+    Launch L = L0;
+    const SearchArgs &sa = L.sa;
+    const LibArgs &la = L.la;
+    const int bins = used_bins(la), G = sa.groups;
+    const bool split = split_library(L);
+    if (split) L.wa.chunk = (la.L + kWays - 1) / kWays;
+    const int ways = std::min(kWays, split ? kWays : bins * G);
+    HIP_TRY(launch_reset(L.wa.counters, 0, kNumCounters, s));
+    HIP_TRY(launch_prep(L.g, sa, la, L.wa, L.oa, s));
+    if (ways > 1) HIP_TRY(hipEventRecord(c->fork_event, s));
+    int rc = DOCK_OK;
+    for (int w = 0; w < ways; ++w) {
+        const hipStream_t t = ways == 1 ? s : c->side_streams[w];
+        if (ways > 1) HIP_TRY(hipStreamWaitEvent(t, c->fork_event, 0));
+        if (split) {
+            // the thirds take the bins from different ones on
+            for (int k = 0; k < bins && !rc; ++k) {
+                const int bin = (k + w * bins / ways) % bins;
+                rc = run_list(c, L, sh, kStageAll, bin, w * kNumBins + bin, kSplitShare, t);
+            }
+        } else {
+            for (int q = bins * G - 1 - w; q >= 0 && !rc; q -= ways)
+                rc = run_list(c, L, sh, kStageAll, q / G, q, 100, t);
+        }
+        if (ways > 1) HIP_TRY(hipEventRecord(c->side_events[w], t));
+    }
+    // Joined when every chain is enqueued (a wait in a queue that `s` shares with a
+    // side stream holds up what is enqueued there later), and also after an error:
+    // `s` then still orders all that was launched.
+    for (int w = 0; ways > 1 && w < ways; ++w)
+        HIP_TRY(hipStreamWaitEvent(s, c->side_events[w], 0));
+    if (rc) return rc;
+    if (L.oa.pcontacts) HIP_TRY(launch_rescore(L.ca, sa, la, L.oa, -1, sh.rescore_blocks, s));
+    return DOCK_OK;
+}
+
+// The tile choice for these search settings: the autotuner's, else the defaults,
+// with more waves on a ligand's selection where the ligands alone do not fill the
+// GPU (as long as its poses still fit the LDS).  With 4, 8 and 16 waves 32 ligands of
+// 20-80 atoms take 2.56, 2.11 and 1.90 ms, 300 take 6.46, 6.16 and 6.14, 1,000 of 16
+// atoms 3.36, 3.29 and 3.47, 2,500 of 20-80 atoms 42.6, 43.4 and 44.4.
+std::array<BinShape, kNumBins> bin_tiles(dock_ctx *c, const SearchArgs &sa, int L) {
     auto it = c->tuned.find(tune_key(sa));
-    return it != c->tuned.end() ? it->second.data() : defaults;
+    if (it != c->tuned.end()) return it->second;
+    std::array<BinShape, kNumBins> tile{};
+    const int want = L <= 512 ? 16 : L <= 1024 ? 8 : 4;
+    for (int bin = 0; bin < kNumBins; ++bin)
+        for (int w = want; w > tile[bin].select_waves; w /= 2)
+            if (select_sel_lds(32 * (bin + 1), w, sa.R, sa.K)) {
+                tile[bin].select_waves = w;
+                break;
+            }
+    return tile;
 }
 
 // Enqueue the whole pipeline for a device-resident library.  With `scratch`
@@ -785,9 +896,17 @@ int enqueue_batch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const 
         return enqueue_plain(c, lib, L.g, L.sa, L.la, L.wa, L.oa, L.ca, ev, s);
     // launch shapes (occupancy queries stay outside any graph capture)
     Shapes sh;
-    rc = make_shapes(c, L, bin_tiles(c, L.sa), &sh);
+    rc = make_shapes(c, L, bin_tiles(c, L.sa, lib->n_ligands).data(), &sh);
     if (rc) return rc;
-    if (timed || s == nullptr || scratch) return run_sequence(c, L, sh, s, timed ? &ev : nullptr);
+    if (timed) return run_sequence(c, L, sh, s, &ev);
+    // A caller's own capture keeps to its stream: the side streams are the context's
+    // and would stay in that capture until it ends.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (s != nullptr) HIP_TRY(hipStreamIsCapturing(s, &cap));
+    const bool capturing = cap != hipStreamCaptureStatusNone;
+    auto run = [&]() { return capturing ? run_sequence(c, L, sh, s, nullptr) : run_overlapped(c, L, sh, s); };
+    // (a split library's kernels are long: eager, on the queues chosen here)
+    if (s == nullptr || scratch || (!capturing && split_library(L))) return run();
     // graph key: everything the kernels' arguments and launch shapes depend on
     std::string key((const char *)&L, sizeof(L));
     key.append((const char *)&sh, sizeof(sh));
@@ -796,7 +915,7 @@ int enqueue_batch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const 
     if (gi == c->graphs.end()) {
         if (c->seen_keys[key]++ == 0) {
             if (c->seen_keys.size() > 256) c->seen_keys.clear();
-            return run_sequence(c, L, sh, s, nullptr);  // first time: eager
+            return run();  // first time: eager
         }
         if (c->graphs.size() >= 16) {
             for (auto &kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
@@ -804,7 +923,7 @@ int enqueue_batch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const 
         }
         hipGraph_t graph = nullptr;
         HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed));
-        const int rc2 = run_sequence(c, L, sh, s, nullptr);
+        const int rc2 = run_overlapped(c, L, sh, s);
         const hipError_t ec = hipStreamEndCapture(s, &graph);
         if (rc2) {
             if (graph) (void)hipGraphDestroy(graph);
@@ -990,6 +1109,19 @@ int dock_create(int device, uint64_t hbm_budget_bytes, dock_ctx **out) {
             return rc;
         }
     }
+    bool made = hipEventCreateWithFlags(&c->fork_event, hipEventDisableTiming) == hipSuccess;
+    for (int i = 0; i < kWays && made; ++i) {
+        hipStream_t t = nullptr;
+        hipEvent_t e = nullptr;
+        made = hipStreamCreateWithFlags(&t, hipStreamNonBlocking) == hipSuccess;
+        if (made) c->side_streams.push_back(t);
+        made = made && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+        if (made) c->side_events.push_back(e);
+    }
+    if (!made) {
+        (void)dock_destroy(c);
+        return fail(DOCK_EDEVICE, "stream creation failed");
+    }
     for (int i = 0; i < kSubmitStreams; ++i) {
         hipStream_t t = nullptr;
         if (hipStreamCreateWithFlags(&t, hipStreamNonBlocking) != hipSuccess) {
@@ -1023,6 +1155,9 @@ int dock_destroy(dock_ctx *c) {
     for (auto t : c->submit_streams) hipStreamDestroy(t);
     for (auto t : c->plain_streams) hipStreamDestroy(t);
     for (auto e : c->plain_events) hipEventDestroy(e);
+    for (auto t : c->side_streams) hipStreamDestroy(t);
+    for (auto e : c->side_events) hipEventDestroy(e);
+    if (c->fork_event) hipEventDestroy(c->fork_event);
     delete c;
     return DOCK_OK;
 }
@@ -1306,6 +1441,11 @@ int dock_autotune(dock_ctx *c, int32_t pocket, const dock_library *lib, const do
         const LibArgs &la = Lc.la;
         const WorkArgs &wa = Lc.wa;
         const OutArgs &oa = Lc.oa;
+        auto on_list = [&](int lst) {
+            WorkArgs w = wa;
+            w.bin_list += list_offset(G, lst, la.L, wa.chunk);
+            return w;
+        };
         // best of two timed runs of one stage launch (each stage's kernels only
         // read what earlier stages wrote and rewrite the same values)
         auto timeit = [&](auto &&launch, float *ms) -> int {
@@ -1339,7 +1479,8 @@ int dock_autotune(dock_ctx *c, int32_t pocket, const dock_library *lib, const do
                 int e = timeit([&]() -> hipError_t {
                     hipError_t q = launch_reset(wa.counters, kMaxLists + bin * G, G, s);
                     for (int k = 0; k < G && !q; ++k)
-                        q = launch_dock(bin, bin * G + k, blocks, w, g, sa, la, wa, s);
+                        q = launch_dock(bin, bin * G + k, blocks, w, g, sa, la,
+                                        on_list(bin * G + k), s);
                     return q;
                 }, &t);
                 if (e) return e;
@@ -1356,7 +1497,8 @@ int dock_autotune(dock_ctx *c, int32_t pocket, const dock_library *lib, const do
                 int e = timeit([&]() -> hipError_t {
                     hipError_t q = launch_reset(wa.counters, 2 * kMaxLists + bin * G, G, s);
                     for (int k = 0; k < G && !q; ++k)
-                        q = launch_select(bin, bin * G + k, blocks, w, g, sa, la, wa, oa, -1, s);
+                        q = launch_select(bin, bin * G + k, blocks, w, g, sa, la,
+                                          on_list(bin * G + k), oa, -1, s);
                     return q;
                 }, &t);
                 if (e) return e;
@@ -1376,8 +1518,8 @@ int dock_autotune(dock_ctx *c, int32_t pocket, const dock_library *lib, const do
                         int e = timeit([&]() -> hipError_t {
                             hipError_t q = hipSuccess;
                             for (int k = 0; k < G && !q; ++k)
-                                q = launch_falign(bin, bin * G + k, blocks, w, g, sa, la, wa, oa,
-                                                  -1, xg ? kXcds : 0, s);
+                                q = launch_falign(bin, bin * G + k, blocks, w, g, sa, la,
+                                                  on_list(bin * G + k), oa, -1, xg ? kXcds : 0, s);
                             return q;
                         }, &t);
                         if (e) return e;

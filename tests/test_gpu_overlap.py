@@ -1,0 +1,72 @@
+"""Work lists side by side on several streams: the same results as one list after the
+other, for lists on streams of their own, for a library split into parts, with the
+next call on the same stream right behind, and under a caller's capture."""
+import numpy as np
+import pytest
+
+import synth
+from tests.test_gpu_parity import D, ctx  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+KEYS = ("best_score", "n_poses", "status", "pose_score", "pose_restart", "pose_xyz")
+
+
+def _setup(D, ctx, L, atoms, seed, **kw):  # noqa: F811
+    pk = synth.pocket_gaussians(seed, 4, 32, 0.5, 40, 4.0)
+    lib = synth.library_uniform(seed, L, atoms, (0, 3))
+    params = D.SearchParams(synth.start_quats(seed, 4), torsion_steps=16, sweep_passes=1,
+                            top_k=2, **kw)
+    pid = D.dock_pocket_load(ctx, pk.values, pk.spacing, pk.origin)
+    dl = D.DeviceLibrary(lib)
+    return pid, params, dl, [D.DeviceResults(L, dl.n_atoms_total, dl.n_rot_total, params)
+                             for _ in range(3)]
+
+
+def _same(a, b):
+    for k in KEYS:
+        np.testing.assert_array_equal(getattr(a, k).cpu().numpy(), getattr(b, k).cpu().numpy(),
+                                      err_msg=k)
+
+
+@pytest.mark.parametrize("L,atoms,bin_mode", [
+    (1, (9, 9), 0), (7, (3, 200), 0), (60, (3, 256), 1), (2047, (3, 40), 0),
+    (2048, (3, 70), 0), (2050, (3, 33), 0), (2100, (3, 70), 1)])
+def test_overlapped_lists_are_the_sequence(D, ctx, L, atoms, bin_mode):  # noqa: F811
+    # (phase timing keeps a call to one stream: the sequence to compare with)
+    pid, params, dl, (ref, got, rep) = _setup(D, ctx, L, atoms, 90 + L % 7, bin_mode=bin_mode)
+    print(f"[case] overlap L={L} bin_mode={bin_mode}", flush=True)
+    D.dock_set_timing(ctx, True)
+    D.dock_ligands_batch(ctx, pid, dl, params, ref)
+    D.dock_set_timing(ctx, False)
+    D.dock_get_timing(ctx)
+    D.dock_ligands_batch(ctx, pid, dl, params, got)
+    # repeated on a stream of its own: eager, captured, replayed, with eager calls between
+    st = torch.cuda.Stream()
+    st.wait_stream(torch.cuda.current_stream())
+    for _ in range(4):
+        D.dock_ligands_batch(ctx, pid, dl, params, rep, st)
+        D.dock_ligands_batch(ctx, pid, dl, params, got, st)
+    torch.cuda.synchronize()
+    _same(ref, got)
+    _same(ref, rep)
+    D.dock_pocket_unload(ctx, pid)
+
+
+def test_overlapped_lists_under_a_callers_capture(D, ctx):  # noqa: F811
+    pid, params, dl, (ref, got, _) = _setup(D, ctx, 40, (3, 100), 95)
+    st = torch.cuda.Stream()
+    D.dock_ligands_batch_noalloc(ctx, pid, dl, params, ref, st)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    print("[case] overlap under capture", flush=True)
+    with torch.cuda.graph(g, stream=st):
+        D.dock_ligands_batch_noalloc(ctx, pid, dl, params, got, st)
+    for _ in range(3):
+        for k in KEYS:
+            getattr(got, k).zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        _same(ref, got)
+    D.dock_pocket_unload(ctx, pid)
