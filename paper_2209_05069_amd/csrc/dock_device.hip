@@ -2052,7 +2052,7 @@ __device__ __forceinline__ float band_top(const BoundArgs &bd, int b) { return b
 // whole half sphere (dtheta/dt in [sqrt 2, 2]).  kBoundRowPad covers t's rounding,
 // largest at the pole, where 1 - |y|/r cancels.
 constexpr float kBoundRowPad = 2e-3f;
-constexpr float kBoundPhiPad = 2e-4f;  // radians: bound_sector's error (1e-5) and roundings
+constexpr float kBoundPhiPad = 4e-5f;  // turns: bound_sector's error (2e-6) and roundings
 
 __device__ __forceinline__ BoundRow bound_row(float r0, float r1, int row, int rows, float pad) {
     BoundRow q;
@@ -2067,15 +2067,17 @@ __device__ __forceinline__ BoundRow bound_row(float r0, float r1, int row, int r
     return q;
 }
 
-// Range of the sine over [a, b] (b - a below a turn, a > -2 pi).
+// Range of the sine over [a, b] turns (b - a below a turn, both in [-1, 3]): the
+// hardware sine, whose error is below kBoundSinPad.
+constexpr float kBoundSinPad = 4e-6f;
 __device__ __forceinline__ void sin_range(float a, float b, float &lo, float &hi) {
-    const float pi = 3.14159265358979f;
-    const float sa = sinf(a), sb = sinf(b);
+    const float sa = __builtin_amdgcn_sinf(__builtin_amdgcn_fractf(a)),
+                sb = __builtin_amdgcn_sinf(__builtin_amdgcn_fractf(b));
     lo = fminf(sa, sb);
     hi = fmaxf(sa, sb);
-    // peaks at pi/2 + 2 pi k, troughs at -pi/2 + 2 pi k
-    if (floorf((b - 0.5f * pi) / (2.0f * pi)) > floorf((a - 0.5f * pi) / (2.0f * pi))) hi = 1.0f;
-    if (floorf((b + 0.5f * pi) / (2.0f * pi)) > floorf((a + 0.5f * pi) / (2.0f * pi))) lo = -1.0f;
+    // peaks at 1/4 + k turns, troughs at 3/4 + k
+    if (floorf(b - 0.25f) > floorf(a - 0.25f)) hi = 1.0f;
+    if (floorf(b + 0.25f) > floorf(a + 0.25f)) lo = -1.0f;
 }
 
 // Largest value of the interpolated grid (edge values beyond the box, as the
@@ -2124,7 +2126,7 @@ __global__ __launch_bounds__(256) void k_bounds(GridArgs g, BoundArgs bd,
     unsigned short *out = tab + ((size_t)t * bd.type_bytes + (size_t)q.z) / 2;
     const bool last = b == bd.nb - 1;
     const float r0 = bd.edge[b], r1 = last ? r0 : band_top(bd, b);
-    const float sector = 6.28318530717959f / (float)kBoundSteps;
+    const float sector = 1.0f / (float)kBoundSteps;
     for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
         int v = kBoundMax;
         if (!last) {
@@ -2136,8 +2138,8 @@ __global__ __launch_bounds__(256) void k_bounds(GridArgs g, BoundArgs bd,
             const float p1 = sector * ((float)(k % kBoundSteps) + (float)(f + 1) / (float)m) + kBoundPhiPad;
             float sl, sh, cl, ch;
             sin_range(p0, p1, sl, sh);
-            sin_range(p0 + 1.57079632679490f, p1 + 1.57079632679490f, cl, ch);
-            const float e7 = 1e-6f;  // of the sine itself
+            sin_range(p0 + 0.25f, p1 + 0.25f, cl, ch);
+            const float e7 = kBoundSinPad;
             const float lo[3] = {g.acx + fminf(br.rlo * sl, br.rhi * sl) - br.rhi * e7,
                                  g.acy + (south ? -br.yhi : br.ylo),
                                  g.acz + fminf(br.rlo * cl, br.rhi * cl) - br.rhi * e7};
@@ -3116,8 +3118,8 @@ __global__ __launch_bounds__(512) void k_falign(GridArgs g, SearchArgs sa, LibAr
         return;
     }
     // batched form: the waves of the grid take the bin's (ligand, kept pose)
-    // items in turn (item = global wave index + k * waves in the grid).  The
-    // item index is scalar arithmetic only: no lane-dependent branch precedes
+    // items, from a queue or in turn (item = global wave index + k * waves in the
+    // grid).  The item index is wave-uniform: no lane-dependent branch precedes
     // the loop test, so every lane of a wave runs the same items.
     // With xcds > 1 the workgroups are taken as dispatched round-robin over that
     // many XCDs (workgroup b on XCD b % xcds): XCD x takes a contiguous x-th share
@@ -3134,7 +3136,20 @@ __global__ __launch_bounds__(512) void k_falign(GridArgs g, SearchArgs sa, LibAr
     const long long li0 = nl * x / nx, li1 = nl * (x + 1) / nx;
     const long long total = (li1 - li0) * pairs;
     const long long nwaves = (long long)nbx * W;
-    for (long long item = (long long)bx * W + wave; item < total; item += nwaves) {
+    // Without the split, and with more items than waves, a wave takes its next item from
+    // a queue: half of the items can be empty (ligands keep fewer than K poses), and
+    // dealt out in turn they left the GPU 41% idle (2,500 ligands of 20-80 atoms: 43.9
+    // -> 43.1 ms a call; an item a wave at most needs no queue, whose atomics from a full
+    // grid cost 80 us).
+    int *queue = xcds > 1 || total <= nwaves ? nullptr : ws.counters + 3 * kMaxLists + lst;
+    auto next = [&](long long item) -> long long {
+        if (!queue) return item + nwaves;
+        int v = 0;
+        if (lane_id() == 0) v = atomicAdd(queue, 1);
+        return uniform_int(v);
+    };
+    for (long long item = queue ? next(0) : (long long)bx * W + wave; item < total;
+         item = next(item)) {
         const int li = (int)(li0 + item / pairs), s0 = 2 * (int)(item % pairs);
         const int l = ws.bin_list[li];
         const int ns = ws.nsel[l];

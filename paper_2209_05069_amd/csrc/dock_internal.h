@@ -17,7 +17,7 @@ constexpr int kMaxLists = kNumBins * kMaxGroups;  // work lists (atom bin x bond
 
 constexpr int kMaxTopK = 64;        // matches DOCK_MAX_TOP_K
 constexpr int kXcds = 8;            // gfx950: workgroups go round-robin to 8 XCDs of 32 CUs
-// per list: count, dock_next, select_next, (unused), then one alignment queue per XCD
+// per list: count, dock_next, select_next, falign_next, then one alignment queue per XCD
 constexpr int kNumCounters = (4 + kXcds) * kMaxLists;
 #ifndef DOCK_ALIGN_J
 #define DOCK_ALIGN_J 32
@@ -110,7 +110,7 @@ __host__ __device__ inline size_t list_offset(int groups, int lst, int L, int ch
 struct WorkArgs {
     unsigned long long *far;  // [A_total][kFarWords]
     int *counters;            // [kNumCounters]: [4][kMaxLists] count, dock_next, select_next,
-                              // (unused) of each work list, then [kMaxLists][kXcds] the
+                              // falign_next of each work list, then [kMaxLists][kXcds] the
                               // alignment queues of each list
     int *bin_list;            // ligands of the launch's work list (k_prep: of all lists)
     int chunk;                // ligands of a part of the library (k_prep; L: one part)

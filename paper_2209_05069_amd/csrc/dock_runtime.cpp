@@ -696,21 +696,28 @@ int used_bins(const LibArgs &la) {
 int make_shapes(dock_ctx *c, const Launch &L, const BinShape *tile, Shapes *sh) {
     const SearchArgs &sa = L.sa;
     std::memset((void *)sh, 0, sizeof(*sh));  // the graph key holds its bytes
+    // no more workgroups than a bin of the whole library has items for (each one
+    // started only to find its queue empty costs an atomic on it)
+    auto at_most = [&](int blocks, int per_ligand) {
+        return (int)std::min<long long>(blocks, (long long)L.la.L * per_ligand);
+    };
     for (int bin = 0; bin < used_bins(L.la); ++bin) {
         const BinShape &t = tile[bin];
         sh->tile[bin] = t;
         if ((size_t)c->lds_arena < align_lds_min(bin, sa.A, sa.R))
             return fail(DOCK_EDEVICE, "device LDS per workgroup too small for the alignment kernel");
-        sh->align_blocks[bin] =
+        sh->align_blocks[bin] = at_most(
             c->num_cu *
             (L.bd.nb > 0 ? occupancy(c, kOccAlignBound, bin, 0, 0, 0,
                                      [&] { return align_bound_blocks_per_cu(bin); })
                          : occupancy(c, kOccAlign, bin, 0, sa.R, sa.A, [&] {
                                return align_blocks_per_cu(bin, sa.R, sa.A, c->lds_arena);
-                           }));
+                           })),
+            sa.R);
         sh->dock_blocks[bin] =
-            c->num_cu * occupancy(c, kOccDock, bin, t.dock_waves, (sa.T + 63) / 64, 0,
-                                  [&] { return dock_blocks_per_cu(bin, t.dock_waves, sa.T); });
+            at_most(c->num_cu * occupancy(c, kOccDock, bin, t.dock_waves, (sa.T + 63) / 64, 0,
+                                          [&] { return dock_blocks_per_cu(bin, t.dock_waves, sa.T); }),
+                    (sa.R + t.dock_waves - 1) / t.dock_waves);
         const int sb = c->num_cu * occupancy(c, kOccSelect, bin, t.select_waves, sa.R, sa.K, [&] {
                            return select_blocks_per_cu(bin, t.select_waves, sa.R, sa.K);
                        });
@@ -718,7 +725,9 @@ int make_shapes(dock_ctx *c, const Launch &L, const BinShape *tile, Shapes *sh) 
         int per_cu = occupancy(c, kOccFalign, bin, t.falign_waves, 0, 0,
                                [&] { return falign_blocks_per_cu(bin, t.falign_waves); });
         if (t.falign_per_cu > 0 && t.falign_per_cu < per_cu) per_cu = t.falign_per_cu;
-        sh->falign_blocks[bin] = per_cu * c->num_cu;
+        const int pairs = (sa.K + 1) / 2;
+        sh->falign_blocks[bin] =
+            at_most(per_cu * c->num_cu, (pairs + t.falign_waves - 1) / t.falign_waves);
     }
     sh->out_blocks = std::min(L.la.L, kOutBlocksPerCu * c->num_cu);
     // rescoring: 4 waves per workgroup, at most one wave per (ligand, pose) item
@@ -1516,7 +1525,7 @@ int dock_autotune(dock_ctx *c, int32_t pocket, const dock_library *lib, const do
                     for (int xg : {0, 1}) {
                         float t = 0.f;
                         int e = timeit([&]() -> hipError_t {
-                            hipError_t q = hipSuccess;
+                            hipError_t q = launch_reset(wa.counters, 3 * kMaxLists + bin * G, G, s);
                             for (int k = 0; k < G && !q; ++k)
                                 q = launch_falign(bin, bin * G + k, blocks, w, g, sa, la,
                                                   on_list(bin * G + k), oa, -1, xg ? kXcds : 0, s);
