@@ -2652,6 +2652,18 @@ __global__ __launch_bounds__(256) void k_plain(DockArgs args) {
         }
     }
     if (ws.scored && lane == 0) atomicAdd(ws.scored, (unsigned long long)nsc);
+    if (ws.rpose && wave == 0) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int i = lane + 64 * s;
+            float *P = ws.rpose + ((size_t)r * n + i) * 3;
+            if (i < n) {
+                P[0] = Y.x[s];
+                P[1] = Y.y[s];
+                P[2] = Y.z[s];
+            }
+        }
+    }
     const float sc = pose_score(Y, n, toff, tr, g);
     if (writer) ws.rscore[(size_t)l * sa.R + r] = sc;
 }
@@ -2728,7 +2740,7 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
                                                 int sel_lds) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int nmax = bin_nmax(bin);
-    const int W = blockDim.x >> 6, wave = threadIdx.x >> 6, lane = lane_id();
+    const int W = blockDim.x >> 6, wave = uniform_int((int)(threadIdx.x >> 6)), lane = lane_id();
     const int R = sa.R, K = sa.K;
     float4 *xyzt = (float4 *)(smem + Lds::xyzt(nmax));
     const u64 *mask = (const u64 *)(smem + Lds::mask(nmax, NS));
@@ -2773,7 +2785,7 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
             order[rk] = r;
         }
         __syncthreads();
-        const int n = misc[1], B = misc[2];
+        const int n = uniform_int(misc[1]), B = uniform_int(misc[2]);
         const int a0 = lib.atom_off[l];
         float *accp = ws.acc_pose + (size_t)a0 * K * 3;
         const uint16_t *trl = ws.rtrace + trace_base(lib, sa, l);
@@ -2791,16 +2803,22 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
                 float *cp = candL + (size_t)wave * n * 3;
                 int flag = 1;  // bit 0: conflicts with a kept pose (or no candidate)
                 if (t < R) {
-                    const int r = order[t];
-                    Pose<NS> Y;
-                    replay_pose(Y, xyzt, mask, rot, n, B, r, trl + (size_t)r * D, g, sa);
+                    const int r = uniform_int(order[t]);
+                    if (single >= 0 && ws.rpose) {
+                        // plain form: as k_plain left it
+                        const float *P = ws.rpose + (size_t)r * n * 3;
+                        for (int e = lane; e < 3 * n; e += 64) cp[e] = P[e];
+                    } else {
+                        Pose<NS> Y;
+                        replay_pose(Y, xyzt, mask, rot, n, B, r, trl + (size_t)r * D, g, sa);
 #pragma unroll
-                    for (int q = 0; q < NS; ++q) {
-                        const int i = lane + 64 * q;
-                        if (i < n) {
-                            cp[3 * i + 0] = Y.x[q];
-                            cp[3 * i + 1] = Y.y[q];
-                            cp[3 * i + 2] = Y.z[q];
+                        for (int q = 0; q < NS; ++q) {
+                            const int i = lane + 64 * q;
+                            if (i < n) {
+                                cp[3 * i + 0] = Y.x[q];
+                                cp[3 * i + 1] = Y.y[q];
+                                cp[3 * i + 2] = Y.z[q];
+                            }
                         }
                     }
                     wave_lds_sync();
@@ -2809,6 +2827,7 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
                         const bool ks = lane < ns;
                         const float *kq = keptL + (size_t)(ks ? lane : 0) * n * 3;
                         float ssd = 0.f;
+#pragma unroll 4
                         for (int i = 0; i < n; ++i) {
                             const float dx = cp[3 * i + 0] - kq[3 * i + 0];
                             const float dy = cp[3 * i + 1] - kq[3 * i + 1];
@@ -2821,6 +2840,7 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
                 }
                 __syncthreads();  // the round's candidates are in LDS
                 if (t < R && sa.dedup2 > 0.f) {
+#pragma unroll 4
                     for (int v = 0; v < wave; ++v) {
                         const float *vp = candL + (size_t)v * n * 3;
                         float ssd = 0.f;

@@ -116,6 +116,8 @@ struct WorkArgs {
     int chunk;                // ligands of a part of the library (k_prep; L: one part)
     float *rscore;            // [L][R]
     uint16_t *rtrace;         // [R*(L + P*Nr_total)]
+    float *rpose;             // plain form: [R][n][3] docked pose of each restart of the
+                              // ligand (null: selection rebuilds them from the traces)
     float *acc_pose;          // [A_total*K*3] kept poses (aligned by the final step in place)
     int *sel;                 // [L*K] restart of each kept pose
     int *nsel;                // [L] kept poses

@@ -70,3 +70,24 @@ def test_overlapped_lists_under_a_callers_capture(D, ctx):  # noqa: F811
         torch.cuda.synchronize()
         _same(ref, got)
     D.dock_pocket_unload(ctx, pid)
+
+
+def test_plain_calls_in_flight_keep_their_poses_apart(D, ctx):  # noqa: F811
+    # plain calls of different sizes on two streams, in flight together on the same
+    # inner streams: each has the batched form's results
+    print("[case] plain calls in flight", flush=True)
+    a = _setup(D, ctx, 9, (60, 250), 97)
+    b = _setup(D, ctx, 30, (3, 30), 98)
+    runs = []
+    for pid, params, dl, (ref, got, _) in (a, b):
+        plain = D.SearchParams(params.quat, **dict(params.values, mode=D.DOCK_MODE_PLAIN))
+        D.dock_ligands_batch(ctx, pid, dl, params, ref)
+        runs.append((pid, plain, dl, got, torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for pid, plain, dl, got, st in runs:
+            D.dock_ligands_batch(ctx, pid, dl, plain, got, st)
+    torch.cuda.synchronize()
+    for pid, params, dl, (ref, got, _) in (a, b):
+        _same(ref, got)
+        D.dock_pocket_unload(ctx, pid)
