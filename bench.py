@@ -9,8 +9,8 @@ with inputs already resident in device memory.
 
 Prints one JSON line.  `value` is ligands docked per second.  The roofline
 object covers the dominant kernel (the alignment or the torsion-sweep kernels
-of a step, whichever takes longer), timed live with HIP events on the stream
-they run on; `cpu_baseline` times the FP64 oracle, single-threaded, on a
+of a step, whichever takes longer), timed live with HIP events in one more step
+whose stages run one after the other on one stream; `cpu_baseline` times the FP64 oracle, single-threaded, on a
 bounded sample of the same library stratified by size.  The plain per-ligand
 form is timed on a stratified sample of the same library for the
 batched/plain factor, and one ligand at a time for its per-ligand latency.
@@ -506,8 +506,6 @@ def main():
         print(f"[bench] warmup {w} done", file=sys.stderr, flush=True)
     assert bool((res.status == 0).all()), "some ligands were rejected"
 
-    D.dock_set_timing(ctx, True)
-    D.dock_get_timing(ctx)
     torch.cuda.synchronize()
     step_ms = []
     e0 = _events(torch, stream)
@@ -519,15 +517,21 @@ def main():
     torch.cuda.synchronize()
     total_ms = e0.elapsed_time(e1)
     per_step = [x.elapsed_time(y) for x, y in step_ms]
+    # the phases, from one more step: a call that records them runs its stages one after
+    # the other on one stream, while the timed steps run work lists side by side
+    D.dock_set_timing(ctx, True)
+    D.dock_get_timing(ctx)
+    D.dock_ligands_batch(ctx, pid, dl, params, res, stream)
     tm = D.dock_get_timing(ctx)
     D.dock_set_timing(ctx, False)
-    print(f"[bench] timed {a.steps} steps: {total_ms:.1f} ms; phases {tm}", file=sys.stderr,
-          flush=True)
+    print(f"[bench] timed {a.steps} steps: {total_ms:.1f} ms; phases of one more {tm}",
+          file=sys.stderr, flush=True)
     graph_ms = None
     if a.graph_steps > 0:
-        # without phase timing, a call repeated with the same arguments on the same
-        # (non-null) stream is captured once as a hipGraph and replayed: the first of
-        # these two calls runs eagerly, the second captures and launches the graph
+        # a call repeated with the same arguments on the same (non-null) stream is
+        # captured once as a hipGraph and replayed, unless the library is split over
+        # several streams: the first of these two calls runs eagerly, the second
+        # captures and launches the graph
         gs = torch.cuda.Stream()
         gs.wait_stream(stream)
         for _ in range(2):
@@ -549,7 +553,7 @@ def main():
     align_ms = tm["align_ms"] / calls
     torsion_ms = (tm["dock_ms"] - tm["align_ms"]) / calls
     # Algorithmic work per step.  Alignment (k_align): R * A^2 * n atom samples per
-    # ligand.  Torsion sweep (k_dock): as in Alg. 1 a candidate that fails the bump
+    # ligand, also where bounds rule an orientation out without its samples (30 steps).  Torsion sweep (k_dock): as in Alg. 1 a candidate that fails the bump
     # check is not scored, so only the scored torsion samples (counted by the
     # kernels) enter, plus the pose score of every restart (R * n).
     n_tot = int(lib.atom_off[-1])
@@ -602,8 +606,9 @@ def main():
         "graph_replay": None if graph_ms is None else {
             "ms_per_step": graph_ms, "ligands_per_s": L / (graph_ms * 1e-3),
             "steps": a.graph_steps,
-            "note": "the same step replayed from its captured hipGraph (phase timing off); the "
-                    "timed steps above run eagerly because they record phase events"},
+            "note": "the same step repeated on a stream of its own, where a library of fewer than "
+                    "2,048 ligands is replayed from a captured hipGraph (a larger one runs "
+                    "eagerly there too)"},
         "roofline": {
             "bound": "alu",
             "achieved": achieved,

@@ -226,6 +226,8 @@ typedef struct {
 
 /* Dock a device-resident library; all work is enqueued on `stream` (a
  * hipStream_t, NULL = the null stream) and the call returns after enqueueing.
+ * Parts of the work may run on streams of the context in between: they start after
+ * what `stream` held before the call and `stream` waits for them.
  * Results are valid once the stream reaches this point.  The library and the
  * results must stay allocated until then.  Internal workspace is allocated on
  * first use and kept per stream; growing it waits for that stream. */
@@ -321,7 +323,8 @@ int dock_autotune(dock_ctx *ctx, int32_t pocket, const dock_library *sample,
 int dock_set_tuning(dock_ctx *ctx, const dock_params *params, const dock_bin_tuning *table);
 
 /* Phase timing, for measurement.  While enabled, every dock_ligands_batch
- * call records HIP events on its own stream before its prep kernel, after it,
+ * call runs its stages one after the other on its stream (without side streams)
+ * and records HIP events there before its prep kernel, after it,
  * after the alignment kernels (batched form), after the docking kernels and
  * after the select/final kernels.
  * dock_get_timing waits for every recorded event, returns the summed

@@ -14,9 +14,9 @@
 //    candidates are ranked by that partial sum (same argmax as the full score);
 //  * bump check in closed form: turning a moving atom about the bond axis makes
 //    its squared distance to a static atom C + A cos(theta) + B sin(theta), so
-//    lanes over static atoms compute (C, A, B) per pair, drop pairs whose
-//    closest approach stays above the bump distance (ballot), and test the few
-//    remaining pairs against every candidate with two FMAs; one 64-bit key max
+//    pairs whose closest approach stays above the bump distance are dropped
+//    (ballot), and the few remaining pairs are tested against the candidates they
+//    can reach with two FMAs; one 64-bit key max
 //    (order-preserving score bits, then the lower index) over the bump-free
 //    candidates picks the step;
 //  * grid gathers are raw buffer loads of cell cubes (a cell's trilinear

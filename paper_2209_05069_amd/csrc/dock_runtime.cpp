@@ -941,7 +941,10 @@ int enqueue_batch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const 
     // A caller's own capture keeps to its stream: the side streams are the context's
     // and would stay in that capture until it ends.
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (s != nullptr) HIP_TRY(hipStreamIsCapturing(s, &cap));
+    if (s != nullptr && hipStreamIsCapturing(s, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        cap = hipStreamCaptureStatusNone;
+    }
     const bool capturing = cap != hipStreamCaptureStatusNone;
     auto run = [&]() { return capturing ? run_sequence(c, L, sh, s, nullptr) : run_overlapped(c, L, sh, s); };
     // (a split library's kernels are long: eager, on the queues chosen here)
