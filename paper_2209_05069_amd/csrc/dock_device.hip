@@ -3689,6 +3689,7 @@ static hipError_t launch_falign_t(int bin, int lst, int blocks, int waves, const
 hipError_t launch_falign(int bin, int lst, int blocks, int waves, const GridArgs &g,
                          const SearchArgs &sa, const LibArgs &lib, const WorkArgs &ws,
                          const OutArgs &out, int single, int xcds, hipStream_t s) {
+    if (xcds > 1 && xcds > blocks) return hipErrorInvalidValue;  // shares without a workgroup
     switch (bin_slots(bin)) {
         case 1: return launch_falign_t<1>(bin, lst, blocks, waves, g, sa, lib, ws, out, single, xcds, s);
         case 2: return launch_falign_t<2>(bin, lst, blocks, waves, g, sa, lib, ws, out, single, xcds, s);

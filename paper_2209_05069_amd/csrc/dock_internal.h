@@ -235,7 +235,8 @@ hipError_t launch_select(int bin, int lst, int blocks, int waves, const GridArgs
                          const SearchArgs &sa, const LibArgs &lib, const WorkArgs &ws,
                          const OutArgs &out, int single, hipStream_t s);
 // xcds > 1: the bin's ligands are split into that many contiguous shares, share x
-// taken by workgroups b with b % xcds == x (the XCD they are dispatched to).
+// taken by workgroups b with b % xcds == x (the XCD they are dispatched to); refused
+// with fewer workgroups than shares.
 hipError_t launch_falign(int bin, int lst, int blocks, int waves, const GridArgs &g,
                          const SearchArgs &sa, const LibArgs &lib, const WorkArgs &ws,
                          const OutArgs &out, int single, int xcds, hipStream_t s);

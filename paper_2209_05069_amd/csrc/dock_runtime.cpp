@@ -791,9 +791,14 @@ int run_list(dock_ctx *c, const Launch &L, const Shapes &sh, int stages, int bin
     if (stages & kStageSelect)
         HIP_TRY(launch_select(bin, lst, part(sh.select_blocks[bin]), sh.tile[bin].select_waves, g,
                               sa, la, wa, oa, -1, s));
-    if (stages & kStageFalign)
-        HIP_TRY(launch_falign(bin, lst, part(sh.falign_blocks[bin]), sh.tile[bin].falign_waves, g,
-                              sa, la, wa, oa, -1, sh.tile[bin].falign_xcd ? kXcds : 0, s));
+    if (stages & kStageFalign) {
+        // the split over XCDs gives every share to workgroups of its own, so a launch of
+        // fewer workgroups than XCDs (few ligands) goes without it
+        const int blocks = part(sh.falign_blocks[bin]);
+        const int xcds = sh.tile[bin].falign_xcd && blocks >= kXcds ? kXcds : 0;
+        HIP_TRY(launch_falign(bin, lst, blocks, sh.tile[bin].falign_waves, g, sa, la, wa, oa, -1,
+                              xcds, s));
+    }
     if (stages & kStageOut) HIP_TRY(launch_out(bin, lst, part(sh.out_blocks), sa, la, wa, oa, -1, s));
     return DOCK_OK;
 }

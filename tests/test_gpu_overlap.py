@@ -91,3 +91,29 @@ def test_plain_calls_in_flight_keep_their_poses_apart(D, ctx):  # noqa: F811
     for pid, params, dl, (ref, got, _) in (a, b):
         _same(ref, got)
         D.dock_pocket_unload(ctx, pid)
+
+
+@pytest.mark.parametrize("top_k", [1, 30])
+@pytest.mark.parametrize("L", [1, 2, 3, 7])
+def test_split_final_step_of_few_ligands(D, ctx, L, top_k):  # noqa: F811
+    # a table tuned on a large sample, with the final step split over the XCDs, used on
+    # a list too short for a workgroup per share
+    pk = synth.pocket_gaussians(99, 4, 32, 0.5, 40, 4.0)
+    lib = synth.library_uniform(99, L, (9, 60), (0, 3))
+    params = D.SearchParams(synth.start_quats(99, 40), torsion_steps=16, sweep_passes=1,
+                            top_k=top_k, dedup_rmsd=0.5)
+    pid = D.dock_pocket_load(ctx, pk.values, pk.spacing, pk.origin)
+    dl = D.DeviceLibrary(lib)
+    ref, got = [D.DeviceResults(L, dl.n_atoms_total, dl.n_rot_total, params) for _ in range(2)]
+    D.dock_ligands_batch(ctx, pid, dl, params, ref)
+    for waves in (2, 4, 8):
+        print(f"[case] split final step L={L} K={top_k} waves={waves}", flush=True)
+        tile = dict(ligands=1, dock_waves=4, select_waves=4, falign_waves=waves, falign_xcd=1)
+        D.dock_set_tuning(ctx, params, [tile] * D.NUM_BINS)
+        for k in KEYS:
+            getattr(got, k).zero_()
+        D.dock_ligands_batch(ctx, pid, dl, params, got)
+        torch.cuda.synchronize()
+        _same(ref, got)
+    D.dock_set_tuning(ctx, params, None)
+    D.dock_pocket_unload(ctx, pid)

@@ -1,0 +1,83 @@
+"""The host runtime's launches, streams and captures, on the CPU: dock_runtime.cpp built
+against a model of HIP streams (tests/host/hip_stub.cpp)."""
+import ctypes
+import os
+import re
+import subprocess
+
+import pytest
+
+import synth
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("stub") / "libdock_stub.so")
+    inc = [a for d in ("/opt/rocm/include", os.path.join(ROOT, "include"),
+                       os.path.join(ROOT, "paper_2209_05069_amd", "csrc")) for a in ("-I", d)]
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-w", "-Wl,-Bsymbolic",
+                    "-D__HIP_PLATFORM_AMD__", *inc,
+                    os.path.join(ROOT, "tests", "host", "hip_stub.cpp"), "-o", so], check=True)
+    return so
+
+
+@pytest.fixture
+def D(stub, monkeypatch):
+    from paper_2209_05069_amd import dock
+    monkeypatch.setattr(dock, "LIBPATH", stub)
+    monkeypatch.setattr(dock, "_lib", None)
+    L = dock.lib()
+    L.stub_log.restype = ctypes.c_char_p
+    for f in (L.stub_hold, L.stub_capture):
+        f.argtypes = [ctypes.c_void_p, ctypes.c_int]
+    L.stub_idle.argtypes = [ctypes.c_void_p]
+    L.stub_fail.argtypes = [ctypes.c_char_p, ctypes.c_int]
+    return dock
+
+
+@pytest.fixture
+def ctx(D):
+    c = D.dock_create(0)
+    yield c
+    D.dock_destroy(c)
+
+
+def _job(D, ctx, ligands, atoms=(12, 40), pid=None, **kw):
+    pk = synth.pocket_gaussians(7, 2, 8, 0.5, 4, 1.0)
+    if pid is None:
+        pid = D.dock_pocket_load(ctx, pk.values, pk.spacing, pk.origin)
+    lib = synth.library_uniform(ligands, ligands, atoms, (0, 2))
+    params = D.SearchParams(synth.start_quats(3, 4), torsion_steps=8, sweep_passes=1, **kw)
+    dl = D.DeviceLibrary(lib, device="cpu")
+    res = D.DeviceResults(ligands, dl.n_atoms_total, dl.n_rot_total, params, device="cpu")
+    return pid, dl, params, res
+
+
+def _log(D):
+    return D.lib().stub_log().decode().splitlines()
+
+
+# ---------------------------------------------------------------------------
+
+
+@pytest.mark.parametrize("top_k", [1, 2, 30])
+@pytest.mark.parametrize("waves", [2, 4, 8])
+@pytest.mark.parametrize("ligands", [1, 2, 3, 7, 40, 2100])
+def test_every_share_of_a_split_final_step_has_a_workgroup(D, ctx, ligands, waves, top_k):
+    # with the per-XCD split, share x of a list's ligands is taken by the workgroups
+    # b with b % xcds == x: fewer workgroups than shares leave ligands undone
+    job = _job(D, ctx, ligands, top_k=top_k)
+    pid, dl, params, res = job
+    tile = dict(ligands=1, dock_waves=4, select_waves=4, falign_waves=waves, falign_xcd=1)
+    D.dock_set_tuning(ctx, params, [tile] * D.NUM_BINS)
+    _log(D)
+    D.dock_ligands_batch(ctx, pid, dl, params, res, 0x77)
+    seen = [m.groups() for m in (re.match(r"falign .* blocks=(\d+) .*xcds=(\d+)", line)
+                                 for line in _log(D)) if m]
+    assert seen
+    for blocks, xcds in seen:
+        assert int(xcds) <= 1 or int(blocks) >= int(xcds)
+    if ligands >= 2000:  # still split where there are workgroups enough
+        assert any(int(x) == 8 for _, x in seen)
