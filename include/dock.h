@@ -227,7 +227,9 @@ typedef struct {
 /* Dock a device-resident library; all work is enqueued on `stream` (a
  * hipStream_t, NULL = the null stream) and the call returns after enqueueing.
  * Parts of the work may run on streams of the context in between: they start after
- * what `stream` held before the call and `stream` waits for them.
+ * what `stream` held before the call and `stream` waits for them.  While those
+ * streams hold another stream's call, all of the work stays on `stream`: calls on
+ * different streams do not wait for each other.
  * Results are valid once the stream reaches this point.  The library and the
  * results must stay allocated until then.  Internal workspace is allocated on
  * first use and kept per stream; growing it waits for that stream. */

@@ -131,6 +131,15 @@ struct TableBlob {
     size_t o_smat = 0, o_amat = 0, o_tors = 0, o_acs = 0;
 };
 
+// Streams the batched form's work lists run on (see run_overlapped).
+constexpr int kWays = 3;
+
+// Events of a fork to the side streams and of the joins.
+struct SideEvents {
+    hipEvent_t fork = nullptr;
+    hipEvent_t join[kWays] = {};
+};
+
 struct Ticket {
     hipEvent_t done = nullptr;
     int32_t pocket = -1;
@@ -183,8 +192,10 @@ struct dock_ctx {
     std::map<std::string, int> seen_keys;
     std::map<std::string, hipGraphExec_t> graphs;
     std::vector<hipStream_t> side_streams;  // batched form: work lists side by side
-    std::vector<hipEvent_t> side_events;
-    hipEvent_t fork_event = nullptr;
+    // events of eager calls, and of captured ones (a captured event cannot be queried)
+    SideEvents side_eager, side_captured;
+    bool side_used = false;           // side_eager has been recorded,
+    hipStream_t side_user = nullptr;  // last by a call on this stream
     std::vector<hipStream_t> plain_streams;  // plain form: ligands round-robin over these
     std::vector<hipEvent_t> plain_events;
     float *plain_pose = nullptr;  // restart poses of the ligand on each plain stream
@@ -840,9 +851,8 @@ int run_sequence(dock_ctx *c, const Launch &L, const Shapes &sh, hipStream_t s,
     return DOCK_OK;
 }
 
-// Streams the batched form's work lists run on, the library size from which every
-// stream gets its own third of the library, and the share of the GPU (per cent) a
-// launch then takes.
+// The library size from which every side stream gets its own third of the library,
+// and the share of the GPU (per cent) a launch then takes.
 // Chains of short kernels (few ligands in a bin) leave the GPU idle one after the
 // other; side by side 200 ligands of 100-256 atoms take 38.4 ms instead of 53.8 (43.1
 // on four streams), 32 ligands of 12-150 atoms 2.7 ms instead of 5.3.  A large
@@ -852,7 +862,6 @@ int run_sequence(dock_ctx *c, const Launch &L, const Shapes &sh, hipStream_t s,
 // 418, 2,500 ligands 43.3 instead of 47.9 (45.2 with lists side by side but unsplit);
 // in halves 393 and 45.3, in quarters 423 and 50.5, on 40 or 60 per cent of the
 // workgroups 390 and 389.
-constexpr int kWays = 3;
 constexpr int kSplitLigands = 2048;
 constexpr int kSplitShare = 50;
 
@@ -864,7 +873,8 @@ bool split_library(const Launch &L) { return L.sa.groups == 1 && L.la.L >= kSpli
 // the call's end on `s`.  They are all the context's own, made one after the other, so
 // that each has a hardware queue of its own (`s` may share one with a side stream, and
 // chains of one queue run one after the other).
-int run_overlapped(dock_ctx *c, const Launch &L0, const Shapes &sh, hipStream_t s) {
+int run_overlapped(dock_ctx *c, const Launch &L0, const Shapes &sh, hipStream_t s,
+                   const SideEvents &ev) {
     Launch L = L0;
     const SearchArgs &sa = L.sa;
     const LibArgs &la = L.la;
@@ -874,11 +884,11 @@ int run_overlapped(dock_ctx *c, const Launch &L0, const Shapes &sh, hipStream_t 
     const int ways = std::min(kWays, split ? kWays : bins * G);
     HIP_TRY(launch_reset(L.wa.counters, 0, kNumCounters, s));
     HIP_TRY(launch_prep(L.g, sa, la, L.wa, L.oa, s));
-    if (ways > 1) HIP_TRY(hipEventRecord(c->fork_event, s));
+    if (ways > 1) HIP_TRY(hipEventRecord(ev.fork, s));
     int rc = DOCK_OK;
     for (int w = 0; w < ways; ++w) {
         const hipStream_t t = ways == 1 ? s : c->side_streams[w];
-        if (ways > 1) HIP_TRY(hipStreamWaitEvent(t, c->fork_event, 0));
+        if (ways > 1) HIP_TRY(hipStreamWaitEvent(t, ev.fork, 0));
         if (split) {
             // the thirds take the bins from different ones on
             for (int k = 0; k < bins && !rc; ++k) {
@@ -889,16 +899,41 @@ int run_overlapped(dock_ctx *c, const Launch &L0, const Shapes &sh, hipStream_t 
             for (int q = bins * G - 1 - w; q >= 0 && !rc; q -= ways)
                 rc = run_list(c, L, sh, kStageAll, q / G, q, 100, t);
         }
-        if (ways > 1) HIP_TRY(hipEventRecord(c->side_events[w], t));
+        if (ways > 1) HIP_TRY(hipEventRecord(ev.join[w], t));
     }
     // Joined when every chain is enqueued (a wait in a queue that `s` shares with a
     // side stream holds up what is enqueued there later), and also after an error:
     // `s` then still orders all that was launched.
     for (int w = 0; ways > 1 && w < ways; ++w)
-        HIP_TRY(hipStreamWaitEvent(s, c->side_events[w], 0));
+        HIP_TRY(hipStreamWaitEvent(s, ev.join[w], 0));
     if (rc) return rc;
     if (L.oa.pcontacts) HIP_TRY(launch_rescore(L.ca, sa, la, L.oa, -1, sh.rescore_blocks, s));
     return DOCK_OK;
+}
+
+// Whether an eager call on `s` may put its chains on the side streams: nothing is left
+// on them, or only what calls on `s` put there.  Behind another stream's call the chains
+// would wait for that call and for all that its stream still has to do before it.
+bool side_streams_free(dock_ctx *c, hipStream_t s) {
+    if (!c->side_used || c->side_user == s) return true;
+    // (a query may not disturb a capture that the caller has under way elsewhere)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    bool done = true;
+    for (hipEvent_t e : c->side_eager.join) done = done && hipEventQuery(e) == hipSuccess;
+    if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (!done) (void)hipGetLastError();
+    return done;
+}
+
+// An eager call: its lists side by side, or, while the side streams hold another
+// stream's call, one after the other on `s` (calls in flight on several streams then
+// run beside each other, and none waits for another's stream).
+int run_eager(dock_ctx *c, const Launch &L, const Shapes &sh, hipStream_t s) {
+    if (!side_streams_free(c, s)) return run_sequence(c, L, sh, s, nullptr);
+    c->side_used = true;
+    c->side_user = s;
+    return run_overlapped(c, L, sh, s, c->side_eager);
 }
 
 // The tile choice for these search settings: the autotuner's, else the defaults,
@@ -951,7 +986,7 @@ int enqueue_batch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const 
         cap = hipStreamCaptureStatusNone;
     }
     const bool capturing = cap != hipStreamCaptureStatusNone;
-    auto run = [&]() { return capturing ? run_sequence(c, L, sh, s, nullptr) : run_overlapped(c, L, sh, s); };
+    auto run = [&]() { return capturing ? run_sequence(c, L, sh, s, nullptr) : run_eager(c, L, sh, s); };
     // (a split library's kernels are long: eager, on the queues chosen here)
     if (s == nullptr || scratch || (!capturing && split_library(L))) return run();
     // graph key: everything the kernels' arguments and launch shapes depend on
@@ -970,7 +1005,7 @@ int enqueue_batch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const 
         }
         hipGraph_t graph = nullptr;
         HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed));
-        const int rc2 = run_overlapped(c, L, sh, s);
+        const int rc2 = run_overlapped(c, L, sh, s, c->side_captured);
         const hipError_t ec = hipStreamEndCapture(s, &graph);
         if (rc2) {
             if (graph) (void)hipGraphDestroy(graph);
@@ -1156,27 +1191,26 @@ int dock_create(int device, uint64_t hbm_budget_bytes, dock_ctx **out) {
             return rc;
         }
     }
-    bool made = hipEventCreateWithFlags(&c->fork_event, hipEventDisableTiming) == hipSuccess;
-    for (int i = 0; i < kWays && made; ++i) {
-        hipStream_t t = nullptr;
-        hipEvent_t e = nullptr;
-        made = hipStreamCreateWithFlags(&t, hipStreamNonBlocking) == hipSuccess;
-        if (made) c->side_streams.push_back(t);
-        made = made && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
-        if (made) c->side_events.push_back(e);
+    bool made = true;
+    auto streams = [&](std::vector<hipStream_t> &to, int n) {
+        for (int i = 0; i < n && made; ++i) {
+            hipStream_t t = nullptr;
+            made = hipStreamCreateWithFlags(&t, hipStreamNonBlocking) == hipSuccess;
+            if (made) to.push_back(t);
+        }
+    };
+    streams(c->side_streams, kWays);
+    streams(c->submit_streams, kSubmitStreams);
+    auto event = [&](hipEvent_t *e) {
+        made = made && hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess;
+    };
+    for (SideEvents *ev : {&c->side_eager, &c->side_captured}) {
+        event(&ev->fork);
+        for (hipEvent_t &e : ev->join) event(&e);
     }
     if (!made) {
         (void)dock_destroy(c);
         return fail(DOCK_EDEVICE, "stream creation failed");
-    }
-    for (int i = 0; i < kSubmitStreams; ++i) {
-        hipStream_t t = nullptr;
-        if (hipStreamCreateWithFlags(&t, hipStreamNonBlocking) != hipSuccess) {
-            for (auto u : c->submit_streams) (void)hipStreamDestroy(u);
-            delete c;
-            return fail(DOCK_EDEVICE, "stream creation failed");
-        }
-        c->submit_streams.push_back(t);
     }
     *out = c;
     g_err.clear();
@@ -1204,8 +1238,11 @@ int dock_destroy(dock_ctx *c) {
     for (auto t : c->plain_streams) hipStreamDestroy(t);
     for (auto e : c->plain_events) hipEventDestroy(e);
     for (auto t : c->side_streams) hipStreamDestroy(t);
-    for (auto e : c->side_events) hipEventDestroy(e);
-    if (c->fork_event) hipEventDestroy(c->fork_event);
+    for (const SideEvents &ev : {c->side_eager, c->side_captured}) {
+        if (ev.fork) hipEventDestroy(ev.fork);
+        for (hipEvent_t e : ev.join)
+            if (e) hipEventDestroy(e);
+    }
     delete c;
     return DOCK_OK;
 }

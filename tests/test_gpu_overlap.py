@@ -117,3 +117,41 @@ def test_split_final_step_of_few_ligands(D, ctx, L, top_k):  # noqa: F811
         _same(ref, got)
     D.dock_set_tuning(ctx, params, None)
     D.dock_pocket_unload(ctx, pid)
+
+
+def test_calls_in_flight_on_several_streams(D, ctx):  # noqa: F811
+    # batched calls of different sizes on streams of their own, split, unsplit and by
+    # buckets, with submitted work between them: each has the results it has alone
+    jobs = [_setup(D, ctx, L, atoms, 100 + L % 9, **kw) for L, atoms, kw in
+            ((2100, (3, 70), {}), (40, (3, 200), {}), (300, (3, 50), {}),
+             (60, (3, 256), dict(bin_mode=1)), (3, (9, 9), {}))]
+    for pid, params, dl, (ref, _, _) in jobs:
+        D.dock_ligands_batch(ctx, pid, dl, params, ref)
+        torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in jobs]
+    lib = jobs[1][2].host
+    sizes = (lib.n_ligands, int(lib.atom_off[-1]), int(lib.rot_off[-1]))
+    for rep in range(3):
+        print(f"[case] calls in flight, round {rep}", flush=True)
+        out = []
+        for (pid, params, dl, (_, got, _)), st in zip(jobs, streams):
+            for k in KEYS:
+                getattr(got, k).zero_()
+        torch.cuda.synchronize()
+        for (pid, params, dl, (_, got, again)), st in zip(jobs, streams):
+            D.dock_ligands_batch(ctx, pid, dl, params, got, st)
+            D.dock_ligands_batch(ctx, pid, dl, params, again, st)
+            h = D.HostResults(*sizes, jobs[1][1])
+            out.append((D.dock_submit(ctx, jobs[1][0], lib, jobs[1][1], h), h))
+        for t, _ in out:
+            D.dock_wait(ctx, t)
+        torch.cuda.synchronize()
+        for pid, params, dl, (ref, got, again) in jobs:
+            _same(ref, got)
+            _same(ref, again)
+        for _, h in out:
+            for k in KEYS:
+                np.testing.assert_array_equal(getattr(h, k), getattr(jobs[1][3][0], k).cpu().numpy(),
+                                              err_msg=k)
+    for pid, params, dl, _ in jobs:
+        D.dock_pocket_unload(ctx, pid)

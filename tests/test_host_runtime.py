@@ -81,3 +81,32 @@ def test_every_share_of_a_split_final_step_has_a_workgroup(D, ctx, ligands, wave
         assert int(xcds) <= 1 or int(blocks) >= int(xcds)
     if ligands >= 2000:  # still split where there are workgroups enough
         assert any(int(x) == 8 for _, x in seen)
+
+
+@pytest.mark.parametrize("ligands,bin_mode", [(7, 0), (2100, 0), (60, 1)])
+def test_calls_on_other_streams_do_not_wait_for_a_stuck_one(D, ctx, ligands, bin_mode):
+    # stream 0x51 still runs something of the caller's: its call waits for that, and
+    # calls on other streams and submitted work do not
+    L = D.lib()
+    pid, dl, params, res = _job(D, ctx, ligands, (12, 200), bin_mode=bin_mode)
+    other = _job(D, ctx, 5, (12, 200), pid=pid)
+    _, _, params2, _ = other
+    host = synth.library_uniform(4, 4, (12, 100), (0, 2))
+    hres = D.HostResults(4, int(host.atom_off[-1]), int(host.rot_off[-1]), params2)
+    D.dock_ligands_batch(ctx, pid, dl, params, res, 0x51)
+    L.stub_hold(0x51, 1)
+    D.dock_ligands_batch(ctx, pid, dl, params, res, 0x51)
+    D.dock_ligands_batch(ctx, pid, other[1], params2, other[3], 0x52)
+    assert L.stub_idle(0x52)
+    D.dock_ligands_batch_noalloc(ctx, pid, other[1], params2, other[3], 0x53)
+    assert L.stub_idle(0x53)
+    tickets = [D.dock_submit(ctx, pid, host, params2, hres) for _ in range(5)]
+    assert all(D.dock_poll(ctx, t) for t in tickets)
+    assert not L.stub_idle(0x51)
+    L.stub_hold(0x51, 0)
+    assert L.stub_idle(0x51) and L.stub_all_idle()
+    # the side streams are free again: the next call runs its lists side by side
+    _log(D)
+    D.dock_ligands_batch(ctx, pid, dl, params, res, 0x54)
+    assert len({line.split("stream=")[1] for line in _log(D) if line.startswith("dock ")}) == 3
+    L.stub_all_idle()
