@@ -134,11 +134,12 @@ struct TableBlob {
 // Streams the batched form's work lists run on (see run_overlapped).
 constexpr int kWays = 3;
 
-// Events of a fork to the side streams and of the joins.
-struct SideEvents {
-    hipEvent_t fork = nullptr;
-    hipEvent_t join[kWays] = {};
+// A captured launch sequence and an event recorded behind its last launch.
+struct Replay {
+    hipGraphExec_t exec = nullptr;
+    hipEvent_t last = nullptr;
 };
+constexpr size_t kMaxReplays = 16;
 
 struct Ticket {
     hipEvent_t done = nullptr;
@@ -190,12 +191,11 @@ struct dock_ctx {
     // Batched launch sequences seen once (eager) and captured as graphs when they
     // repeat with identical arguments.
     std::map<std::string, int> seen_keys;
-    std::map<std::string, hipGraphExec_t> graphs;
+    std::map<std::string, Replay> graphs;
     std::vector<hipStream_t> side_streams;  // batched form: work lists side by side
-    // events of eager calls, and of captured ones (a captured event cannot be queried)
-    SideEvents side_eager, side_captured;
-    bool side_used = false;           // side_eager has been recorded,
-    hipStream_t side_user = nullptr;  // last by a call on this stream
+    hipEvent_t side_fork = nullptr, side_join[kWays] = {};
+    bool side_used = false;           // the side streams have had a call,
+    hipStream_t side_user = nullptr;  // the last one from this stream
     std::vector<hipStream_t> plain_streams;  // plain form: ligands round-robin over these
     std::vector<hipEvent_t> plain_events;
     float *plain_pose = nullptr;  // restart poses of the ligand on each plain stream
@@ -867,28 +867,32 @@ constexpr int kSplitShare = 50;
 
 bool split_library(const Launch &L) { return L.sa.groups == 1 && L.la.L >= kSplitLigands; }
 
+// Side streams a call's chains can use.
+int side_ways(const Launch &L) {
+    return split_library(L) ? kWays : std::min(kWays, used_bins(L.la) * L.sa.groups);
+}
+
 // The batched launch sequence over several streams: after prep the work lists are
 // independent of each other, each a chain of its own (alignment, sweep, selection,
 // final step, outputs).  The side streams start after prep and are joined before
 // the call's end on `s`.  They are all the context's own, made one after the other, so
 // that each has a hardware queue of its own (`s` may share one with a side stream, and
 // chains of one queue run one after the other).
-int run_overlapped(dock_ctx *c, const Launch &L0, const Shapes &sh, hipStream_t s,
-                   const SideEvents &ev) {
+int run_overlapped(dock_ctx *c, const Launch &L0, const Shapes &sh, hipStream_t s) {
     Launch L = L0;
     const SearchArgs &sa = L.sa;
     const LibArgs &la = L.la;
     const int bins = used_bins(la), G = sa.groups;
     const bool split = split_library(L);
     if (split) L.wa.chunk = (la.L + kWays - 1) / kWays;
-    const int ways = std::min(kWays, split ? kWays : bins * G);
+    const int ways = side_ways(L0);
     HIP_TRY(launch_reset(L.wa.counters, 0, kNumCounters, s));
     HIP_TRY(launch_prep(L.g, sa, la, L.wa, L.oa, s));
-    if (ways > 1) HIP_TRY(hipEventRecord(ev.fork, s));
+    if (ways > 1) HIP_TRY(hipEventRecord(c->side_fork, s));
     int rc = DOCK_OK;
     for (int w = 0; w < ways; ++w) {
         const hipStream_t t = ways == 1 ? s : c->side_streams[w];
-        if (ways > 1) HIP_TRY(hipStreamWaitEvent(t, ev.fork, 0));
+        if (ways > 1) HIP_TRY(hipStreamWaitEvent(t, c->side_fork, 0));
         if (split) {
             // the thirds take the bins from different ones on
             for (int k = 0; k < bins && !rc; ++k) {
@@ -899,41 +903,56 @@ int run_overlapped(dock_ctx *c, const Launch &L0, const Shapes &sh, hipStream_t 
             for (int q = bins * G - 1 - w; q >= 0 && !rc; q -= ways)
                 rc = run_list(c, L, sh, kStageAll, q / G, q, 100, t);
         }
-        if (ways > 1) HIP_TRY(hipEventRecord(ev.join[w], t));
+        if (ways > 1) HIP_TRY(hipEventRecord(c->side_join[w], t));
     }
     // Joined when every chain is enqueued (a wait in a queue that `s` shares with a
     // side stream holds up what is enqueued there later), and also after an error:
     // `s` then still orders all that was launched.
     for (int w = 0; ways > 1 && w < ways; ++w)
-        HIP_TRY(hipStreamWaitEvent(s, ev.join[w], 0));
+        HIP_TRY(hipStreamWaitEvent(s, c->side_join[w], 0));
     if (rc) return rc;
     if (L.oa.pcontacts) HIP_TRY(launch_rescore(L.ca, sa, la, L.oa, -1, sh.rescore_blocks, s));
     return DOCK_OK;
 }
 
-// Whether an eager call on `s` may put its chains on the side streams: nothing is left
-// on them, or only what calls on `s` put there.  Behind another stream's call the chains
-// would wait for that call and for all that its stream still has to do before it.
-bool side_streams_free(dock_ctx *c, hipStream_t s) {
-    if (!c->side_used || c->side_user == s) return true;
-    // (a query may not disturb a capture that the caller has under way elsewhere)
+// Whether all that the events were recorded behind has run.  (A query may not disturb a
+// capture that the caller has under way elsewhere.)
+template <class Events>
+bool all_done(const Events &events) {
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
     bool done = true;
-    for (hipEvent_t e : c->side_eager.join) done = done && hipEventQuery(e) == hipSuccess;
+    for (hipEvent_t e : events) done = done && hipEventQuery(e) == hipSuccess;
     if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
     if (!done) (void)hipGetLastError();
     return done;
 }
 
-// An eager call: its lists side by side, or, while the side streams hold another
-// stream's call, one after the other on `s` (calls in flight on several streams then
-// run beside each other, and none waits for another's stream).
-int run_eager(dock_ctx *c, const Launch &L, const Shapes &sh, hipStream_t s) {
-    if (!side_streams_free(c, s)) return run_sequence(c, L, sh, s, nullptr);
-    c->side_used = true;
-    c->side_user = s;
-    return run_overlapped(c, L, sh, s, c->side_eager);
+// Whether a call on `s` may put its chains on the side streams: nothing is left on them,
+// or only what calls on `s` put there.  Behind another stream's call the chains
+// would wait for that call and for all that its stream still has to do before it.
+bool side_streams_free(dock_ctx *c, hipStream_t s) {
+    return !c->side_used || c->side_user == s || all_done(c->side_join);
+}
+
+void drop_replay(Replay &r) {
+    (void)hipGraphExecDestroy(r.exec);
+    (void)hipEventDestroy(r.last);
+}
+
+// Room for one more captured sequence: of a full cache, those whose last launch has run
+// are dropped (not one that may still run).
+bool room_for_replay(dock_ctx *c) {
+    if (c->graphs.size() < kMaxReplays) return true;
+    for (auto it = c->graphs.begin(); it != c->graphs.end();) {
+        if (all_done(std::array<hipEvent_t, 1>{it->second.last})) {
+            drop_replay(it->second);
+            it = c->graphs.erase(it);
+        } else {
+            ++it;
+        }
+    }
+    return c->graphs.size() < kMaxReplays;
 }
 
 // The tile choice for these search settings: the autotuner's, else the defaults,
@@ -986,9 +1005,17 @@ int enqueue_batch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const 
         cap = hipStreamCaptureStatusNone;
     }
     const bool capturing = cap != hipStreamCaptureStatusNone;
-    auto run = [&]() { return capturing ? run_sequence(c, L, sh, s, nullptr) : run_eager(c, L, sh, s); };
-    // (a split library's kernels are long: eager, on the queues chosen here)
-    if (s == nullptr || scratch || (!capturing && split_library(L))) return run();
+    if (!capturing && side_ways(L) > 1 && side_streams_free(c, s)) {
+        c->side_used = true;
+        c->side_user = s;
+        return run_overlapped(c, L, sh, s);
+    }
+    // One stream: a call with one list, one beside another stream's (calls in flight on
+    // several streams run beside each other), or one that a caller captures.  Repeated, it
+    // is replayed from a graph.  (Chains on several streams are not captured: a program
+    // with four requests in flight, replayed from such branched graphs, ended with a
+    // segmentation fault on the host, which the same requests without branches do not.)
+    if (s == nullptr || scratch) return run_sequence(c, L, sh, s, nullptr);
     // graph key: everything the kernels' arguments and launch shapes depend on
     std::string key((const char *)&L, sizeof(L));
     key.append((const char *)&sh, sizeof(sh));
@@ -997,28 +1024,31 @@ int enqueue_batch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const 
     if (gi == c->graphs.end()) {
         if (c->seen_keys[key]++ == 0) {
             if (c->seen_keys.size() > 256) c->seen_keys.clear();
-            return run();  // first time: eager
+            return run_sequence(c, L, sh, s, nullptr);  // first time: eager
         }
-        if (c->graphs.size() >= 16) {
-            for (auto &kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
-            c->graphs.clear();
-        }
+        if (!room_for_replay(c)) return run_sequence(c, L, sh, s, nullptr);
         hipGraph_t graph = nullptr;
         HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed));
-        const int rc2 = run_overlapped(c, L, sh, s, c->side_captured);
+        const int rc2 = run_sequence(c, L, sh, s, nullptr);
         const hipError_t ec = hipStreamEndCapture(s, &graph);
         if (rc2) {
             if (graph) (void)hipGraphDestroy(graph);
             return rc2;
         }
         if (ec != hipSuccess) return fail(DOCK_EDEVICE, std::string("graph capture: ") + hipGetErrorString(ec));
-        hipGraphExec_t exec = nullptr;
-        const hipError_t ei = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+        Replay r;
+        hipError_t ei = hipGraphInstantiate(&r.exec, graph, nullptr, nullptr, 0);
         (void)hipGraphDestroy(graph);
         if (ei != hipSuccess) return fail(DOCK_EDEVICE, std::string("graph instantiate: ") + hipGetErrorString(ei));
-        gi = c->graphs.emplace(key, exec).first;
+        ei = hipEventCreateWithFlags(&r.last, hipEventDisableTiming);
+        if (ei != hipSuccess) {
+            (void)hipGraphExecDestroy(r.exec);
+            return fail(DOCK_EDEVICE, std::string("graph event: ") + hipGetErrorString(ei));
+        }
+        gi = c->graphs.emplace(key, r).first;
     }
-    HIP_TRY(hipGraphLaunch(gi->second, s));
+    HIP_TRY(hipGraphLaunch(gi->second.exec, s));
+    HIP_TRY(hipEventRecord(gi->second.last, s));
     return DOCK_OK;
 }
 
@@ -1204,10 +1234,8 @@ int dock_create(int device, uint64_t hbm_budget_bytes, dock_ctx **out) {
     auto event = [&](hipEvent_t *e) {
         made = made && hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess;
     };
-    for (SideEvents *ev : {&c->side_eager, &c->side_captured}) {
-        event(&ev->fork);
-        for (hipEvent_t &e : ev->join) event(&e);
-    }
+    event(&c->side_fork);
+    for (hipEvent_t &e : c->side_join) event(&e);
     if (!made) {
         (void)dock_destroy(c);
         return fail(DOCK_EDEVICE, "stream creation failed");
@@ -1233,16 +1261,14 @@ int dock_destroy(dock_ctx *c) {
     for (auto &kv : c->tables) hipFree(kv.second.d);
     for (auto &m : c->marks)
         for (auto &e : m) hipEventDestroy(e);
-    for (auto &kv : c->graphs) hipGraphExecDestroy(kv.second);
+    for (auto &kv : c->graphs) drop_replay(kv.second);
     for (auto t : c->submit_streams) hipStreamDestroy(t);
     for (auto t : c->plain_streams) hipStreamDestroy(t);
     for (auto e : c->plain_events) hipEventDestroy(e);
     for (auto t : c->side_streams) hipStreamDestroy(t);
-    for (const SideEvents &ev : {c->side_eager, c->side_captured}) {
-        if (ev.fork) hipEventDestroy(ev.fork);
-        for (hipEvent_t e : ev.join)
-            if (e) hipEventDestroy(e);
-    }
+    if (c->side_fork) hipEventDestroy(c->side_fork);
+    for (hipEvent_t e : c->side_join)
+        if (e) hipEventDestroy(e);
     delete c;
     return DOCK_OK;
 }

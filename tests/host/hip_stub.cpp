@@ -36,6 +36,7 @@ std::map<hipStream_t, std::deque<Op>> g_queue;
 std::set<hipStream_t> g_held;
 std::map<hipStream_t, Capture> g_capture;  // by origin stream
 std::set<hipStream_t> g_caller_capture;    // streams a caller captures (stub_capture)
+std::map<hipGraphExec_t, Token> g_exec;    // last launch of each
 std::map<std::string, int> g_fail;
 std::string g_log;
 std::string g_log_out;
@@ -217,9 +218,16 @@ hipError_t hipGraphInstantiate(hipGraphExec_t *x, hipGraph_t, hipGraphNode_t *, 
     return hipSuccess;
 }
 hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
-hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
-hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t s) {
+hipError_t hipGraphExecDestroy(hipGraphExec_t x) {
+    run_queues();
+    Token t = g_exec[x];
+    note(t && *t == 0 ? "graph destroyed in flight" : "graph destroyed", nullptr);
+    return hipSuccess;
+}
+hipError_t hipGraphLaunch(hipGraphExec_t x, hipStream_t s) {
     if (g_caller_capture.count(s)) return hipErrorIllegalState;
+    g_exec[x] = std::make_shared<int>(0);
+    g_queue[s].push_back({nullptr, g_exec[x]});
     return launched("graph", s);
 }
 

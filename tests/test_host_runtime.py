@@ -110,3 +110,46 @@ def test_calls_on_other_streams_do_not_wait_for_a_stuck_one(D, ctx, ligands, bin
     D.dock_ligands_batch(ctx, pid, dl, params, res, 0x54)
     assert len({line.split("stream=")[1] for line in _log(D) if line.startswith("dock ")}) == 3
     L.stub_all_idle()
+
+
+def test_captured_sequences_keep_to_one_stream(D, ctx):
+    # two requests of different lists in flight: what is captured for a replay is one
+    # stream's sequence (no branches)
+    L = D.lib()
+    pid, dl, params, res = _job(D, ctx, 40, (12, 200))
+    for held in (False, True):
+        D.dock_ligands_batch(ctx, pid, dl, params, res, 0x61)
+        L.stub_hold(0x61, 1 if held else 0)
+        for _ in range(3):
+            D.dock_ligands_batch(ctx, pid, dl, params, res, 0x61)
+            D.dock_ligands_batch(ctx, pid, dl, params, res, 0x62)
+    L.stub_hold(0x61, 0)
+    log = _log(D)
+    assert any(line.startswith("graph ") for line in log)
+    captured = [line for line in log if line.endswith("captured")]
+    assert captured and {re.search(r"stream=(\d+)", line).group(1) for line in captured} == {str(0x62)}
+    assert L.stub_all_idle()
+
+
+def test_cached_sequences_are_not_destroyed_in_flight(D, ctx):
+    # more distinct repeated requests than the cache holds, all still running
+    L = D.lib()
+    big = _job(D, ctx, 60, (20, 20))
+    pid = big[0]
+    # (of one list each: a list for one stream has no side streams to use)
+    jobs = [_job(D, ctx, 1 + i % 3, (9, 9 + i // 12), pid=pid) for i in range(40)]
+    D.dock_ligands_batch(ctx, pid, *big[1:], 0x63)  # the stream's workspace
+    L.stub_hold(0x63, 1)
+    for _ in range(2):
+        for _, dl, params, res in jobs:
+            D.dock_ligands_batch(ctx, pid, dl, params, res, 0x63)
+    log = _log(D)
+    assert sum(line.startswith("graph stream") for line in log) >= 8, log
+    assert not any("in flight" in line for line in log)
+    L.stub_hold(0x63, 0)
+    assert L.stub_all_idle()
+    for _, dl, params, res in jobs[20:] + jobs[20:]:  # done: they make room
+        D.dock_ligands_batch(ctx, pid, dl, params, res, 0x63)
+    log = _log(D)
+    assert any(line.startswith("graph destroyed") for line in log)
+    L.stub_all_idle()
