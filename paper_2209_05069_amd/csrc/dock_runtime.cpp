@@ -9,6 +9,7 @@
 // asynchronous submit/poll path with free-memory admission.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -729,10 +730,11 @@ std::string tune_key(const SearchArgs &sa) {
 
 // Atom bins a ligand of the library can be in: atoms are limited by the mask words
 // (k_prep refuses the others) and by the atoms that all ligands have together.
-int used_bins(const LibArgs &la) {
-    const long long most = std::min<long long>({64LL * la.mask_words, la.A_total, kMaxAtoms});
+int used_bins(int mask_words, long long atoms_total) {
+    const long long most = std::min<long long>({64LL * mask_words, atoms_total, kMaxAtoms});
     return most < 1 ? 0 : (int)((most - 1) >> 5) + 1;
 }
+int used_bins(const LibArgs &la) { return used_bins(la.mask_words, la.A_total); }
 
 int make_shapes(dock_ctx *c, const Launch &L, const BinShape *tile, Shapes *sh) {
     const SearchArgs &sa = L.sa;
@@ -865,11 +867,11 @@ int run_sequence(dock_ctx *c, const Launch &L, const Shapes &sh, hipStream_t s,
 constexpr int kSplitLigands = 2048;
 constexpr int kSplitShare = 50;
 
-bool split_library(const Launch &L) { return L.sa.groups == 1 && L.la.L >= kSplitLigands; }
+bool split_library(int ligands, int groups) { return groups == 1 && ligands >= kSplitLigands; }
 
 // Side streams a call's chains can use.
-int side_ways(const Launch &L) {
-    return split_library(L) ? kWays : std::min(kWays, used_bins(L.la) * L.sa.groups);
+int side_ways(int ligands, int bins, int groups) {
+    return split_library(ligands, groups) ? kWays : std::min(kWays, bins * groups);
 }
 
 // The batched launch sequence over several streams: after prep the work lists are
@@ -883,9 +885,9 @@ int run_overlapped(dock_ctx *c, const Launch &L0, const Shapes &sh, hipStream_t 
     const SearchArgs &sa = L.sa;
     const LibArgs &la = L.la;
     const int bins = used_bins(la), G = sa.groups;
-    const bool split = split_library(L);
+    const bool split = split_library(la.L, G);
     if (split) L.wa.chunk = (la.L + kWays - 1) / kWays;
-    const int ways = side_ways(L0);
+    const int ways = side_ways(la.L, bins, G);
     HIP_TRY(launch_reset(L.wa.counters, 0, kNumCounters, s));
     HIP_TRY(launch_prep(L.g, sa, la, L.wa, L.oa, s));
     if (ways > 1) HIP_TRY(hipEventRecord(c->side_fork, s));
@@ -915,24 +917,54 @@ int run_overlapped(dock_ctx *c, const Launch &L0, const Shapes &sh, hipStream_t 
     return DOCK_OK;
 }
 
-// Whether all that the events were recorded behind has run.  (A query may not disturb a
-// capture that the caller has under way elsewhere.)
+// While it lives, this thread's event and stream queries do not disturb a capture that
+// the caller has under way elsewhere.
+struct QueryScope {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    bool swapped;
+    QueryScope() : swapped(hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {}
+    ~QueryScope() {
+        if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        (void)hipGetLastError();  // "not ready" is an answer
+    }
+};
+
+// Whether all that the events were recorded behind has run.
 template <class Events>
 bool all_done(const Events &events) {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-    bool done = true;
-    for (hipEvent_t e : events) done = done && hipEventQuery(e) == hipSuccess;
-    if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
-    if (!done) (void)hipGetLastError();
-    return done;
+    QueryScope q;
+    for (hipEvent_t e : events)
+        if (hipEventQuery(e) != hipSuccess) return false;
+    return true;
 }
 
-// Whether a call on `s` may put its chains on the side streams: nothing is left on them,
-// or only what calls on `s` put there.  Behind another stream's call the chains
-// would wait for that call and for all that its stream still has to do before it.
-bool side_streams_free(dock_ctx *c, hipStream_t s) {
-    return !c->side_used || c->side_user == s || all_done(c->side_join);
+// Whether `s` has nothing left to do, or is done within `us` microseconds.
+bool stream_idle(hipStream_t s, int us) {
+    QueryScope q;
+    const auto end = std::chrono::steady_clock::now() + std::chrono::microseconds(us);
+    for (;;) {
+        if (hipStreamQuery(s) == hipSuccess) return true;
+        if (std::chrono::steady_clock::now() >= end) return false;
+    }
+}
+
+// Whether a call on `s` may put its chains on the side streams.  They start with a wait
+// for `s`, and what waits in a stream can hold up other streams of its hardware queue:
+// the side streams and `s` together are on all four of them.  So `s` has nothing left to
+// do but its previous call on the side streams, or a request's copy on a submit stream
+// without other requests, and the side streams hold no other stream's call.  Behind 70 ms of the caller's work on one
+// stream, with the chains waiting for it, a call on another stream takes 70 ms instead
+// of 3; without a look at what they still hold, it also queues behind all chains there.
+// What `s` does within kIdleWait microseconds (an event, a small copy) is waited for:
+// the call's kernels could not start before, and one after the other they take longer
+// than that (a split library's by tens of milliseconds).
+constexpr int kIdleWait = 50, kIdleWaitSplit = 1000;
+
+bool side_streams_free(dock_ctx *c, hipStream_t s, bool split) {
+    if (c->side_used && !all_done(c->side_join)) return c->side_user == s;
+    const auto &own = c->submit_streams;
+    if (std::find(own.begin(), own.end(), s) != own.end()) return c->stream_tickets[s] == 0;
+    return stream_idle(s, split ? kIdleWaitSplit : kIdleWait);
 }
 
 void drop_replay(Replay &r) {
@@ -982,6 +1014,20 @@ int enqueue_batch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const 
                   const dock_results *o, hipStream_t s, char *scratch = nullptr) {
     if (lib->n_ligands == 0) return DOCK_OK;
     const bool timed = c->timing && !scratch;
+    // A caller's own capture keeps to its stream: the side streams are the context's
+    // and would stay in that capture until it ends.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (s != nullptr && hipStreamIsCapturing(s, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        cap = hipStreamCaptureStatusNone;
+    }
+    const bool capturing = cap != hipStreamCaptureStatusNone;
+    // (looked at before anything of this call is enqueued)
+    const int groups = p->bin_mode ? kMaxGroups : 1;
+    const bool side = p->mode == DOCK_MODE_BATCHED && !timed && !capturing &&
+                      side_ways(lib->n_ligands, used_bins(lib->mask_words, lib->n_atoms_total),
+                                groups) > 1 &&
+                      side_streams_free(c, s, split_library(lib->n_ligands, groups));
     Launch L;
     int rc = prepare_launch(c, pk, lib, p, o, s, scratch, timed, &L);
     if (rc) return rc;
@@ -997,15 +1043,7 @@ int enqueue_batch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const 
     rc = make_shapes(c, L, bin_tiles(c, L.sa, lib->n_ligands).data(), &sh);
     if (rc) return rc;
     if (timed) return run_sequence(c, L, sh, s, &ev);
-    // A caller's own capture keeps to its stream: the side streams are the context's
-    // and would stay in that capture until it ends.
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (s != nullptr && hipStreamIsCapturing(s, &cap) != hipSuccess) {
-        (void)hipGetLastError();
-        cap = hipStreamCaptureStatusNone;
-    }
-    const bool capturing = cap != hipStreamCaptureStatusNone;
-    if (!capturing && side_ways(L) > 1 && side_streams_free(c, s)) {
+    if (side) {
         c->side_used = true;
         c->side_user = s;
         return run_overlapped(c, L, sh, s);

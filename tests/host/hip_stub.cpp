@@ -149,6 +149,10 @@ hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) {
     *s = (hipStream_t)(g_next++);
     return hipSuccess;
 }
+hipError_t hipStreamQuery(hipStream_t s) {
+    run_queues();
+    return g_queue[s].empty() ? hipSuccess : hipErrorNotReady;
+}
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) {
     *e = (hipEvent_t) new Event();

@@ -94,8 +94,12 @@ def test_calls_on_other_streams_do_not_wait_for_a_stuck_one(D, ctx, ligands, bin
     host = synth.library_uniform(4, 4, (12, 100), (0, 2))
     hres = D.HostResults(4, int(host.atom_off[-1]), int(host.rot_off[-1]), params2)
     D.dock_ligands_batch(ctx, pid, dl, params, res, 0x51)
+    L.stub_all_idle()
     L.stub_hold(0x51, 1)
+    _log(D)
     D.dock_ligands_batch(ctx, pid, dl, params, res, 0x51)
+    # nothing waits for it in another stream (whose hardware queue others may share)
+    assert {line.split("stream=")[1].split()[0] for line in _log(D)} == {str(0x51)}
     D.dock_ligands_batch(ctx, pid, other[1], params2, other[3], 0x52)
     assert L.stub_idle(0x52)
     D.dock_ligands_batch_noalloc(ctx, pid, other[1], params2, other[3], 0x53)
@@ -105,10 +109,12 @@ def test_calls_on_other_streams_do_not_wait_for_a_stuck_one(D, ctx, ligands, bin
     assert not L.stub_idle(0x51)
     L.stub_hold(0x51, 0)
     assert L.stub_idle(0x51) and L.stub_all_idle()
-    # the side streams are free again: the next call runs its lists side by side
-    _log(D)
-    D.dock_ligands_batch(ctx, pid, dl, params, res, 0x54)
-    assert len({line.split("stream=")[1] for line in _log(D) if line.startswith("dock ")}) == 3
+    # the side streams are free: the next calls run their lists side by side, one behind
+    # the other on one stream too
+    for _ in range(3):
+        _log(D)
+        D.dock_ligands_batch(ctx, pid, dl, params, res, 0x54)
+        assert len({line.split("stream=")[1] for line in _log(D) if line.startswith("dock ")}) == 3
     L.stub_all_idle()
 
 
