@@ -890,11 +890,18 @@ int run_overlapped(dock_ctx *c, const Launch &L0, const Shapes &sh, hipStream_t 
     const int ways = side_ways(la.L, bins, G);
     HIP_TRY(launch_reset(L.wa.counters, 0, kNumCounters, s));
     HIP_TRY(launch_prep(L.g, sa, la, L.wa, L.oa, s));
-    if (ways > 1) HIP_TRY(hipEventRecord(c->side_fork, s));
+    HIP_TRY(hipEventRecord(c->side_fork, s));
     int rc = DOCK_OK;
-    for (int w = 0; w < ways; ++w) {
-        const hipStream_t t = ways == 1 ? s : c->side_streams[w];
-        if (ways > 1) HIP_TRY(hipStreamWaitEvent(t, c->side_fork, 0));
+    auto check = [&](hipError_t e, const char *what) {
+        if (e != hipSuccess && !rc)
+            rc = fail(DOCK_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
+        return e == hipSuccess;
+    };
+    int forked = 0;  // side streams that have work of this call
+    for (int w = 0; w < ways && !rc; ++w) {
+        const hipStream_t t = c->side_streams[w];
+        if (!check(hipStreamWaitEvent(t, c->side_fork, 0), "fork")) break;
+        forked = w + 1;
         if (split) {
             // the thirds take the bins from different ones on
             for (int k = 0; k < bins && !rc; ++k) {
@@ -905,13 +912,16 @@ int run_overlapped(dock_ctx *c, const Launch &L0, const Shapes &sh, hipStream_t 
             for (int q = bins * G - 1 - w; q >= 0 && !rc; q -= ways)
                 rc = run_list(c, L, sh, kStageAll, q / G, q, 100, t);
         }
-        if (ways > 1) HIP_TRY(hipEventRecord(c->side_join[w], t));
     }
     // Joined when every chain is enqueued (a wait in a queue that `s` shares with a
     // side stream holds up what is enqueued there later), and also after an error:
-    // `s` then still orders all that was launched.
-    for (int w = 0; ways > 1 && w < ways; ++w)
-        HIP_TRY(hipStreamWaitEvent(s, c->side_join[w], 0));
+    // `s` then still orders all that was launched, or the host has waited for it.
+    bool recorded[kWays] = {};
+    for (int w = 0; w < forked; ++w)
+        recorded[w] = check(hipEventRecord(c->side_join[w], c->side_streams[w]), "join");
+    for (int w = 0; w < forked; ++w)
+        if (!recorded[w] || !check(hipStreamWaitEvent(s, c->side_join[w], 0), "join"))
+            (void)hipStreamSynchronize(c->side_streams[w]);
     if (rc) return rc;
     if (L.oa.pcontacts) HIP_TRY(launch_rescore(L.ca, sa, la, L.oa, -1, sh.rescore_blocks, s));
     return DOCK_OK;

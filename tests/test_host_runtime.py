@@ -159,3 +159,34 @@ def test_cached_sequences_are_not_destroyed_in_flight(D, ctx):
     log = _log(D)
     assert any(line.startswith("graph destroyed") for line in log)
     L.stub_all_idle()
+
+
+@pytest.mark.parametrize("ligands", [40, 2100])
+@pytest.mark.parametrize("name", ["launch", "hipEventRecord", "hipStreamWaitEvent"])
+def test_a_failed_call_leaves_nothing_beside_its_stream(D, ctx, name, ligands):
+    # whatever call of the runtime fails: what was launched on side streams is behind the
+    # caller's stream, or waited for, when the entry point returns (the caller may free
+    # its buffers then)
+    L = D.lib()
+    pid, dl, params, res = _job(D, ctx, ligands, (12, 200))
+    D.dock_ligands_batch(ctx, pid, dl, params, res, 0x71)
+    L.stub_all_idle()
+    failed = 0
+    for nth in range(1, 60):
+        _log(D)
+        L.stub_fail(name.encode(), nth)
+        try:
+            D.dock_ligands_batch(ctx, pid, dl, params, res, 0x71)
+        except D.DockError:
+            failed += 1
+        L.stub_fail(name.encode(), 0)
+        ops = [re.match(r"(.*) stream=(\d+)", line).groups() for line in _log(D)]
+        for t in {s for _, s in ops} - {str(0x71)}:
+            mine = [i for i, (op, s) in enumerate(ops) if s == t and op not in ("record", "wait")]
+            if not mine or ops[mine[-1]][0] == "synchronize":
+                continue
+            rec = [i for i, (op, s) in enumerate(ops) if s == t and op == "record" and i > mine[-1]]
+            assert rec and ("wait", str(0x71)) in ops[rec[0]:], (nth, t, ops)
+        assert L.stub_all_idle()
+    assert failed >= (30 if name == "launch" else 4)
+    D.dock_ligands_batch(ctx, pid, dl, params, res, 0x71)  # the context is as before
