@@ -232,7 +232,11 @@ typedef struct {
  * different streams do not wait for each other.
  * Results are valid once the stream reaches this point.  The library and the
  * results must stay allocated until then.  Internal workspace is allocated on
- * first use and kept per stream; growing it waits for that stream. */
+ * first use and kept per stream; growing it waits for that stream.  A caller's
+ * capture of `stream` records the batched form's kernels as one sequence when an
+ * earlier call there has allocated workspace and tables enough; they use that
+ * workspace, which is then kept until dock_destroy, so replays are ordered with
+ * the stream's other calls by the caller. */
 int dock_ligands_batch(dock_ctx *ctx, int32_t pocket, const dock_library *lib,
                        const dock_params *params, dock_results *out, void *stream);
 

@@ -107,6 +107,7 @@ struct Pocket {
 struct Workspace {
     void *base = nullptr;
     size_t bytes = 0;
+    bool captured = false;  // a caller's capture holds launches that use it
 };
 
 struct Tables {
@@ -169,6 +170,7 @@ struct dock_ctx {
     std::map<int32_t, Pocket> pockets;
     int32_t next_pocket = 1;
     std::map<hipStream_t, Workspace> ws;
+    std::vector<void *> retired;  // outgrown workspaces that a caller's capture still uses
     std::map<std::string, Tables> tables;
     // dock_ligands_batch_noalloc: host images of the tables it copied into the
     // scratch array, kept until destroy so no asynchronous copy outlives its source
@@ -392,9 +394,9 @@ int get_workspace(dock_ctx *c, hipStream_t s, size_t bytes, void **out) {
     if (w.bytes < bytes) {
         if (w.base) {
             HIP_TRY(hipStreamSynchronize(s));
-            HIP_TRY(hipFree(w.base));
-            w.base = nullptr;
-            w.bytes = 0;
+            if (w.captured) c->retired.push_back(w.base);  // (each a quarter larger at least)
+            else HIP_TRY(hipFree(w.base));
+            w = Workspace{};
         }
         const size_t nb = ws_grown_bytes(bytes);
         if (hipMalloc(&w.base, nb) != hipSuccess) {
@@ -1041,6 +1043,7 @@ int enqueue_batch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const 
     Launch L;
     int rc = prepare_launch(c, pk, lib, p, o, s, scratch, timed, &L);
     if (rc) return rc;
+    if (capturing && !scratch) c->ws[s].captured = true;
     std::array<hipEvent_t, 5> ev{};
     if (timed) {
         for (auto &e : ev) HIP_TRY(hipEventCreate(&e));
@@ -1058,12 +1061,13 @@ int enqueue_batch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const 
         c->side_user = s;
         return run_overlapped(c, L, sh, s);
     }
-    // One stream: a call with one list, one beside another stream's (calls in flight on
-    // several streams run beside each other), or one that a caller captures.  Repeated, it
-    // is replayed from a graph.  (Chains on several streams are not captured: a program
-    // with four requests in flight, replayed from such branched graphs, ended with a
-    // segmentation fault on the host, which the same requests without branches do not.)
-    if (s == nullptr || scratch) return run_sequence(c, L, sh, s, nullptr);
+    // One stream: a call that a caller captures, one with one list, or one beside another
+    // stream's (calls in flight on several streams run beside each other).  The last two
+    // are replayed from a graph when repeated.  (Chains on several streams are not
+    // captured: a program with four requests in flight, replayed from such branched
+    // graphs, ended with a segmentation fault on the host, which the same requests
+    // without branches do not.)
+    if (s == nullptr || scratch || capturing) return run_sequence(c, L, sh, s, nullptr);
     // graph key: everything the kernels' arguments and launch shapes depend on
     std::string key((const char *)&L, sizeof(L));
     key.append((const char *)&sh, sizeof(sh));
@@ -1306,6 +1310,7 @@ int dock_destroy(dock_ctx *c) {
     if (c->d_scored) hipFree(c->d_scored);
     if (c->plain_pose) hipFree(c->plain_pose);
     for (auto &kv : c->ws) hipFree(kv.second.base);
+    for (void *b : c->retired) hipFree(b);
     for (auto &kv : c->tables) hipFree(kv.second.d);
     for (auto &m : c->marks)
         for (auto &e : m) hipEventDestroy(e);

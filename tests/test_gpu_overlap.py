@@ -155,3 +155,33 @@ def test_calls_in_flight_on_several_streams(D, ctx):  # noqa: F811
                                               err_msg=k)
     for pid, params, dl, _ in jobs:
         D.dock_pocket_unload(ctx, pid)
+
+
+def test_warmed_up_calls_under_a_callers_capture(D, ctx):  # noqa: F811
+    # dock_ligands_batch captured by the caller after eager and replayed calls on the
+    # stream, and replayed behind a larger call that grows the stream's workspace
+    pid, params, dl, (ref, got, _) = _setup(D, ctx, 40, (3, 100), 96)
+    one = _setup(D, ctx, 6, (20, 20), 96)
+    big = _setup(D, ctx, 300, (3, 100), 97)
+    for pid_, params_, dl_, (ref_, got_, _) in ((pid, params, dl, (ref, got, None)), one):
+        st = torch.cuda.Stream()
+        for _ in range(4):
+            D.dock_ligands_batch(ctx, pid_, dl_, params_, ref_, st)
+            D.dock_ligands_batch(ctx, pid_, dl_, params_, got_, st)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        print("[case] warmed up, then captured", flush=True)
+        with torch.cuda.graph(g, stream=st):
+            D.dock_ligands_batch(ctx, pid_, dl_, params_, got_, st)
+        for rep in range(3):
+            for k in KEYS:
+                getattr(got_, k).zero_()
+            torch.cuda.synchronize()
+            if rep == 1:
+                D.dock_ligands_batch(ctx, big[0], big[2], big[1], big[3][0], st)
+            with torch.cuda.stream(st):
+                g.replay()
+            torch.cuda.synchronize()
+            _same(ref_, got_)
+    for j in (pid, one[0], big[0]):
+        D.dock_pocket_unload(ctx, j)

@@ -190,3 +190,28 @@ def test_a_failed_call_leaves_nothing_beside_its_stream(D, ctx, name, ligands):
         assert L.stub_all_idle()
     assert failed >= (30 if name == "launch" else 4)
     D.dock_ligands_batch(ctx, pid, dl, params, res, 0x71)  # the context is as before
+
+
+@pytest.mark.parametrize("ligands,atoms", [(40, (12, 200)), (5, (9, 20)), (2100, (12, 60))])
+def test_a_callers_capture_keeps_to_its_stream(D, ctx, ligands, atoms):
+    # also of a call that the stream has had before, and of one with a cached replay: the
+    # launches go to the caller's capture, and no later call frees what they use
+    L = D.lib()
+    pid, dl, params, res = _job(D, ctx, ligands, atoms)
+    big = _job(D, ctx, 2 * ligands, atoms, pid=pid)
+    for warm in range(4):
+        L.stub_all_idle()
+        L.stub_capture(0x81, 1)
+        _log(D)
+        D.dock_ligands_batch(ctx, pid, dl, params, res, 0x81)
+        log = _log(D)
+        L.stub_capture(0x81, 0)
+        assert any(line.startswith("dock ") for line in log)
+        assert all(line.split("stream=")[1] == str(0x81) for line in log)
+        assert not any(line.startswith(("graph", "beginCapture", "synchronize")) for line in log)
+        D.dock_ligands_batch(ctx, pid, dl, params, res, 0x81)
+    L.stub_all_idle()
+    _log(D)
+    D.dock_ligands_batch(ctx, big[0], big[1], big[2], big[3], 0x81)
+    assert not any(line.startswith("free") for line in _log(D))
+    L.stub_all_idle()
