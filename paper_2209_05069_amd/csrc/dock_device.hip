@@ -2734,6 +2734,15 @@ int select_sel_lds(int nmax, int waves, int R, int K) {
     return select_lds_bytes(nmax, waves, R, K, 1) <= (size_t)160 * 1024 ? 1 : 0;
 }
 
+// Whether the poses are kept in LDS, and the waves: the batched form decides by what
+// fits with kSelectGroup waves, whatever the tile, and a tile that needs more LDS than
+// there is loses waves (the path over global memory sums distances in another order).
+static int select_shape(int nmax, int R, int K, bool plain, int *waves) {
+    const int sel = select_sel_lds(nmax, plain ? *waves : kSelectGroup, R, K);
+    while (sel && !select_sel_lds(nmax, *waves, R, K)) --*waves;
+    return sel;
+}
+
 template <int NS>
 __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibArgs lib,
                                                 WorkArgs ws, OutArgs out, int bin, int lst, int single,
@@ -2749,7 +2758,7 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
     unsigned char *p = smem + Lds::rec(nmax, NS);
     u64 *rkey = (u64 *)p;                     // [R]
     int *order = (int *)(p + (size_t)R * 8);  // [R]
-    int *sel = (int *)(p + (size_t)R * 12);   // [K]
+    int *sel = (int *)(p + (size_t)R * 12);   // [K] restart, and its rank << 16
     int *nsel = sel + K;                      // [1]
     int *cflag = nsel + 1;                    // [W] candidate conflicts
     int *kinfo = cflag + W;                   // [1 + W] kept count, slot of each wave's candidate
@@ -2792,16 +2801,45 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
         const int D = 1 + sa.P * B;
         if (sel_lds) {
             // Select Poses with every wave: per round, wave w replays the restart
-            // ranked t0 + w and tests it against the poses kept so far (lanes over
-            // kept poses) and against the round's earlier candidates (lanes over
-            // atoms); one thread then takes the round's candidates in rank order,
-            // which is the greedy rule.
+            // ranked t0 + w and tests it against the poses kept so far and against the
+            // round's earlier candidates; one thread then takes the round's candidates
+            // in rank order, which is the greedy rule.  How a distance is summed depends
+            // on the two ranks alone, so that the number of waves changes no rounding:
+            // of two in the same group of G ranks over lanes, else over the atoms in
+            // order (a lane per earlier pose).
             const float lim = sa.dedup2 * (float)n;
+            const int G = single >= 0 ? kPlainSelectGroup : kSelectGroup;
             int ns = 0;
             for (int t0 = 0; t0 < R && ns < K; t0 += W) {
-                const int t = t0 + wave;
+                const int t = t0 + wave, g0 = t - t % G;  // g0: first rank of its group
                 float *cp = candL + (size_t)wave * n * 3;
                 int flag = 1;  // bit 0: conflicts with a kept pose (or no candidate)
+                // over the atoms in order / over lanes, to pose vp
+                auto in_order = [&](const float *vp) -> float {
+                    float ssd = 0.f;
+#pragma unroll 4
+                    for (int i = 0; i < n; ++i) {
+                        const float dx = cp[3 * i + 0] - vp[3 * i + 0];
+                        const float dy = cp[3 * i + 1] - vp[3 * i + 1];
+                        const float dz = cp[3 * i + 2] - vp[3 * i + 2];
+                        ssd = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, ssd)));
+                    }
+                    return ssd;
+                };
+                auto over_lanes = [&](const float *vp) -> float {
+                    float ssd = 0.f;
+#pragma unroll
+                    for (int q = 0; q < NS; ++q) {
+                        const int i = lane + 64 * q;
+                        if (i < n) {
+                            const float dx = cp[3 * i + 0] - vp[3 * i + 0];
+                            const float dy = cp[3 * i + 1] - vp[3 * i + 1];
+                            const float dz = cp[3 * i + 2] - vp[3 * i + 2];
+                            ssd = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, ssd)));
+                        }
+                    }
+                    return wave_sum(ssd);
+                };
                 if (t < R) {
                     const int r = uniform_int(order[t]);
                     if (single >= 0 && ws.rpose) {
@@ -2824,38 +2862,28 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
                     wave_lds_sync();
                     bool conflict = false;
                     if (sa.dedup2 > 0.f && ns > 0) {
-                        const bool ks = lane < ns;
-                        const float *kq = keptL + (size_t)(ks ? lane : 0) * n * 3;
-                        float ssd = 0.f;
-#pragma unroll 4
-                        for (int i = 0; i < n; ++i) {
-                            const float dx = cp[3 * i + 0] - kq[3 * i + 0];
-                            const float dy = cp[3 * i + 1] - kq[3 * i + 1];
-                            const float dz = cp[3 * i + 2] - kq[3 * i + 2];
-                            ssd = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, ssd)));
-                        }
+                        // (kept poses of its own group: the last ones, with W not a multiple of G)
+                        int na = ns;
+                        while (na > 0 && (uniform_int(sel[na - 1]) >> 16) >= g0) --na;
+                        const bool ks = lane < na;
+                        const float ssd = in_order(keptL + (size_t)(ks ? lane : 0) * n * 3);
                         conflict = __ballot(ks && ssd < lim) != 0ull;
+                        for (int k = na; k < ns; ++k)
+                            conflict = conflict || over_lanes(keptL + (size_t)k * n * 3) < lim;
                     }
                     flag = conflict ? 1 : 0;
                 }
                 __syncthreads();  // the round's candidates are in LDS
                 if (t < R && sa.dedup2 > 0.f) {
-#pragma unroll 4
-                    for (int v = 0; v < wave; ++v) {
-                        const float *vp = candL + (size_t)v * n * 3;
-                        float ssd = 0.f;
-#pragma unroll
-                        for (int q = 0; q < NS; ++q) {
-                            const int i = lane + 64 * q;
-                            if (i < n) {
-                                const float dx = cp[3 * i + 0] - vp[3 * i + 0];
-                                const float dy = cp[3 * i + 1] - vp[3 * i + 1];
-                                const float dz = cp[3 * i + 2] - vp[3 * i + 2];
-                                ssd = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, ssd)));
-                            }
-                        }
-                        if (wave_sum(ssd) < lim) flag |= 2 << v;
+                    const int ve = g0 > t0 ? g0 - t0 : 0;  // earlier candidates of other groups
+                    if (ve > 0) {
+                        const bool vs = lane < ve;
+                        const float ssd = in_order(candL + (size_t)(vs ? lane : 0) * n * 3);
+                        flag |= (int)__ballot(vs && ssd < lim) << 1;
                     }
+#pragma unroll 4
+                    for (int v = ve; v < wave; ++v)
+                        if (over_lanes(candL + (size_t)v * n * 3) < lim) flag |= 2 << v;
                 }
                 if (lane == 0) cflag[wave] = flag;
                 __syncthreads();
@@ -2867,7 +2895,7 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
                         if (nn >= K || (f & 1) || ((f >> 1) & kept)) continue;
                         kept |= 1 << w;
                         kinfo[1 + w] = nn;
-                        sel[nn++] = order[t0 + w];
+                        sel[nn++] = order[t0 + w] | (t0 + w) << 16;
                     }
                     kinfo[0] = nn;
                 }
@@ -2928,7 +2956,7 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
         }
         __syncthreads();
         const int ns = *nsel;
-        for (int s = threadIdx.x; s < ns; s += blockDim.x) ws.sel[(size_t)l * K + s] = sel[s];
+        for (int s = threadIdx.x; s < ns; s += blockDim.x) ws.sel[(size_t)l * K + s] = sel[s] & 0xFFFF;
         if (threadIdx.x == 0) ws.nsel[l] = ns;
         __syncthreads();
     }
@@ -3654,7 +3682,7 @@ template <int NS>
 static hipError_t launch_select_t(int bin, int lst, int blocks, int waves, const GridArgs &g,
                                   const SearchArgs &sa, const LibArgs &lib, const WorkArgs &ws,
                                   const OutArgs &out, int single, hipStream_t s) {
-    const int sel = select_sel_lds(bin_nmax(bin), waves, sa.R, sa.K);
+    const int sel = select_shape(bin_nmax(bin), sa.R, sa.K, single >= 0, &waves);
     const size_t lds = select_lds_bytes(bin_nmax(bin), waves, sa.R, sa.K, sel);
     hipFuncSetAttribute((const void *)k_select<NS>, hipFuncAttributeMaxDynamicSharedMemorySize,
                         (int)lds);
@@ -3863,8 +3891,8 @@ int dock_blocks_per_cu(int bin, int waves, int T) {
 template <int NS>
 static int select_occ(int bin, int waves, int R, int K) {
     int nb = 0;
-    const size_t lds = select_lds_bytes(bin_nmax(bin), waves, R, K,
-                                        select_sel_lds(bin_nmax(bin), waves, R, K));
+    const int sel = select_shape(bin_nmax(bin), R, K, false, &waves);
+    const size_t lds = select_lds_bytes(bin_nmax(bin), waves, R, K, sel);
     hipFuncSetAttribute((const void *)k_select<NS>, hipFuncAttributeMaxDynamicSharedMemorySize,
                         (int)lds);
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_select<NS>, 64 * waves, lds) !=

@@ -16,6 +16,8 @@ constexpr int kMaxGroups = 8;       // paper buckets: rotatable bonds in groups 
 constexpr int kMaxLists = kNumBins * kMaxGroups;  // work lists (atom bin x bond group)
 
 constexpr int kMaxTopK = 64;        // matches DOCK_MAX_TOP_K
+// k_select: ranks in a group whose distances are summed over lanes (batched, plain form)
+constexpr int kSelectGroup = 4, kPlainSelectGroup = 16;
 constexpr int kXcds = 8;            // gfx950: workgroups go round-robin to 8 XCDs of 32 CUs
 // per list: count, dock_next, select_next, falign_next, then one alignment queue per XCD
 constexpr int kNumCounters = (4 + kXcds) * kMaxLists;
