@@ -1163,10 +1163,13 @@ __global__ __launch_bounds__(512, C <= 4 ? (NS == 1 ? 5 : 4) : 2) void k_dock(Do
 // sample whose cell is not in the band reads its cube from global memory; both
 // give the same values, and the transform, blend and atom-order sum are those
 // of align_pose, so the scores are bit-identical.
-// The pad covers the rounding of a sample's distance from the grid centre (the
-// pose centroid lands there up to ~1e-5 cells, the turn keeps |r| up to a few
-// ulps): ~1e-4 cells at most, 200 times less than the pad.
+// The pad covers the rounding of a sample's distance from the grid centre (the turn
+// keeps |r| up to a few ulps: ~1e-4 cells, and pockets whose coordinates round by more
+// have no atlas) and the pose centroid's own distance from it: ~1e-5 cells for ligands
+// near their frame's origin, more for coordinates far from it; beyond kShellOffset the
+// ligand's samples read global memory.
 constexpr float kShellPad = 0.02f;
+constexpr float kShellOffset = 0.008f;
 constexpr float kBandWidth = 0.125f;
 constexpr int kShellRowsPerThread = 4;  // atlas kernels: rows per thread of 1024
 #ifndef DOCK_SHELL_BATCH
@@ -1233,6 +1236,14 @@ __device__ RowShell shell_row(int iy, int iz, float ecx, float ecy, float ecz, f
         r.merged = true;
     }
     return r;
+}
+
+// Whether a pose turns about the grid centre: its centroid (grid units) is within
+// `limit` of it.
+__device__ __forceinline__ bool centred(const GridArgs &g, float ex, float ey, float ez,
+                                        float limit) {
+    const float x = ex - g.acx, y = ey - g.acy, z = ez - g.acz;
+    return fmaf(x, x, fmaf(y, y, z * z)) <= limit * limit;
 }
 
 struct BandGeom {
@@ -1818,7 +1829,10 @@ __global__ __launch_bounds__(1024) void k_align(GridArgs g, SearchArgs sa, LibAr
                 ectr[2 * gg + 1] = make_float4(ex, ey, ez, 0.0f);
             }
             if (gg != 0) continue;
-            // each atom's band in the atlas (radius from the group's first restart)
+            // each atom's band in the atlas (radius from the group's first restart); none
+            // where the restarts turn about a point so far off the grid centre (by a
+            // rotated offset each) that samples may leave the padded band
+            const bool on_centre = centred(g, ex, ey, ez, kShellOffset);
 #pragma unroll
             for (int q = 0; q < NS; ++q) {
                 const int a = lane + 64 * q;
@@ -1830,7 +1844,7 @@ __global__ __launch_bounds__(1024) void k_align(GridArgs g, SearchArgs sa, LibAr
                 // clamps are the identity when the sphere stays inside [0, n-2]
                 const bool inside = ball_inside(tr, ex, ey, ez, rg);
                 int4 c0 = make_int4(-1, 0, 0, 0), c1 = make_int4(0, 0, 0, inside ? 1 : 0);
-                if (b < g.nbands) {
+                if (b < g.nbands && on_centre) {
                     const int4 gi = g.bands[2 * b], gj = g.bands[2 * b + 1];
                     const int size16 = gj.z / 16 + gj.y;
                     const int t = (int)(lib.type[a0 + a]);
@@ -2021,7 +2035,10 @@ __global__ __launch_bounds__(1024) void k_align(GridArgs g, SearchArgs sa, LibAr
 // Batched rigid alignment by score bounds.
 //
 // As for the shells, every alignment sample of an atom lies on the sphere of its
-// radius r about the grid centre.  On that sphere a sample is (polar position,
+// radius r about the grid centre, up to roundings and to twice the distance of the
+// start pose's centroid from that centre: zero but for the rounding of the ligand's own
+// centroid, which grows with its coordinates.  The bins are padded for kBoundOffset of
+// it; restarts farther off score every orientation.  On that sphere a sample is (polar position,
 // azimuth phi about the y axis), and the y rotations of a strip (restart, x
 // rotation i) only turn phi by 12 degrees each: its 30 samples share the polar
 // position and take phi0 + 12 j degrees.  At pocket load k_bounds stores, per
@@ -2140,12 +2157,13 @@ __global__ __launch_bounds__(256) void k_bounds(GridArgs g, BoundArgs bd,
             sin_range(p0, p1, sl, sh);
             sin_range(p0 + 0.25f, p1 + 0.25f, cl, ch);
             const float e7 = kBoundSinPad;
-            const float lo[3] = {g.acx + fminf(br.rlo * sl, br.rhi * sl) - br.rhi * e7,
+            const float side = fmaf(br.rhi, e7, bd.pad);
+            const float lo[3] = {g.acx + fminf(br.rlo * sl, br.rhi * sl) - side,
                                  g.acy + (south ? -br.yhi : br.ylo),
-                                 g.acz + fminf(br.rlo * cl, br.rhi * cl) - br.rhi * e7};
-            const float hi[3] = {g.acx + fmaxf(br.rlo * sh, br.rhi * sh) + br.rhi * e7,
+                                 g.acz + fminf(br.rlo * cl, br.rhi * cl) - side};
+            const float hi[3] = {g.acx + fmaxf(br.rlo * sh, br.rhi * sh) + side,
                                  g.acy + (south ? -br.ylo : br.yhi),
-                                 g.acz + fmaxf(br.rlo * ch, br.rhi * ch) + br.rhi * e7};
+                                 g.acz + fmaxf(br.rlo * ch, br.rhi * ch) + side};
             const float u = (box_max(g, t, lo, hi) - bd.vlow) / bd.step;
             // the integer above u, so that vlow + step * v is not below the maximum
             v = u > 0.0f ? (u < (float)kBoundMax ? (int)u + 1 : kBoundMax) : 1;
@@ -2398,6 +2416,7 @@ __global__ __launch_bounds__(64 * kBoundWaves, 4) void k_align_bound(GridArgs g,
         }
         int r[kBoundPerWave];
         float4 cw[kBoundPerWave], ce[kBoundPerWave];
+        bool off[kBoundPerWave];  // turns about a point too far off the grid centre
         bool out_any = false;
         const int rbase = grp * GR + wave * kBoundPerWave;
 #pragma unroll
@@ -2410,6 +2429,7 @@ __global__ __launch_bounds__(64 * kBoundWaves, 4) void k_align_bound(GridArgs g,
             cw[k] = make_float4(cx, cy, cz, 0.f);
             ce[k] = make_float4((cx - g.ox) * g.inv_h, (cy - g.oy) * g.inv_h,
                                 (cz - g.oz) * g.inv_h, 0.f);
+            off[k] = !centred(g, ce[k].x, ce[k].y, ce[k].z, kBoundOffset);
 #pragma unroll
             for (int q = 0; q < NS; ++q) {
                 const float rx = (Y.x[q] - cx) * g.inv_h, ry = (Y.y[q] - cy) * g.inv_h,
@@ -2562,7 +2582,7 @@ __global__ __launch_bounds__(64 * kBoundWaves, 4) void k_align_bound(GridArgs g,
                                   nf * 2e-3f * bd.step;
                 const float x = (low - nf * bd.vlow) / bd.step;
                 // not above 2, or NaN: every orientation stays
-                least[k] = x > 2.0f ? (uint32_t)fminf(x, 1e9f) - 1u : 1u;
+                least[k] = x > 2.0f && !off[k] ? (uint32_t)fminf(x, 1e9f) - 1u : 1u;
             }
             // the orientations that stay
             int nc = 0;

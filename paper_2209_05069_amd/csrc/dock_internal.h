@@ -63,6 +63,7 @@ constexpr int kBoundRec = kBoundSteps + 3;  // entries: a turn and 3 repeated
 constexpr int kMaxBoundBands = 1024;
 constexpr int kBoundMax = 511;     // entries are in [1, kBoundMax]
 constexpr int kBoundRun = 128;     // atoms whose bounds sum in 16 bits
+constexpr float kBoundOffset = 0.002f;  // cells a pose may turn off the grid centre
 struct BoundArgs {
     const unsigned short *tab;  // [ntypes][type_bytes / 2]
     const float *edge;          // [nb] lower radius of each band (grid units), edge[0] = 0

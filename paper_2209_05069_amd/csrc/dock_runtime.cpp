@@ -1104,16 +1104,27 @@ int enqueue_batch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const 
     return DOCK_OK;
 }
 
+// Bound on the rounding of a sample's coordinates in grid units: 16 ulps of the farthest
+// grid coordinate from the frame's origin.
+double grid_rounding(const GridArgs &g) {
+    const double far = std::max({std::fabs((double)g.ox * g.inv_h) + g.nx,
+                                 std::fabs((double)g.oy * g.inv_h) + g.ny,
+                                 std::fabs((double)g.oz * g.inv_h) + g.nz});
+    return far * std::ldexp(1.0, -20);
+}
+constexpr double kMaxGridRounding = 0.01;
+
 // Shell atlas of the alignment kernel: band geometry (pass 1), then the bands
 // that fit one workgroup's LDS, for every type (pass 2).  Grids wider than 256
-// cells in x keep no atlas (every alignment sample reads global memory).
+// cells in x, or whose coordinates round by more than the bands are padded for, keep no
+// atlas (every alignment sample reads global memory).
 int build_atlas(dock_ctx *c, Pocket &pk) {
     GridArgs &g = pk.g;
     g.atlas = nullptr;
     g.bands = nullptr;
     g.blob16 = nullptr;
     g.nbands = 0;
-    if (g.nx > 256) return DOCK_OK;
+    if (g.nx > 256 || grid_rounding(g) > kMaxGridRounding) return DOCK_OK;
     const size_t ib = (size_t)2 * kMaxBands * sizeof(int4);
     if (hipMalloc(&pk.d_bands, ib) != hipSuccess) {
         (void)hipGetLastError();
@@ -1175,14 +1186,9 @@ int build_bounds(Pocket &pk, const float *d_vals) {
     const GridArgs &g = pk.g;
     BoundArgs bd{};
     const int nmax = std::max(g.nx, std::max(g.ny, g.nz));
-    const float o[3] = {g.ox, g.oy, g.oz};
-    const int dim[3] = {g.nx, g.ny, g.nz};
-    double far = 0;
-    for (int a = 0; a < 3; ++a)
-        far = std::max(far, std::fabs((double)o[a] * g.inv_h) + dim[a]);
-    const double rounding = far * std::ldexp(1.0, -20);
-    if (rounding > 0.01) return DOCK_OK;
-    bd.pad = 0.01f + (float)rounding;
+    const double rounding = grid_rounding(g);
+    if (rounding > kMaxGridRounding) return DOCK_OK;
+    bd.pad = 2.0f * kBoundOffset + 0.001f + (float)rounding;
     std::vector<float> edge;
     std::vector<int4> band;
     size_t off = 0;
@@ -1231,7 +1237,7 @@ int build_bounds(Pocket &pk, const float *d_vals) {
         return DOCK_OK;
     }
     const float vmax = value(h[0]), vmin = value(~h[1]);
-        bd.vlow = vmax > 0.f ? std::max(vmin, -0.5f * vmax) : vmin;
+    bd.vlow = vmax > 0.f ? std::max(vmin, -0.5f * vmax) : vmin;
     bd.mag = std::max(std::fabs(vmax), std::fabs(bd.vlow));
     bd.step = std::max((vmax - bd.vlow + 1e-5f * bd.mag) / (float)(kBoundMax - 2), 1e-30f);
     bd.tab = tab;

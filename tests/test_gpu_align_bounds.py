@@ -63,3 +63,37 @@ def test_pocket_without_bounds_takes_the_same_orientations(D, ctx, kind, atoms, 
     b, _ = run_batch(D, ctx, synth.Pocket(off, pk.spacing, pk.origin), lib, q, **kw)
     for k in ("trace", "restart_score", "pose_score", "pose_xyz", "final_trace"):
         np.testing.assert_array_equal(a[k], b[k], err_msg=k)
+
+
+@pytest.mark.parametrize("align_steps", [30, 20])
+@pytest.mark.parametrize("shift", [300.0, 6e4, 1e6, 4e6, 2e7])
+def test_ligands_far_from_their_origin(D, ctx, shift, align_steps):  # noqa: F811
+    # a ligand's coordinates round in its own frame, and the centroid of its start pose
+    # misses the grid centre by that much: the batched alignment takes the orientations
+    # of the plain form, which samples every one from global memory
+    pk = synth.pocket_gaussians(74, 4, 48, 0.25, 60, 4.0)
+    lib = synth.library_from_sizes(75, [9, 31, 40, 66, 100, 150], [0] * 6)
+    lib.xyz = (lib.xyz + np.array([shift, -0.7 * shift, 0.4 * shift])).astype(np.float32)
+    q = synth.start_quats(76, 19)
+    kw = dict(torsion_steps=16, sweep_passes=1, align_steps=align_steps, top_k=4, dedup_rmsd=0.0)
+    print(f"[case] far ligands {shift} A={align_steps}", flush=True)
+    a, _ = run_batch(D, ctx, pk, lib, q, **kw)
+    b, _ = run_batch(D, ctx, pk, lib, q, mode=D.DOCK_MODE_PLAIN, **kw)
+    for k in ("trace", "restart_score", "pose_score", "pose_xyz"):
+        np.testing.assert_array_equal(a[k], b[k], err_msg=k)
+
+
+@pytest.mark.parametrize("align_steps", [30, 20])
+@pytest.mark.parametrize("shift", [300.0, 4e3, 6e4, 1e6])
+def test_pockets_far_from_the_origin(D, ctx, shift, align_steps):  # noqa: F811
+    pk = synth.pocket_gaussians(74, 4, 48, 0.25, 60, 4.0)
+    o = tuple(float(np.float32(x + s * shift)) for x, s in zip(pk.origin, (1.0, -0.7, 0.4)))
+    pk = synth.Pocket(pk.values, pk.spacing, o)
+    lib = synth.library_from_sizes(75, [9, 31, 40, 66, 100, 150], [0] * 6)
+    q = synth.start_quats(76, 19)
+    kw = dict(torsion_steps=16, sweep_passes=1, align_steps=align_steps, top_k=4, dedup_rmsd=0.0)
+    print(f"[case] far pocket {shift} A={align_steps}", flush=True)
+    a, _ = run_batch(D, ctx, pk, lib, q, **kw)
+    b, _ = run_batch(D, ctx, pk, lib, q, mode=D.DOCK_MODE_PLAIN, **kw)
+    for k in ("trace", "restart_score", "pose_score", "pose_xyz"):
+        np.testing.assert_array_equal(a[k], b[k], err_msg=k)
