@@ -839,8 +839,9 @@ __device__ int torsion_decide(Pose<NS> &Y, int n, const u64 *mrow, int a, int b,
     // each other at (height difference, radius difference) about the axis; pairs that
     // may come within the bump distance are listed, and the list is tested 64 pairs
     // at a time, a lane per pair (bump_pairs).  The filter's limit is above what
-    // the roundings of both forms of the distance can differ by (Cq is up to about
-    // (2 |V|)^2, its terms round at 2^-24 of that).
+    // the roundings of both forms of the distance can differ by: Cq is up to about
+    // (2 |V|)^2, its terms round at 2^-24 of that; and P0 rounds at the coordinates' own
+    // magnitude, which the axial form does not (see torsion_args).
     u64 bumped[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) bumped[c] = 0ull;
@@ -852,8 +853,7 @@ __device__ int torsion_decide(Pose<NS> &Y, int n, const u64 *mrow, int a, int b,
     float reach[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s)
-        reach[s] = fmaf(lim, 1.0f + 2e-3f,
-                        fmaf(fmaf(rad[s], rad[s], hgt[s] * hgt[s]), 1e-4f, 1e-3f));
+        reach[s] = fmaf(fmaf(rad[s], rad[s], hgt[s] * hgt[s]), 1e-4f, g.reach);
     wave_lds_sync();  // the frames
     // the moving atoms in order: their bits, and each one's far row a step ahead
     int q = 0, sw = 0;
@@ -3613,6 +3613,12 @@ static TorsionArgs torsion_args(const GridArgs &g, const SearchArgs &sa) {
     t.ox = g.ox; t.oy = g.oy; t.oz = g.oz;
     t.m2x = g.m2x; t.m2y = g.m2y; t.m2z = g.m2z;
     t.lim = sa.bump2g;
+    // P0 rounds at 2^-24 of the largest coordinate on each axis (1000 cells: a ligand that
+    // reaches out of the grid), so that a distance near the limit is off by up to `off`
+    const double far = 1000.0 + std::fmax(std::fabs((double)g.ox), std::fmax(std::fabs((double)g.oy),
+                                                                   std::fabs((double)g.oz))) * g.inv_h;
+    const double off = 4.0 * far * std::ldexp(1.0, -24), lim = t.lim;
+    t.reach = (float)(lim * (1.0 + 2e-3) + 1e-3 + off * (2.0 * std::sqrt(lim) + off));
     t.T = sa.T;
     t.prune = sa.prune;
     t.tors = sa.tors;

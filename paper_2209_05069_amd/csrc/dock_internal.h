@@ -152,6 +152,7 @@ struct ContactArgs {
 struct TorsionArgs {
     float inv_h, ox, oy, oz;
     float m2x, m2y, m2z, lim;  // lim: (bump_dist / spacing)^2
+    float reach;               // lim and what the axial form of a distance may differ by
     float cw, sw, tw, sb;      // cos w, sin w, tan w, 0
     int T, prune;
     const float2 *tors;

@@ -36,3 +36,22 @@ def test_listed_bump_check_is_the_oracles(D, ctx, bump_dist):  # noqa: F811
     h, params = run_batch(D, ctx, pk, lib, q, torsion_steps=256, sweep_passes=1, align_steps=6,
                           top_k=2, bump_dist=bump_dist)
     check_all(D, pk, lib, q, h, params, label=f"bump-{bump_dist}")
+
+
+@pytest.mark.parametrize("plain", [True, False])
+@pytest.mark.parametrize("shift,bump_dist", [(3e3, 2.0), (3e5, 2.0), (2e6, 1.0), (2e6, 4.0), (8e6, 3.0)])
+def test_pruned_decisions_of_a_pocket_far_from_the_origin(D, ctx, shift, bump_dist, plain):  # noqa: F811
+    # coordinates round by up to half an Angstrom there: a pair that the tested form of the distance
+    # calls a bump is listed although its axial distance is a little above
+    pk = synth.pocket_gaussians(87, 4, 40, 0.25, 40, 4.0)
+    o = tuple(float(np.float32(x + s * shift)) for x, s in zip(pk.origin, (1.0, -0.7, 0.4)))
+    pk = synth.Pocket(pk.values, pk.spacing, o)
+    lib = synth.library_from_sizes(88, [40, 64, 65, 129], [9, 12, 14, 20])
+    q = synth.start_quats(89, 8)
+    kw = dict(torsion_steps=256, sweep_passes=2, align_steps=6, top_k=3, bump_dist=bump_dist,
+              mode=D.DOCK_MODE_PLAIN if plain else D.DOCK_MODE_BATCHED)
+    print(f"[case] bump lists, far pocket {shift} dist={bump_dist}", flush=True)
+    a, _ = run_batch(D, ctx, pk, lib, q, bump_prune=1, **kw)
+    b, _ = run_batch(D, ctx, pk, lib, q, bump_prune=0, **kw)
+    for k in ("trace", "restart_score", "pose_score", "pose_xyz"):
+        np.testing.assert_array_equal(a[k], b[k], err_msg=k)
