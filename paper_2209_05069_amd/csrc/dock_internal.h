@@ -227,9 +227,17 @@ int align_bound_blocks_per_cu(int bin);
 // complement of the smallest, mm[2] = 1 when a value is not finite or beyond 1e30
 // (mm zeroed by the caller).
 hipError_t launch_value_range(const float *v, long long n, uint32_t *mm, hipStream_t s);
-// Fills the bound tables of every type.
-hipError_t launch_bounds(const GridArgs &g, const BoundArgs &bd, unsigned short *tab,
-                         hipStream_t s);
+// Low end and step of the bounds' integers, and the largest magnitude they stand for,
+// of a grid with these extremes.
+__host__ __device__ inline void bound_scale(float vmax, float vmin, float &vlow, float &step,
+                                            float &mag) {
+    vlow = vmax > 0.f ? fmaxf(vmin, -0.5f * vmax) : vmin;
+    mag = fmaxf(fabsf(vmax), fabsf(vlow));
+    step = fmaxf((vmax - vlow + 1e-5f * mag) / (float)(kBoundMax - 2), 1e-30f);
+}
+// Fills the bound tables of every type from the plain grid (mm: its extremes, as above).
+hipError_t launch_bounds(const GridArgs &g, const BoundArgs &bd, const float *vals,
+                         const uint32_t *mm, unsigned short *tab, hipStream_t s);
 // Smallest arena k_align accepts for the bin (fixed part plus a minimal region).
 size_t align_lds_min(int bin, int A, int R);
 int align_blocks_per_cu(int bin, int R, int A, int arena);

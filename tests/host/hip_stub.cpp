@@ -292,7 +292,7 @@ hipError_t launch_prep_one(const GridArgs &, const SearchArgs &, const LibArgs &
 hipError_t launch_atlas_count(const GridArgs &, int4 *, hipStream_t s) { return launched("atlas_count", s); }
 hipError_t launch_atlas_fill(const GridArgs &, int4 *, const int *, float4 *, int, hipStream_t s) { return launched("atlas_fill", s); }
 hipError_t launch_value_range(const float *, long long, uint32_t *, hipStream_t s) { return launched("value_range", s); }
-hipError_t launch_bounds(const GridArgs &, const BoundArgs &, unsigned short *, hipStream_t s) { return launched("bounds", s); }
+hipError_t launch_bounds(const GridArgs &, const BoundArgs &, const float *, const uint32_t *, unsigned short *, hipStream_t s) { return launched("bounds", s); }
 hipError_t launch_align(int bin, int lst, int blocks, int, const GridArgs &, const SearchArgs &, const LibArgs &, const WorkArgs &, hipStream_t s) { return launched(text("align bin=", bin, " lst=", lst, " blocks=", blocks), s); }
 hipError_t launch_align_bound(int bin, int lst, int blocks, const GridArgs &, const SearchArgs &, const LibArgs &, const WorkArgs &, const BoundArgs &, hipStream_t s) { return launched(text("align_bound bin=", bin, " lst=", lst, " blocks=", blocks), s); }
 hipError_t launch_dock(int bin, int lst, int blocks, int waves, const GridArgs &, const SearchArgs &, const LibArgs &, const WorkArgs &, hipStream_t s) { return launched(text("dock bin=", bin, " lst=", lst, " blocks=", blocks, " waves=", waves), s); }
