@@ -2838,7 +2838,7 @@ static __host__ __device__ size_t select_sel_offset(int nmax, int waves, int R, 
 
 size_t select_lds_bytes(int nmax, int waves, int R, int K, int sel_lds) {
     return select_sel_offset(nmax, waves, R, K) +
-           (sel_lds ? (size_t)(waves + K) * (size_t)nmax * 12 : 0);
+           (sel_lds ? (size_t)(waves + K) * ((size_t)nmax * 12 + (sel_lds == 2 ? 4 : 0)) : 0);
 }
 
 int select_sel_lds(int nmax, int waves, int R, int K) {
@@ -2848,10 +2848,12 @@ int select_sel_lds(int nmax, int waves, int R, int K) {
 // Whether the poses are kept in LDS, and the waves: the batched form decides by what
 // fits with kSelectGroup waves, whatever the tile, and a tile that needs more LDS than
 // there is loses waves (the path over global memory sums distances in another order).
+// 2: with room for an odd number of words a pose, so that lanes that each read one are on
+// different banks.
 static int select_shape(int nmax, int R, int K, bool plain, int *waves) {
     const int sel = select_sel_lds(nmax, plain ? *waves : kSelectGroup, R, K);
     while (sel && !select_sel_lds(nmax, *waves, R, K)) --*waves;
-    return sel;
+    return sel && select_lds_bytes(nmax, *waves, R, K, 2) <= (size_t)160 * 1024 ? 2 : sel;
 }
 
 template <int NS>
@@ -2873,8 +2875,9 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
     int *nsel = sel + K;                      // [1]
     int *cflag = nsel + 1;                    // [W] candidate conflicts
     int *kinfo = cflag + W;                   // [1 + W] kept count, slot of each wave's candidate
-    float *candL = (float *)(smem + select_sel_offset(nmax, W, R, K));  // [W][n][3]
-    float *keptL = candL + (size_t)W * nmax * 3;                         // [K][n][3]
+    const int pad = sel_lds == 2 ? 1 : 0;
+    float *candL = (float *)(smem + select_sel_offset(nmax, W, R, K));  // [W][ps] poses [n][3]
+    float *keptL = candL + (size_t)W * (nmax * 3 + pad);                 // [K][ps]
 
     if (single >= 0 && out.status[single] != 0) return;
     for (int pass = 0;; ++pass) {
@@ -2920,10 +2923,11 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
             // order (a lane per earlier pose).
             const float lim = sa.dedup2 * (float)n;
             const int G = single >= 0 ? kPlainSelectGroup : kSelectGroup;
+            const int ps = pad ? (3 * n) | 1 : 3 * n;  // words a pose
             int ns = 0;
             for (int t0 = 0; t0 < R && ns < K; t0 += W) {
                 const int t = t0 + wave, g0 = t - t % G;  // g0: first rank of its group
-                float *cp = candL + (size_t)wave * n * 3;
+                float *cp = candL + (size_t)wave * ps;
                 int flag = 1;  // bit 0: conflicts with a kept pose (or no candidate)
                 // over the atoms in order / over lanes, to pose vp
                 auto in_order = [&](const float *vp) -> float {
@@ -2971,30 +2975,41 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
                         }
                     }
                     wave_lds_sync();
-                    bool conflict = false;
-                    if (sa.dedup2 > 0.f && ns > 0) {
-                        // (kept poses of its own group: the last ones, with W not a multiple of G)
-                        int na = ns;
-                        while (na > 0 && (uniform_int(sel[na - 1]) >> 16) >= g0) --na;
-                        const bool ks = lane < na;
-                        const float ssd = in_order(keptL + (size_t)(ks ? lane : 0) * n * 3);
-                        conflict = __ballot(ks && ssd < lim) != 0ull;
-                        for (int k = na; k < ns; ++k)
-                            conflict = conflict || over_lanes(keptL + (size_t)k * n * 3) < lim;
-                    }
-                    flag = conflict ? 1 : 0;
+                    flag = 0;
                 }
-                __syncthreads();  // the round's candidates are in LDS
-                if (t < R && sa.dedup2 > 0.f) {
-                    const int ve = g0 > t0 ? g0 - t0 : 0;  // earlier candidates of other groups
-                    if (ve > 0) {
-                        const bool vs = lane < ve;
-                        const float ssd = in_order(candL + (size_t)(vs ? lane : 0) * n * 3);
-                        flag |= (int)__ballot(vs && ssd < lim) << 1;
+                // of other groups: kept poses (all but the last ones, those with W not a
+                // multiple of G) and the round's earlier candidates, a lane each
+                int na = ns;
+                while (na > 0 && (uniform_int(sel[na - 1]) >> 16) >= g0) --na;
+                const int ve = g0 > t0 ? g0 - t0 : 0;
+                auto others = [&]() {
+                    u64 kept = 0ull, cand = 0ull;  // (na < 64)
+                    for (int e0 = 0; e0 < na + ve; e0 += 64) {
+                        const int e = e0 + lane;
+                        const bool on = e < na + ve;
+                        const float ssd = in_order(e < na ? keptL + (size_t)e * ps
+                                                          : candL + (size_t)(on ? e - na : 0) * ps);
+                        const u64 hit = __ballot(on && ssd < lim);
+                        if (e0 == 0) {
+                            kept = hit & ((1ull << na) - 1ull);
+                            cand = hit >> na;
+                        } else {
+                            cand |= hit << (64 - na);
+                        }
                     }
+                    flag = (kept != 0ull ? 1 : 0) | (int)(uint32_t)cand << 1;
+                    for (int k = na; k < ns; ++k)
+                        if (over_lanes(keptL + (size_t)k * ps) < lim) flag |= 1;
+                };
+                const bool test = t < R && sa.dedup2 > 0.f;
+                const bool alone = G % W == 0;  // no earlier candidates of other groups
+                if (test && alone) others();
+                __syncthreads();  // the round's candidates are in LDS
+                if (test && !alone) others();
+                if (test) {
 #pragma unroll 4
                     for (int v = ve; v < wave; ++v)
-                        if (over_lanes(candL + (size_t)v * n * 3) < lim) flag |= 2 << v;
+                        if (over_lanes(candL + (size_t)v * ps) < lim) flag |= 2 << v;
                 }
                 if (lane == 0) cflag[wave] = flag;
                 __syncthreads();
@@ -3013,7 +3028,7 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
                 __syncthreads();
                 const int slot = kinfo[1 + wave];
                 if (slot >= 0) {
-                    float *kd = keptL + (size_t)slot * n * 3;
+                    float *kd = keptL + (size_t)slot * ps;
                     for (int e = lane; e < 3 * n; e += 64) kd[e] = cp[e];
                 }
                 ns = kinfo[0];
@@ -3021,7 +3036,9 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
             }
             if (threadIdx.x == 0) *nsel = ns;
             // kept poses to the workspace, for k_falign
-            for (int e = threadIdx.x; e < ns * n * 3; e += blockDim.x) accp[e] = keptL[e];
+            for (int k = 0; k < ns; ++k)
+                for (int e = threadIdx.x; e < 3 * n; e += blockDim.x)
+                    accp[(size_t)k * 3 * n + e] = keptL[(size_t)k * ps + e];
         } else if (wave == 0) {
             // greedy selection with plain-RMSD dedup; poses rebuilt from traces
             int ns = 0;
