@@ -2299,6 +2299,116 @@ __device__ __forceinline__ float bound_sector(float x, float z) {
     return x < 0.0f ? kTurn - p : p;
 }
 
+// Record in a band (rows per half sphere, azimuth sub-bins m) of a sample whose place on
+// the sphere, before its y rotation, is (rx, gy, qz); k0: its sector.
+__device__ __forceinline__ float bound_record(float rx, float gy, float qz, float inv_r,
+                                              float rows, float m, float &k0) {
+    // t and the sector fraction are below 1 by an ulp at least, so their rows and
+    // sub-bins are in range
+    const float t = __builtin_amdgcn_sqrtf(fmaxf(fmaf(-fabsf(gy), inv_r, 0.99999988f), 0.0f));
+    const float row = floorf(t * rows) + (gy < 0.0f ? rows : 0.0f);
+    const float p = bound_sector(rx, qz);
+    k0 = floorf(p);
+    return fmaf(row, m, floorf((p - k0) * m));
+}
+
+// Last band whose lower radius is not above rad.
+__device__ __forceinline__ int bound_band(const BoundArgs &bd, float rad) {
+    int lo = 0, hi = bd.nb - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (bd.edge[mid] <= rad) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// The smallest bound (an integer) that can be the best score of n atoms, given that some
+// orientation scores `got`.  Roundings of the two sums of n terms: their magnitudes add up
+// to at most 3 n mag where `got` is not below n vlow (a term is at most mag, and so the
+// negative ones at most 2 n mag together), n^2 2^-24 times 3 mag each; below that, every
+// orientation's bound is higher.  And of the bound's quantisation.
+__device__ __forceinline__ uint32_t bound_least(float got, int n, float vlow, float step,
+                                                float mag) {
+    const float nf = (float)n;
+    const float low = got - fabsf(got) * 1e-5f - nf * nf * 5e-7f * mag - nf * 2e-3f * step;
+    const float x = (low - nf * vlow) / step;
+    // not above 2, or NaN: every orientation stays
+    return x > 2.0f ? (uint32_t)fminf(x, 1e9f) - 1u : 1u;
+}
+
+// Orientations that stay, of 900, in alignments of made-up ligands: block (bin, probe) takes
+// 32 bin + 24 atoms of random types in a ball of 1.1 n^0.4 A, as wide as molecules of
+// n heavy atoms are, and adds their number to stay[bin].
+__global__ __launch_bounds__(960) void k_bound_probe(GridArgs g, BoundArgs bd,
+                                                     const uint32_t *__restrict__ mm,
+                                                     int *__restrict__ stay) {
+    __shared__ float4 unit[kMaxAtoms], band[kMaxAtoms];  // as k_align_bound; band.w: cubes' type
+    __shared__ u64 key[15];
+    __shared__ float part[15];
+    const int bin = blockIdx.x / kBoundProbes, n = 32 * bin + 24;
+    const int tid = threadIdx.x, wave = tid >> 6;
+    float vlow, step, mag;
+    bound_scale(unord_f32(mm[0]), unord_f32(~mm[1]), vlow, step, mag);
+    if (tid < n) {
+        uint32_t h = ((uint32_t)blockIdx.x * kMaxAtoms + (uint32_t)tid) * 2654435761u + 12345u;
+        auto next = [&]() -> float {  // in [0, 1)
+            h ^= h >> 16;
+            h *= 0x7feb352du;
+            h ^= h >> 15;
+            h *= 0x846ca68bu;
+            h ^= h >> 16;
+            return (float)(h >> 8) * (1.0f / 16777216.0f);
+        };
+        const float rad = 1.1f * powf((float)n, 0.4f) * g.inv_h * cbrtf(next());
+        const float z = 2.0f * next() - 1.0f, w = sqrtf(fmaxf(1.0f - z * z, 0.0f)), phi = next();
+        const int type = min((int)(next() * (float)g.ntypes), g.ntypes - 1);
+        const int4 bq = bd.band[bound_band(bd, rad)];
+        unit[tid] = make_float4(rad * w * __builtin_amdgcn_cosf(phi), rad * w * __builtin_amdgcn_sinf(phi),
+                                rad * z, rad > 1e-6f ? 1.0f / rad : 0.0f);
+        band[tid] = make_float4((float)bq.x, (float)bq.y,
+                                __uint_as_float((uint32_t)type * bd.type_bytes + (uint32_t)bq.z),
+                                __uint_as_float((uint32_t)type * g.type_bytes));
+    }
+    __syncthreads();
+    const bool real = tid < kBoundSteps * kBoundSteps;
+    const int ii = tid / kBoundSteps, j = tid - ii * kBoundSteps, i = min(ii, kBoundSteps - 1);
+    const float turn = 1.0f / (float)kBoundSteps;
+    const float ci = __builtin_amdgcn_cosf((float)i * turn), si = __builtin_amdgcn_sinf((float)i * turn);
+    uint32_t sum = 0u;
+#pragma unroll 8
+    for (int a = 0; a < n; ++a) {  // (n is a multiple of 8)
+        const float4 u = unit[a], b = band[a];
+        float k0;
+        const float rec = bound_record(u.x, fmaf(ci, u.y, -si * u.z), fmaf(si, u.y, ci * u.z), u.w,
+                                       b.x, b.y, k0);
+        const int s0 = (int)k0 + j, at = (int)rec * kBoundRec + (s0 < kBoundSteps ? s0 : s0 - kBoundSteps);
+        sum += bd.tab[__float_as_uint(b.z) / 2 + (uint32_t)at];
+    }
+    u64 top = wave_max_key(real ? ((u64)sum << 32) | (uint32_t)tid : 0ull);
+    if (lane_id() == 0) key[wave] = top;
+    __syncthreads();
+    for (int w = 0; w < 15; ++w) top = key[w] > top ? key[w] : top;
+    // the score of the orientation of the largest bound
+    const int best = (int)(uint32_t)top, bi = best / kBoundSteps, bj = best - bi * kBoundSteps;
+    float v = 0.0f;
+    if (tid < n) {
+        const float4 u = unit[tid];
+        const float2 x = make_float2(__builtin_amdgcn_cosf((float)bi * turn), __builtin_amdgcn_sinf((float)bi * turn));
+        const float2 y = make_float2(__builtin_amdgcn_cosf((float)bj * turn), __builtin_amdgcn_sinf((float)bj * turn));
+        const XStage xs = align_x(u.x, u.y, u.z, x, g.acy);
+        v = tri_v(make_tri(g), align_gx(xs, y, g.acx), xs.gy, align_gz(xs, y, g.acz),
+                  __float_as_uint(band[tid].w));
+    }
+    v = wave_sum(v);
+    if (lane_id() == 0) part[wave] = v;
+    __syncthreads();
+    float got = 0.0f;
+    for (int w = 0; w < 15; ++w) got += part[w];
+    const u64 bm = __ballot(real && sum >= bound_least(got, n, vlow, step, mag));
+    if (lane_id() == 0 && bm != 0ull) atomicAdd(&stay[bin], __popcll(bm));
+}
+
 // Low 24 bits of x, plus c.
 __device__ __forceinline__ uint32_t add_low24(uint32_t x, int c) {
     uint32_t r;
@@ -2492,13 +2602,7 @@ __global__ __launch_bounds__(64 * kBoundWaves, 4) void k_align_bound(GridArgs g,
                 const float dx = X.x[q] - c0x, dy = X.y[q] - c0y, dz = X.z[q] - c0z;
                 const float ux = dx * g.inv_h, uy = dy * g.inv_h, uz = dz * g.inv_h;
                 const float rad = sqrtf(fmaf(ux, ux, fmaf(uy, uy, uz * uz)));
-                int lo = 0, hi = bd.nb - 1;  // last band whose lower radius is not above rad
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (bd.edge[mid] <= rad) lo = mid;
-                    else hi = mid - 1;
-                }
-                const int4 bq = bd.band[lo];
+                const int4 bq = bd.band[bound_band(bd, rad)];
                 const uint32_t off = (uint32_t)lib.type[a0 + i] * bd.type_bytes + (uint32_t)bq.z;
                 dxyz[i] = make_float4(dx, dy, dz, xyzt[i].w);
                 unit[i] = make_float4(ux, uy, uz, rad > 1e-6f ? 1.0f / rad : 0.0f);
@@ -2557,13 +2661,8 @@ __global__ __launch_bounds__(64 * kBoundWaves, 4) void k_align_bound(GridArgs g,
                 const float rx = fmaf(s0.x, u.x, fmaf(s0.y, u.y, s0.z * u.z));
                 const float gy = fmaf(ax, u.x, fmaf(ay, u.y, az * u.z));
                 const float qz = fmaf(bx, u.x, fmaf(by, u.y, bz * u.z));
-                // t and the sector fraction are below 1 by an ulp at least, so their rows
-                // and sub-bins are in range
-                const float t = __builtin_amdgcn_sqrtf(fmaxf(fmaf(-fabsf(gy), u.w, 0.99999988f), 0.0f));
-                const float rowf = floorf(t * bq.x) + (gy < 0.0f ? bq.x : 0.0f);
-                const float p = bound_sector(rx, qz);
-                const float k0 = floorf(p);
-                const float rec = fmaf(rowf, bq.y, floorf((p - k0) * bq.y));
+                float k0;
+                const float rec = bound_record(rx, gy, qz, u.w, bq.x, bq.y, k0);
                 const uint32_t ki = (uint32_t)k0;
                 const uint32_t at = (uint32_t)(rec * (2.0f * (float)kBoundRec)) + 2u * ki;
                 soff = uniform_int(__float_as_int(bq.z));
@@ -2666,14 +2765,7 @@ __global__ __launch_bounds__(64 * kBoundWaves, 4) void k_align_bound(GridArgs g,
                     }
                 }
                 const float got = wave_sum(v);
-                // roundings: of the two sums of n terms (n^2 2^-24 of the largest term
-                // each, and relative to the score), and of the bound's quantisation
-                const float nf = (float)n;
-                const float low = got - fabsf(got) * 1e-5f - nf * nf * 5e-7f * bd.mag -
-                                  nf * 2e-3f * bd.step;
-                const float x = (low - nf * bd.vlow) / bd.step;
-                // not above 2, or NaN: every orientation stays
-                least[k] = x > 2.0f && !off[k] ? (uint32_t)fminf(x, 1e9f) - 1u : 1u;
+                least[k] = off[k] ? 1u : bound_least(got, n, bd.vlow, bd.step, bd.mag);
             }
             // the orientations that stay
             int nc = 0;
@@ -3950,6 +4042,12 @@ hipError_t launch_bounds(const GridArgs &g, const BoundArgs &bd, const float *va
                          const uint32_t *mm, unsigned short *tab, hipStream_t s) {
     if (bd.nb <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_bounds, dim3(8, bd.nb * g.ntypes), dim3(256), 0, s, g, bd, vals, mm, tab);
+    return hipGetLastError();
+}
+
+hipError_t launch_bound_probe(const GridArgs &g, const BoundArgs &bd, const uint32_t *mm, int *stay,
+                              hipStream_t s) {
+    hipLaunchKernelGGL(k_bound_probe, dim3(kNumBins * kBoundProbes), dim3(960), 0, s, g, bd, mm, stay);
     return hipGetLastError();
 }
 

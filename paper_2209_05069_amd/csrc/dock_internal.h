@@ -63,6 +63,7 @@ constexpr int kBoundRec = kBoundSteps + 3;  // entries: a turn and 3 repeated
 constexpr int kMaxBoundBands = 1024;
 constexpr int kBoundMax = 511;     // entries are in [1, kBoundMax]
 constexpr int kBoundRun = 128;     // atoms whose bounds sum in 16 bits
+constexpr int kBoundProbes = 16;   // made-up ligands per atom bin (k_bound_probe)
 constexpr float kBoundOffset = 0.002f;  // cells a pose may turn off the grid centre
 struct BoundArgs {
     const unsigned short *tab;  // [ntypes][type_bytes / 2]
@@ -71,6 +72,7 @@ struct BoundArgs {
     uint32_t bytes, type_bytes;
     int nb;                     // bands; 0: no bounds (every orientation is scored).  The
                                 // last band has no upper radius and holds kBoundMax.
+    uint32_t bins;              // atom bins whose alignment the bounds pay for (bits)
     float step, vlow;
     float mag;                  // max(|vlow|, |largest value|)
     float pad;                  // bin padding, grid units
@@ -218,7 +220,8 @@ hipError_t launch_align(int bin, int lst, int blocks, int arena, const GridArgs 
                         const SearchArgs &sa, const LibArgs &lib, const WorkArgs &ws,
                         hipStream_t s);
 // Alignment with score bounds (k_align_bound), for searches of kBoundSteps steps on
-// a pocket that has them; the same results as launch_align.
+// a pocket that has them; the same results as launch_align.  The caller takes it for the
+// bins of bd.bins.
 hipError_t launch_align_bound(int bin, int lst, int blocks, const GridArgs &g,
                               const SearchArgs &sa, const LibArgs &lib, const WorkArgs &ws,
                               const BoundArgs &bd, hipStream_t s);
@@ -238,6 +241,10 @@ __host__ __device__ inline void bound_scale(float vmax, float vmin, float &vlow,
 // Fills the bound tables of every type from the plain grid (mm: its extremes, as above).
 hipError_t launch_bounds(const GridArgs &g, const BoundArgs &bd, const float *vals,
                          const uint32_t *mm, unsigned short *tab, hipStream_t s);
+// Adds to stay[bin] how many of 900 orientations stay for each of kBoundProbes made-up
+// ligands of every atom bin (tables and cubes filled; stay zeroed by the caller).
+hipError_t launch_bound_probe(const GridArgs &g, const BoundArgs &bd, const uint32_t *mm, int *stay,
+                              hipStream_t s);
 // Smallest arena k_align accepts for the bin (fixed part plus a minimal region).
 size_t align_lds_min(int bin, int A, int R);
 int align_blocks_per_cu(int bin, int R, int A, int arena);

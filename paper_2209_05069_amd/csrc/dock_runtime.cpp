@@ -616,6 +616,9 @@ struct Launch {
     BoundArgs bd;  // nb = 0: the alignment runs from the shell atlas (k_align)
 };
 
+// Whether a bin's alignment takes the bounds.
+bool bounded(const Launch &L, int bin) { return L.bd.nb > 0 && (L.bd.bins >> bin & 1u); }
+
 // Tables, workspace and kernel arguments of a call on a device-resident library
 // and results.  With `scratch` (dock_ligands_batch_noalloc) the tables and the
 // workspace are placed in that buffer and nothing is allocated on the device.
@@ -757,11 +760,11 @@ int make_shapes(dock_ctx *c, const Launch &L, const BinShape *tile, Shapes *sh) 
             return fail(DOCK_EDEVICE, "device LDS per workgroup too small for the alignment kernel");
         sh->align_blocks[bin] = at_most(
             c->num_cu *
-            (L.bd.nb > 0 ? occupancy(c, kOccAlignBound, bin, 0, 0, 0,
-                                     [&] { return align_bound_blocks_per_cu(bin); })
-                         : occupancy(c, kOccAlign, bin, 0, sa.R, sa.A, [&] {
-                               return align_blocks_per_cu(bin, sa.R, sa.A, c->lds_arena);
-                           })),
+            (bounded(L, bin) ? occupancy(c, kOccAlignBound, bin, 0, 0, 0,
+                                         [&] { return align_bound_blocks_per_cu(bin); })
+                             : occupancy(c, kOccAlign, bin, 0, sa.R, sa.A, [&] {
+                                   return align_blocks_per_cu(bin, sa.R, sa.A, c->lds_arena);
+                               })),
             sa.R);
         sh->dock_blocks[bin] =
             at_most(c->num_cu * occupancy(c, kOccDock, bin, t.dock_waves, (sa.T + 63) / 64, 0,
@@ -800,10 +803,10 @@ int run_list(dock_ctx *c, const Launch &L, const Shapes &sh, int stages, int bin
     wa.bin_list += list_offset(sa.groups, lst, la.L, wa.chunk);
     auto part = [&](int blocks) { return std::max(1, (blocks * share + 99) / 100); };
     if (stages & kStageAlign)
-        HIP_TRY(L.bd.nb > 0 ? launch_align_bound(bin, lst, part(sh.align_blocks[bin]), g, sa, la, wa,
-                                                 L.bd, s)
-                            : launch_align(bin, lst, part(sh.align_blocks[bin]), c->lds_arena, g,
-                                           sa, la, wa, s));
+        HIP_TRY(bounded(L, bin) ? launch_align_bound(bin, lst, part(sh.align_blocks[bin]), g, sa,
+                                                     la, wa, L.bd, s)
+                                : launch_align(bin, lst, part(sh.align_blocks[bin]), c->lds_arena,
+                                               g, sa, la, wa, s));
     if (stages & kStageDock)
         HIP_TRY(launch_dock(bin, lst, part(sh.dock_blocks[bin]), sh.tile[bin].dock_waves, g, sa, la,
                             wa, s));
@@ -1189,14 +1192,24 @@ int build_atlas(dock_ctx *c, Pocket &pk, F &&meanwhile) {
 constexpr float kBoundBin = 0.25f;
 constexpr float kBoundRadial = 0.5f;
 constexpr float kBoundTop = 40.0f;
+constexpr int kBoundStayAt = 8;  // words from the extremes to the probes' counts
+// Orientations of 900 that may stay in a bin's probes for its alignment to take the bounds:
+// each costs a scattered sample an atom, and k_align, which samples all from LDS, is the
+// faster one from some number on.  They do not pay for grids with a few values far above the
+// others (no resolution is left below), with forbidden regions that every orientation
+// meets, or without a gradient.  Alignment of 400 to 600 ligands (ms; probes' count, bounds,
+// k_align): 10-30 atoms 212, 2.4, 2.8 and 315, 4.3, 2.6; 34-62 atoms 113, 5.5, 6.8 and 195,
+// 8.9, 6.3; 100-126 atoms 57, 10.6, 13.7, 93, 14.0, 13.8 and 204, 20, 11; 162-190 atoms 47,
+// 8.8, 14.1, 103, 17.9, 14.1 and 206, 23, 10; 226-254 atoms 91, 17.6, 22.1, 253, 34.6, 22.4
+// and 262, 42, 16; every orientation: 12, 37, 83, 77 and 121.
+constexpr int kBoundStay[kNumBins] = {200, 130, 120, 115, 105, 95, 115, 125};
 
-//
 // start_bounds makes the allocation and enqueues the grid's extremes on `s`, fill_bounds
-// the tables; finish_bounds waits and looks at the extremes.  Loading a pocket of 4 types
-// of 32^3, 64^3 and 96^3 values takes 0.62, 1.06 and 1.43 ms (0.77, 1.37 and 1.75 one
-// step after the other with a thread per entry), and 0.23, 0.43 and 0.73 without bounds:
-// that buys 0.1 ms a call of 8 small ligands, 18 ms a call of 2,500 ordinary ones, and
-// nothing in the plain form, with other step counts or for ligands without a call.
+// the tables and the probes; finish_bounds waits and looks at both.  Loading a pocket of 4
+// types of 32^3, 64^3 and 96^3 values takes 0.71, 1.16 and 1.53 ms (0.77, 1.37 and 1.75 one
+// step after the other with a thread per entry), of which the probes 0.1, and 0.23, 0.43
+// and 0.73 without bounds: that buys 0.2 ms a call of 8 small ligands, 18 ms a call of
+// 2,500 ordinary ones, and nothing in the plain form or with other step counts.
 int start_bounds(Pocket &pk, const float *d_vals, hipStream_t s) {
     const GridArgs &g = pk.g;
     BoundArgs &bd = pk.bd;
@@ -1248,16 +1261,22 @@ int start_bounds(Pocket &pk, const float *d_vals, hipStream_t s) {
 int fill_bounds(Pocket &pk, const float *d_vals, hipStream_t s) {
     if (pk.bd.nb == 0) return DOCK_OK;
     unsigned short *tab = const_cast<unsigned short *>(pk.bd.tab);
-    HIP_TRY(launch_bounds(pk.g, pk.bd, d_vals, (const uint32_t *)((char *)tab - 256), tab, s));
+    uint32_t *mm = (uint32_t *)((char *)tab - 256);
+    HIP_TRY(launch_bounds(pk.g, pk.bd, d_vals, mm, tab, s));
+    HIP_TRY(hipStreamSynchronize(nullptr));  // the cubes
+    HIP_TRY(launch_bound_probe(pk.g, pk.bd, mm, (int *)(mm + kBoundStayAt), s));
     return DOCK_OK;
 }
 
 int finish_bounds(Pocket &pk) {
     HIP_TRY(hipDeviceSynchronize());  // of the whole pocket
     if (pk.bd.nb == 0) return DOCK_OK;
-    uint32_t h[3];
+    uint32_t h[kBoundStayAt + kNumBins];
     HIP_TRY(hipMemcpy(h, (const char *)pk.bd.tab - 256, sizeof(h), hipMemcpyDeviceToHost));
-    if (h[2]) {  // a value that is not finite
+    for (int bin = 0; bin < kNumBins; ++bin)
+        if (h[kBoundStayAt + bin] <= (uint32_t)(kBoundStay[bin] * kBoundProbes))
+            pk.bd.bins |= 1u << bin;
+    if (h[2] || pk.bd.bins == 0) {  // a value that is not finite, or no bin they pay for
         pk.release_bounds();
         return DOCK_OK;
     }

@@ -38,6 +38,7 @@ std::map<hipStream_t, Capture> g_capture;  // by origin stream
 std::set<hipStream_t> g_caller_capture;    // streams a caller captures (stub_capture)
 std::map<hipGraphExec_t, Token> g_exec;    // last launch of each
 std::map<std::string, int> g_fail;
+int g_stay[kNumBins];  // orientations that stay in the probes of a pocket's bounds
 std::string g_log;
 std::string g_log_out;
 uintptr_t g_next = 0x1000;
@@ -268,6 +269,7 @@ void stub_fail(const char *name, int nth) {
     if (nth > 0) g_fail[name] = nth;
     else g_fail.erase(name);
 }
+void stub_stay(int bin, int orientations) { g_stay[bin] = orientations; }
 long long stub_allocs() { return (long long)g_allocs; }
 }
 
@@ -293,6 +295,10 @@ hipError_t launch_atlas_count(const GridArgs &, int4 *, hipStream_t s) { return 
 hipError_t launch_atlas_fill(const GridArgs &, int4 *, const int *, float4 *, int, hipStream_t s) { return launched("atlas_fill", s); }
 hipError_t launch_value_range(const float *, long long, uint32_t *, hipStream_t s) { return launched("value_range", s); }
 hipError_t launch_bounds(const GridArgs &, const BoundArgs &, const float *, const uint32_t *, unsigned short *, hipStream_t s) { return launched("bounds", s); }
+hipError_t launch_bound_probe(const GridArgs &, const BoundArgs &, const uint32_t *, int *stay, hipStream_t s) {
+    for (int b = 0; b < kNumBins; ++b) stay[b] = g_stay[b] * kBoundProbes;
+    return launched("bound_probe", s);
+}
 hipError_t launch_align(int bin, int lst, int blocks, int, const GridArgs &, const SearchArgs &, const LibArgs &, const WorkArgs &, hipStream_t s) { return launched(text("align bin=", bin, " lst=", lst, " blocks=", blocks), s); }
 hipError_t launch_align_bound(int bin, int lst, int blocks, const GridArgs &, const SearchArgs &, const LibArgs &, const WorkArgs &, const BoundArgs &, hipStream_t s) { return launched(text("align_bound bin=", bin, " lst=", lst, " blocks=", blocks), s); }
 hipError_t launch_dock(int bin, int lst, int blocks, int waves, const GridArgs &, const SearchArgs &, const LibArgs &, const WorkArgs &, hipStream_t s) { return launched(text("dock bin=", bin, " lst=", lst, " blocks=", blocks, " waves=", waves), s); }

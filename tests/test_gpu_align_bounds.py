@@ -15,6 +15,8 @@ def _pocket(kind, seed):
         pk.values[:] = 0.25
     elif kind == "walls":  # forbidden regions
         pk.values[pk.values < -0.2] = -1e6
+    elif kind == "peak":  # one value far above the others: few bins keep the bounds
+        pk.values[2, 16, 17, 15] = 60.0 * pk.values.max()
     elif kind == "negative":  # no positive value
         pk.values -= 3.0
     elif kind == "far":  # coordinates far from the origin
@@ -30,6 +32,8 @@ def _pocket(kind, seed):
     ("plain", [20, 40], 17),
     ("flat", [7, 40], 3),
     ("walls", [12, 66], 9),
+    ("walls", [130, 200, 256], 5),
+    ("peak", [12, 40, 66, 130, 200, 256], 5),
     ("negative", [12, 66], 8),
 ])
 def test_bounded_alignment_is_the_oracles(D, ctx, kind, atoms, restarts):  # noqa: F811

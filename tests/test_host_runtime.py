@@ -34,6 +34,7 @@ def D(stub, monkeypatch):
         f.argtypes = [ctypes.c_void_p, ctypes.c_int]
     L.stub_idle.argtypes = [ctypes.c_void_p]
     L.stub_fail.argtypes = [ctypes.c_char_p, ctypes.c_int]
+    L.stub_allocs.restype = ctypes.c_longlong
     return dock
 
 
@@ -215,3 +216,34 @@ def test_a_callers_capture_keeps_to_its_stream(D, ctx, ligands, atoms):
     D.dock_ligands_batch(ctx, big[0], big[1], big[2], big[3], 0x81)
     assert not any(line.startswith("free") for line in _log(D))
     L.stub_all_idle()
+
+
+def test_bounds_are_taken_where_few_orientations_stay(D, ctx):
+    # per atom bin; a pocket where they pay for no bin gives the tables' memory back
+    L = D.lib()
+
+    def route(pid=None):
+        pid, dl, params, res = _job(D, ctx, 40, (20, 250), pid=pid)
+        _log(D)
+        D.dock_ligands_batch(ctx, pid, dl, params, res, 0x91)
+        L.stub_all_idle()
+        pairs = [re.match(r"(align\w*) bin=(\d)", line) for line in _log(D)]
+        return pid, {int(m.group(2)): m.group(1) for m in pairs if m}
+
+    few, _ = route()
+    assert set(route(few)[1].values()) == {"align_bound"}
+    for b in (1, 4, 7):
+        L.stub_stay(b, 900)
+    before = L.stub_allocs()
+    some, got = route()
+    assert got == {b: "align" if b in (1, 4, 7) else "align_bound" for b in range(8)}
+    with_tables = L.stub_allocs() - before
+    for b in range(8):
+        L.stub_stay(b, 900)
+    before = L.stub_allocs()
+    none, got = route()
+    assert set(got.values()) == {"align"}
+    assert L.stub_allocs() - before == with_tables - 1
+    for b in range(8):
+        L.stub_stay(b, 0)
+    assert set(route(few)[1].values()) == {"align_bound"}  # each pocket keeps its own
