@@ -302,8 +302,11 @@ int dock_wait(dock_ctx *ctx, uint64_t ticket);
  * the fastest tile of each kernel is kept by the context for these search
  * settings (restarts, torsion_steps, align_steps, top_k, sweep_passes) and used
  * by every later batched call with them (results do not depend on the tiles).
+ * Libraries of 2,048 ligands and more run in thirds side by side: for these a
+ * kernel's tiles are kept only if they make the whole sample, in thirds, faster.
  * `sample` is device memory, as for dock_ligands_batch; `out` (NULL to skip)
- * receives DOCK_NUM_BINS entries.  The call allocates its own result buffers,
+ * receives DOCK_NUM_BINS entries: the tiles that a library as large as the sample
+ * takes.  The call allocates its own result buffers,
  * waits for `stream` and returns when done. */
 #define DOCK_NUM_BINS 8
 typedef struct {
@@ -314,8 +317,10 @@ typedef struct {
     int32_t falign_per_cu;   /* final alignment: workgroups per CU (0: all that fit) */
     int32_t falign_xcd;      /* final alignment: 1 = the ligands are split into 8 contiguous
                                 shares, one per XCD (workgroups go round-robin to the
-                                8 XCDs), so a ligand's kept poses share one L2; 0 = the
-                                grid's waves take (ligand, pose) items in turn */
+                                8 XCDs), so a ligand's kept poses share one L2 (launches
+                                of fewer than 8 workgroups go without); 0 = the grid's
+                                waves take (ligand, pose) items from a queue, or in turn
+                                when there is at most one each */
     float dock_ms, select_ms, falign_ms;  /* the chosen tiles on the sample */
     float dock_ms_default, select_ms_default, falign_ms_default;  /* the default tiles
                                                 (4, 4, 4 waves, all that fit) */

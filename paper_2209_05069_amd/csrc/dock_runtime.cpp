@@ -131,6 +131,12 @@ struct BinShape {
     int falign_xcd = 0;     // k_falign: 1 = each XCD takes a contiguous share of ligands
 };
 
+// Tile choices of every bin, for launches of the whole library and of its thirds (see
+// run_overlapped).
+struct Tuned {
+    std::array<BinShape, kNumBins> whole, split;
+};
+
 // Host image of a Tables allocation (offsets relative to its start).
 struct TableBlob {
     std::vector<char> bytes;
@@ -182,7 +188,7 @@ struct dock_ctx {
     char *scratch = nullptr;  // this device's copy of the scratch array
     std::map<std::array<int, 5>, int> occ;  // see occupancy()
     // per-bin tile choices of dock_autotune, by (R, T, A, K, P)
-    std::map<std::string, std::array<BinShape, kNumBins>> tuned;
+    std::map<std::string, Tuned> tuned;
     std::vector<hipStream_t> submit_streams;  // dock_submit: requests round-robin over these
     size_t next_submit = 0;
     std::map<uint64_t, Ticket> tickets;
@@ -879,8 +885,8 @@ constexpr int kSplitShare = 50;
 bool split_library(int ligands, int groups) { return groups == 1 && ligands >= kSplitLigands; }
 
 // Side streams a call's chains can use.
-int side_ways(int ligands, int bins, int groups) {
-    return split_library(ligands, groups) ? kWays : std::min(kWays, bins * groups);
+int side_ways(bool split, int bins, int groups) {
+    return split ? kWays : std::min(kWays, bins * groups);
 }
 
 // The batched launch sequence over several streams: after prep the work lists are
@@ -889,14 +895,13 @@ int side_ways(int ligands, int bins, int groups) {
 // the call's end on `s`.  They are all the context's own, made one after the other, so
 // that each has a hardware queue of its own (`s` may share one with a side stream, and
 // chains of one queue run one after the other).
-int run_overlapped(dock_ctx *c, const Launch &L0, const Shapes &sh, hipStream_t s) {
+int run_overlapped(dock_ctx *c, const Launch &L0, const Shapes &sh, hipStream_t s, bool split) {
     Launch L = L0;
     const SearchArgs &sa = L.sa;
     const LibArgs &la = L.la;
     const int bins = used_bins(la), G = sa.groups;
-    const bool split = split_library(la.L, G);
     if (split) L.wa.chunk = (la.L + kWays - 1) / kWays;
-    const int ways = side_ways(la.L, bins, G);
+    const int ways = side_ways(split, bins, G);
     HIP_TRY(launch_reset(L.wa.counters, 0, kNumCounters, s));
     HIP_TRY(launch_prep(L.g, sa, la, L.wa, L.oa, s));
     HIP_TRY(hipEventRecord(c->side_fork, s));
@@ -1011,9 +1016,9 @@ bool room_for_replay(dock_ctx *c) {
 // GPU (as long as its poses still fit the LDS).  With 4, 8 and 16 waves 32 ligands of
 // 20-80 atoms take 2.56, 2.11 and 1.90 ms, 300 take 6.46, 6.16 and 6.14, 1,000 of 16
 // atoms 3.36, 3.29 and 3.47, 2,500 of 20-80 atoms 42.6, 43.4 and 44.4.
-std::array<BinShape, kNumBins> bin_tiles(dock_ctx *c, const SearchArgs &sa, int L) {
+std::array<BinShape, kNumBins> bin_tiles(dock_ctx *c, const SearchArgs &sa, int L, bool split) {
     auto it = c->tuned.find(tune_key(sa));
-    if (it != c->tuned.end()) return it->second;
+    if (it != c->tuned.end()) return split ? it->second.split : it->second.whole;
     std::array<BinShape, kNumBins> tile{};
     const int want = L <= 512 ? 16 : L <= 1024 ? 8 : 4;
     for (int bin = 0; bin < kNumBins; ++bin)
@@ -1043,10 +1048,10 @@ int enqueue_batch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const 
     const bool capturing = cap != hipStreamCaptureStatusNone;
     // (looked at before anything of this call is enqueued)
     const int groups = p->bin_mode ? kMaxGroups : 1;
+    const bool split = split_library(lib->n_ligands, groups);
     const bool side = p->mode == DOCK_MODE_BATCHED && !timed && !capturing &&
-                      side_ways(lib->n_ligands, used_bins(lib->mask_words, lib->n_atoms_total),
-                                groups) > 1 &&
-                      side_streams_free(c, s, split_library(lib->n_ligands, groups));
+                      side_ways(split, used_bins(lib->mask_words, lib->n_atoms_total), groups) > 1 &&
+                      side_streams_free(c, s, split);
     Launch L;
     int rc = prepare_launch(c, pk, lib, p, o, s, scratch, timed, &L);
     if (rc) return rc;
@@ -1060,13 +1065,13 @@ int enqueue_batch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const 
         return enqueue_plain(c, lib, L.g, L.sa, L.la, L.wa, L.oa, L.ca, ev, s);
     // launch shapes (occupancy queries stay outside any graph capture)
     Shapes sh;
-    rc = make_shapes(c, L, bin_tiles(c, L.sa, lib->n_ligands).data(), &sh);
+    rc = make_shapes(c, L, bin_tiles(c, L.sa, lib->n_ligands, side && split).data(), &sh);
     if (rc) return rc;
     if (timed) return run_sequence(c, L, sh, s, &ev);
     if (side) {
         c->side_used = true;
         c->side_user = s;
-        return run_overlapped(c, L, sh, s);
+        return run_overlapped(c, L, sh, s, split);
     }
     // One stream: a call that a caller captures, one with one list, or one beside another
     // stream's (calls in flight on several streams run beside each other).  The last two
@@ -1674,10 +1679,11 @@ int dock_autotune(dock_ctx *c, int32_t pocket, const dock_library *lib, const do
             return DOCK_OK;
         };
         std::array<BinShape, kNumBins> pick;
+        std::array<dock_bin_tuning, kNumBins> reps{};
         for (int bin = 0; bin < kNumBins; ++bin) pick[bin] = defaults[bin];
         for (int bin = 0; bin < kNumBins; ++bin) {
             if (counts[bin] <= 0) continue;
-            dock_bin_tuning rep{};
+            dock_bin_tuning &rep = reps[bin];
             rep.ligands = counts[bin];
             const BinShape def = defaults[bin];
             BinShape &bs = pick[bin];
@@ -1752,9 +1758,78 @@ int dock_autotune(dock_ctx *c, int32_t pocket, const dock_library *lib, const do
             rep.falign_waves = bs.falign_waves;
             rep.falign_per_cu = bs.falign_per_cu;
             rep.falign_xcd = bs.falign_xcd;
-            if (out) out[bin] = rep;
         }
-        c->tuned[tune_key(sa)] = pick;
+        // In thirds side by side a launch shares the GPU with the other thirds' stages, and
+        // the tile that is fastest alone need not be (16-wave selections, alone the
+        // fastest for ligands of 20-100 atoms, take 3 to 5% more of the whole call there;
+        // all the tiles tuned alone 4 to 10%).  So each stage's tiles are taken for
+        // it only if the whole call on the sample, in thirds, is faster by 1%.
+        Tuned t{pick, pick};
+        if (G == 1 && side_streams_free(c, s, true)) {
+            std::array<BinShape, kNumBins> cur;
+            for (int bin = 0; bin < kNumBins; ++bin) cur[bin] = defaults[bin];
+            auto whole = [&](const std::array<BinShape, kNumBins> &tile, float *ms) -> int {
+                Shapes shp;
+                int e = make_shapes(c, Lc, tile.data(), &shp);
+                if (e) return e;
+                c->side_used = true;
+                c->side_user = s;
+                *ms = 3.4e38f;
+                for (int rep = 0; rep < 4; ++rep) {
+                    HIP_TRY(hipEventRecord(e0, s));
+                    e = run_overlapped(c, Lc, shp, s, true);
+                    if (e) return e;
+                    HIP_TRY(hipEventRecord(e1, s));
+                    HIP_TRY(hipEventSynchronize(e1));
+                    float v = 0.f;
+                    HIP_TRY(hipEventElapsedTime(&v, e0, e1));
+                    *ms = v < *ms ? v : *ms;
+                }
+                return DOCK_OK;
+            };
+            float best = 0.f;
+            int e = whole(cur, &best);
+            if (e) return e;
+            for (int stage = 0; stage < 3; ++stage) {
+                std::array<BinShape, kNumBins> with = cur;
+                for (int bin = 0; bin < kNumBins; ++bin) {
+                    if (stage == 0) with[bin].dock_waves = pick[bin].dock_waves;
+                    if (stage == 1) with[bin].select_waves = pick[bin].select_waves;
+                    if (stage == 2) {
+                        with[bin].falign_waves = pick[bin].falign_waves;
+                        with[bin].falign_per_cu = pick[bin].falign_per_cu;
+                        with[bin].falign_xcd = pick[bin].falign_xcd;
+                    }
+                }
+                float ms = 0.f;
+                e = whole(with, &ms);
+                if (e) return e;
+                if (ms < 0.99f * best) {
+                    cur = with;
+                    best = ms;
+                }
+            }
+            t.split = cur;
+        }
+        c->tuned[tune_key(sa)] = t;
+        const bool in_thirds = split_library(la.L, G);
+        for (int bin = 0; out && bin < kNumBins; ++bin) {
+            dock_bin_tuning &r = reps[bin];
+            if (in_thirds && r.ligands > 0) {
+                const BinShape &b = t.split[bin], &d = defaults[bin];
+                r.dock_waves = b.dock_waves;
+                r.select_waves = b.select_waves;
+                r.falign_waves = b.falign_waves;
+                r.falign_per_cu = b.falign_per_cu;
+                r.falign_xcd = b.falign_xcd;
+                if (b.dock_waves == d.dock_waves) r.dock_ms = r.dock_ms_default;
+                if (b.select_waves == d.select_waves) r.select_ms = r.select_ms_default;
+                if (b.falign_waves == d.falign_waves && b.falign_per_cu == d.falign_per_cu &&
+                    b.falign_xcd == d.falign_xcd)
+                    r.falign_ms = r.falign_ms_default;
+            }
+            out[bin] = r;
+        }
         return DOCK_OK;
     };
     const int rc3 = body();
@@ -1803,7 +1878,7 @@ int dock_set_tuning(dock_ctx *c, const dock_params *p, const dock_bin_tuning *ta
         }
         pick[bin] = b;
     }
-    c->tuned[tune_key(sa)] = pick;
+    c->tuned[tune_key(sa)] = Tuned{pick, pick};
     return DOCK_OK;
 }
 

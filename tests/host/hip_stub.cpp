@@ -26,6 +26,7 @@ struct Op {
 struct Event {
     Token last;
     hipStream_t on = nullptr;
+    size_t at = 0;  // place in the log
 };
 struct Capture {
     std::set<hipStream_t> members;   // the origin and the streams forked from it
@@ -171,6 +172,7 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
         g_queue[s].push_back({nullptr, ev->last});
     }
     ev->on = s;
+    ev->at = g_log.size();
     note("record", s);
     return hipSuccess;
 }
@@ -198,7 +200,19 @@ hipError_t hipEventQuery(hipEvent_t e) {
     return *ev->last == 2 ? hipErrorCapturedEvent : hipErrorNotReady;
 }
 hipError_t hipEventSynchronize(hipEvent_t e) { return hipEventQuery(e); }
-hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 1.f; return hipSuccess; }
+// A launch takes 1 ms, a selection of 16 waves 0.5 by itself and 2 beside a sweep.
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t a, hipEvent_t b) {
+    const std::string part = g_log.substr(((Event *)a)->at, ((Event *)b)->at - ((Event *)a)->at);
+    const bool beside = part.find("dock bin") != std::string::npos;
+    std::istringstream in(part);
+    *ms = 0.f;
+    for (std::string line; std::getline(in, line);) {
+        if (line.find("blocks=") == std::string::npos) continue;
+        const bool s16 = line.find("select") == 0 && line.find("waves=16") != std::string::npos;
+        *ms += !s16 ? 1.f : beside ? 2.f : 0.5f;
+    }
+    return hipSuccess;
+}
 hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *) { return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *st) {
     *st = g_caller_capture.count(s) || capture_of(s) ? hipStreamCaptureStatusActive
@@ -288,8 +302,17 @@ int falign_blocks_per_cu(int, int) { return 8; }
 int align_blocks_per_cu(int, int, int, int) { return 1; }
 int align_bound_blocks_per_cu(int) { return 4; }
 hipError_t launch_build_cubes(const float *, float4 *, int, int, int, int, hipStream_t s) { return launched("cubes", s); }
-hipError_t launch_reset(int *, int first, int count, hipStream_t s) { return launched(text("reset first=", first, " count=", count), s); }
-hipError_t launch_prep(const GridArgs &, const SearchArgs &, const LibArgs &, const WorkArgs &ws, const OutArgs &, hipStream_t s) { return launched(text("prep chunk=", ws.chunk), s); }
+hipError_t launch_reset(int *counters, int first, int count, hipStream_t s) {
+    std::fill(counters + first, counters + first + count, 0);
+    return launched(text("reset first=", first, " count=", count), s);
+}
+hipError_t launch_prep(const GridArgs &, const SearchArgs &sa, const LibArgs &la, const WorkArgs &ws, const OutArgs &, hipStream_t s) {
+    for (int l = 0; l < la.L; ++l) {
+        const int bin = (la.atom_off[l + 1] - la.atom_off[l] - 1) >> 5;
+        ws.counters[sa.groups > 1 ? bin * sa.groups : l / ws.chunk * kNumBins + bin] += 1;
+    }
+    return launched(text("prep chunk=", ws.chunk), s);
+}
 hipError_t launch_prep_one(const GridArgs &, const SearchArgs &, const LibArgs &, const WorkArgs &, const OutArgs &, int l, hipStream_t s) { return launched(text("prep_one l=", l), s); }
 hipError_t launch_atlas_count(const GridArgs &, int4 *, hipStream_t s) { return launched("atlas_count", s); }
 hipError_t launch_atlas_fill(const GridArgs &, int4 *, const int *, float4 *, int, hipStream_t s) { return launched("atlas_fill", s); }

@@ -247,3 +247,19 @@ def test_bounds_are_taken_where_few_orientations_stay(D, ctx):
     for b in range(8):
         L.stub_stay(b, 0)
     assert set(route(few)[1].values()) == {"align_bound"}  # each pocket keeps its own
+
+
+@pytest.mark.parametrize("sample", [60, 2100])
+def test_tuned_tiles_are_those_of_the_form_that_runs(D, ctx, sample):
+    # the model's selection is faster alone with 16 waves, and slower beside a sweep: a
+    # library in thirds keeps 4 waves, a short list takes the 16
+    pid, dl, params, res = _job(D, ctx, sample, (12, 120))
+    table = D.dock_autotune(ctx, pid, dl, params, 0xA1)
+    assert {t["select_waves"] for t in table if t["ligands"]} == {16 if sample < 2048 else 4}
+    for n, waves in ((60, 16), (2100, 4)):
+        _, dl, _, res = _job(D, ctx, n, (12, 120), pid=pid)
+        _log(D)
+        D.dock_ligands_batch(ctx, pid, dl, params, res, 0xA1)
+        D.lib().stub_all_idle()
+        seen = [re.match(r"select .* waves=(\d+)", line) for line in _log(D)]
+        assert {int(m.group(1)) for m in seen if m} == {waves}
