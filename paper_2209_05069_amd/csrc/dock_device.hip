@@ -74,17 +74,6 @@ __device__ __forceinline__ float wave_sum(float v) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
-__device__ __forceinline__ u64 wave_max_u64(u64 v) {
-#define DOCK_MAX_STEP(C, R)                 \
-    {                                       \
-        const u64 w = dpp_read64<C, R>(v);  \
-        v = w > v ? w : v;                  \
-    }
-    DOCK_DPP_STEPS(DOCK_MAX_STEP)
-#undef DOCK_MAX_STEP
-    return read_lane64(v, 63);
-}
-
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
     v = max(v, (uint32_t)dpp_read<0x111, 0xF>((int)v));
     v = max(v, (uint32_t)dpp_read<0x112, 0xF>((int)v));
@@ -673,13 +662,6 @@ __device__ __forceinline__ int mbcnt(u64 m) {
                                           __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// Scratch of the bump check, in the LDS of the candidate list that follows it.
-// Pairs of a slot up to which their terms are read from their lanes (7 VALU a pair)
-// rather than through LDS (3 a pair and 10 to lay them out).
-#ifndef KFEW
-#define KFEW 3
-#endif
-constexpr int kBumpFew = KFEW;
 // Moving atoms up to which a decision tests each row's pairs as they are found.  More
 // rows are listed first: finding a pair then costs less (10 VALU a row instead of 25),
 // a list costs about 120 more.  Torsion sweep of 2,500 ligands of 20-80 atoms and of
@@ -687,6 +669,7 @@ constexpr int kBumpFew = KFEW;
 // every decision listed, 21.3 and 11.4 ms with the line at 4 (21.5 and 11.8 ms at 2,
 // 21.3 and 11.4 ms at 8).
 constexpr int kBumpDirect = 4;
+// Scratch of the bump check, in the LDS of the candidate list that follows it.
 struct BumpLds {
     float4 coef[64];                // (Cq, Aq, Bq, 0) of pairs
     uint16_t pair[64 + kMaxAtoms];  // pairs: moving row << 8 | static atom
@@ -2445,8 +2428,9 @@ __device__ __forceinline__ int bound_slot(uint32_t e, int &oi, int &oj) {
     return k;
 }
 
-// Exact scores of the listed orientations (see bound_slot), 64 at a time, lane per orientation: align_pose's samples in its atom order.  best[k] is
-// raised to the best key of restart slot k.
+// Exact scores of the listed orientations (see bound_slot), 64 at a time, a lane per
+// orientation: align_pose's samples in its atom order.  best[k] is raised to the best key
+// of restart slot k.
 template <bool Inside>
 __device__ __forceinline__ void score_listed(const uint16_t *cand, int nc, const float4 *dxyz, int n,
                                              const int (&r)[kBoundPerWave],
@@ -2911,8 +2895,8 @@ __device__ void replay_pose(Pose<NS> &Y, const float4 *xyzt, const u64 *mask, co
 //   k_select: one workgroup per ligand (persistent over the bin list): ranks the
 //     restarts, rebuilds candidates from their traces and keeps them greedily;
 //     writes the kept poses (workspace acc_pose), their restarts and count;
-//   k_falign: one wave per (ligand, kept pose) item (the grid's waves take the
-//     bin's items in turn), or in the plain form one workgroup per kept pose
+//   k_falign: one wave per (ligand, pair of kept poses) item (the grid's waves take the
+//     bin's items from a queue or in turn), or in the plain form one workgroup per kept pose
 //     with the orientations split over its waves: alignment again about the
 //     pose centroid, final score and orientation;
 //   k_out: one workgroup per ligand: output order (final score desc, restart
