@@ -875,10 +875,12 @@ int run_sequence(dock_ctx *c, const Launch &L, const Shapes &sh, hipStream_t s,
 // on four streams), 32 ligands of 12-150 atoms 2.7 ms instead of 5.3.  A large
 // library's kernels fill the GPU each, but with different units: on half the
 // workgroups each, an alignment or final step (texture unit) of one third of the
-// library runs beside the sweep (VALU) of another: 16,000 ligands 379 ms instead of
-// 418, 2,500 ligands 43.3 instead of 47.9 (45.2 with lists side by side but unsplit);
-// in halves 393 and 45.3, in quarters 423 and 50.5, on 40 or 60 per cent of the
-// workgroups 390 and 389.
+// library runs beside the sweep (VALU) of another.  Lists of the whole library / thirds
+// (ms): 20-80 atoms 33.4 / 35.2 at 2,000 ligands, 43.4 / 44.7 at 2,600, 53.6 / 53.4 at
+// 3,200, 102 / 99 at 6,000, 270 / 260 at 16,000; 64 atoms 24.8 / 24.2 at 2,000; 16 atoms
+// 8.0 / 8.2 at 2,600, 45.5 / 47.7 at 16,000.  (When the line was drawn 2,500 ligands of
+// 20-80 atoms took 45.2 / 43.3 and 16,000 of 20-100 418 / 379; in halves 45.3 and 393, in
+// quarters 50.5 and 423, on 40 or 60 per cent of the workgroups 390 and 389.)
 constexpr int kSplitLigands = 2048;
 constexpr int kSplitShare = 50;
 
@@ -979,16 +981,16 @@ bool stream_idle(hipStream_t s, int us) {
 // without other requests, and the side streams hold no other stream's call.  Behind 70 ms of the caller's work on one
 // stream, with the chains waiting for it, a call on another stream takes 70 ms instead
 // of 3; without a look at what they still hold, it also queues behind all chains there.
-// What `s` does within kIdleWait microseconds (an event, a small copy) is waited for:
-// the call's kernels could not start before, and one after the other they take longer
-// than that (a split library's by tens of milliseconds).
-constexpr int kIdleWait = 50, kIdleWaitSplit = 1000;
+// What `s` does within some microseconds (an event, a copy) is waited for: the call's
+// kernels could not start before, and one after the other they take longer than that (8
+// ligands by 0.1 ms, 200 of 100-256 atoms by 19).
+int idle_wait(int ligands) { return std::min(1000, 50 + 5 * std::min(ligands, 1000)); }
 
-bool side_streams_free(dock_ctx *c, hipStream_t s, bool split) {
+bool side_streams_free(dock_ctx *c, hipStream_t s, int ligands) {
     if (c->side_used && !all_done(c->side_join)) return c->side_user == s;
     const auto &own = c->submit_streams;
     if (std::find(own.begin(), own.end(), s) != own.end()) return c->stream_tickets[s] == 0;
-    return stream_idle(s, split ? kIdleWaitSplit : kIdleWait);
+    return stream_idle(s, idle_wait(ligands));
 }
 
 void drop_replay(Replay &r) {
@@ -1051,7 +1053,7 @@ int enqueue_batch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const 
     const bool split = split_library(lib->n_ligands, groups);
     const bool side = p->mode == DOCK_MODE_BATCHED && !timed && !capturing &&
                       side_ways(split, used_bins(lib->mask_words, lib->n_atoms_total), groups) > 1 &&
-                      side_streams_free(c, s, split);
+                      side_streams_free(c, s, lib->n_ligands);
     Launch L;
     int rc = prepare_launch(c, pk, lib, p, o, s, scratch, timed, &L);
     if (rc) return rc;
@@ -1765,7 +1767,7 @@ int dock_autotune(dock_ctx *c, int32_t pocket, const dock_library *lib, const do
         // all the tiles tuned alone 4 to 10%).  So each stage's tiles are taken for
         // it only if the whole call on the sample, in thirds, is faster by 1%.
         Tuned t{pick, pick};
-        if (G == 1 && side_streams_free(c, s, true)) {
+        if (G == 1 && side_streams_free(c, s, la.L)) {
             std::array<BinShape, kNumBins> cur;
             for (int bin = 0; bin < kNumBins; ++bin) cur[bin] = defaults[bin];
             auto whole = [&](const std::array<BinShape, kNumBins> &tile, float *ms) -> int {

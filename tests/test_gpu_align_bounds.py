@@ -101,3 +101,19 @@ def test_pockets_far_from_the_origin(D, ctx, shift, align_steps):  # noqa: F811
     b, _ = run_batch(D, ctx, pk, lib, q, mode=D.DOCK_MODE_PLAIN, **kw)
     for k in ("trace", "restart_score", "pose_score", "pose_xyz"):
         np.testing.assert_array_equal(a[k], b[k], err_msg=k)
+
+
+@pytest.mark.parametrize("box", [(48, 30, 21), (20, 48, 33), (17, 24, 48), (3, 40, 40)])
+def test_bounds_of_a_box_that_is_no_cube(D, ctx, box):  # noqa: F811
+    # (nz, ny, nx): the bins' spheres leave the grid at different radii on each axis
+    pk = synth.pocket_gaussians(77, 4, 48, 0.5, 60, 5.0)
+    v = np.ascontiguousarray(pk.values[:, :box[0], :box[1], :box[2]])
+    pk = synth.Pocket(v, pk.spacing, pk.origin)
+    lib = synth.library_from_sizes(78, [4, 20, 33, 64, 90, 130], [0] * 6)
+    q = synth.start_quats(79, 18)
+    kw = dict(torsion_steps=16, sweep_passes=1, top_k=4, dedup_rmsd=0.0)
+    print(f"[case] bounds, box {box}", flush=True)
+    a, _ = run_batch(D, ctx, pk, lib, q, **kw)
+    b, _ = run_batch(D, ctx, pk, lib, q, mode=D.DOCK_MODE_PLAIN, **kw)
+    for k in ("trace", "restart_score", "pose_score", "pose_xyz"):
+        np.testing.assert_array_equal(a[k], b[k], err_msg=k)
