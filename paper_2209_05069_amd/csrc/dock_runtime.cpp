@@ -1211,6 +1211,20 @@ constexpr int kBoundStayAt = 8;  // words from the extremes to the probes' count
 // and 262, 42, 16; every orientation: 12, 37, 83, 77 and 121.
 constexpr int kBoundStay[kNumBins] = {200, 130, 120, 115, 105, 95, 115, 125};
 
+// The part of kBoundStay that holds for ligands of n atoms.  Molecules reach out by about
+// 0.8 n^1/2 A from their centre: where that passes the grid's nearest face, the samples of
+// the orientations that stay are clamped and tested one by one, and cost up to three times as
+// much, which k_align's band in LDS saves.  128 ligands on grids of 0.5 A (bounds' time /
+// k_align's; the grid's half extent by n^1/2, in cells): 88 atoms 0.7 at 2.2, 0.6 at 1.5,
+// 0.9-1.1 at 1.3, 1.5 at 1.1; 120 atoms 0.7-0.8 at 2.8, 0.8-0.9 at 1.7, 1.6 at 1.3, 2.2 at 1.0;
+// 184 atoms 0.9-1.2 at 2.2, 1.0-1.2 at 1.7, 1.7 at 1.4, 2.5 at 1.1; with 50 orientations 56
+// atoms 0.5 at 1.9, 0.6 at 1.4, 0.9 at 1.1, 1.3 at 0.9.
+double bound_share(const GridArgs &g, int n) {
+    const double half = 0.5 * (std::min(g.nx, std::min(g.ny, g.nz)) - 1) - 1.0;
+    const double reach = half / (g.inv_h * std::sqrt((double)n));
+    return std::min(1.0, std::max(0.25, 1.0 - 3.0 * (0.825 - reach)));
+}
+
 // start_bounds makes the allocation and enqueues the grid's extremes on `s`, fill_bounds
 // the tables and the probes; finish_bounds waits and looks at both.  Loading a pocket of 4
 // types of 32^3, 64^3 and 96^3 values takes 0.71, 1.16 and 1.53 ms (0.77, 1.37 and 1.75 one
@@ -1281,7 +1295,8 @@ int finish_bounds(Pocket &pk) {
     uint32_t h[kBoundStayAt + kNumBins];
     HIP_TRY(hipMemcpy(h, (const char *)pk.bd.tab - 256, sizeof(h), hipMemcpyDeviceToHost));
     for (int bin = 0; bin < kNumBins; ++bin)
-        if (h[kBoundStayAt + bin] <= (uint32_t)(kBoundStay[bin] * kBoundProbes))
+        if (h[kBoundStayAt + bin] <=
+            kBoundStay[bin] * kBoundProbes * bound_share(pk.g, 32 * bin + 24))
             pk.bd.bins |= 1u << bin;
     if (h[2] || pk.bd.bins == 0) {  // a value that is not finite, or no bin they pay for
         pk.release_bounds();

@@ -5,6 +5,7 @@ import os
 import re
 import subprocess
 
+import numpy as np
 import pytest
 
 import synth
@@ -247,6 +248,25 @@ def test_bounds_are_taken_where_few_orientations_stay(D, ctx):
     for b in range(8):
         L.stub_stay(b, 0)
     assert set(route(few)[1].values()) == {"align_bound"}  # each pocket keeps its own
+
+
+@pytest.mark.parametrize("shape,bins", [((64, 64, 64), range(8)), ((24, 24, 24), (0, 1)),
+                                        ((64, 64, 24), (0, 1)), ((8, 8, 8), ())])
+def test_bounds_need_fewer_orientations_where_ligands_reach_out_of_the_grid(D, ctx, shape, bins):
+    # 60 of 900 are few for every bin inside the grid (its limits are 95 to 200)
+    L = D.lib()
+    for b in range(8):
+        L.stub_stay(b, 60)
+    pid = D.dock_pocket_load(ctx, np.zeros((2,) + shape, np.float32), 0.5, (0.0, 0.0, 0.0))
+    for b in range(8):
+        L.stub_stay(b, 0)
+    _, dl, params, res = _job(D, ctx, 40, (20, 250), pid=pid)
+    _log(D)
+    D.dock_ligands_batch(ctx, pid, dl, params, res, 0x92)
+    L.stub_all_idle()
+    pairs = [re.match(r"(align\w*) bin=(\d)", line) for line in _log(D)]
+    got = {int(m.group(2)): m.group(1) for m in pairs if m}
+    assert got == {b: "align_bound" if b in bins else "align" for b in range(8)}
 
 
 @pytest.mark.parametrize("sample", [60, 2100])
