@@ -783,7 +783,7 @@ int make_shapes(dock_ctx *c, const Launch &L, const BinShape *tile, Shapes *sh) 
         int per_cu = occupancy(c, kOccFalign, bin, t.falign_waves, 0, 0,
                                [&] { return falign_blocks_per_cu(bin, t.falign_waves); });
         if (t.falign_per_cu > 0 && t.falign_per_cu < per_cu) per_cu = t.falign_per_cu;
-        const int pairs = (sa.K + 1) / 2;
+        const int pairs = (std::min(sa.K, sa.R) + 1) / 2;
         sh->falign_blocks[bin] =
             at_most(per_cu * c->num_cu, (pairs + t.falign_waves - 1) / t.falign_waves);
     }
