@@ -302,7 +302,8 @@ int dock_wait(dock_ctx *ctx, uint64_t ticket);
  * the fastest tile of each kernel is kept by the context for these search
  * settings (restarts, torsion_steps, align_steps, top_k, sweep_passes) and used
  * by every later batched call with them (results do not depend on the tiles).
- * Libraries of 2,048 ligands and more run in thirds side by side: for these a
+ * Libraries of 2,048 ligands and more (with restarts x atoms of 10 million and more)
+ * run in thirds side by side: for these a
  * kernel's tiles are kept only if they make the whole sample, in thirds, faster.
  * `sample` is device memory, as for dock_ligands_batch; `out` (NULL to skip)
  * receives DOCK_NUM_BINS entries: the tiles that a library as large as the sample

@@ -868,8 +868,8 @@ int run_sequence(dock_ctx *c, const Launch &L, const Shapes &sh, hipStream_t s,
     return DOCK_OK;
 }
 
-// The library size from which every side stream gets its own third of the library,
-// and the share of the GPU (per cent) a launch then takes.
+// The library size, and the work in restarts x atoms, from which every side stream gets its
+// own third of the library, and the share of the GPU (per cent) a launch then takes.
 // Chains of short kernels (few ligands in a bin) leave the GPU idle one after the
 // other; side by side 200 ligands of 100-256 atoms take 38.4 ms instead of 53.8 (43.1
 // on four streams), 32 ligands of 12-150 atoms 2.7 ms instead of 5.3.  A large
@@ -881,10 +881,19 @@ int run_sequence(dock_ctx *c, const Launch &L, const Shapes &sh, hipStream_t s,
 // 8.0 / 8.2 at 2,600, 45.5 / 47.7 at 16,000.  (When the line was drawn 2,500 ligands of
 // 20-80 atoms took 45.2 / 43.3 and 16,000 of 20-100 418 / 379; in halves 45.3 and 393, in
 // quarters 50.5 and 423, on 40 or 60 per cent of the workgroups 390 and 389.)
+// Three chains of half a GPU each cost more launches than they fill where the lists are
+// short in time.  Whole / thirds (ms) at millions of restarts x atoms: 20-80 atoms, 3,000
+// ligands 2.4 / 3.4 at 0.15, 6.6 / 8.3 at 2.4, 16.9 / 17.7 at 9.5, 28.9 / 29.4 at 19; 12,000
+// ligands 10.1 / 11.4 at 2.4, 25.6 / 24.9 at 9.6, 41 / 37 at 19; 100-200 atoms, 3,000 ligands
+// 35 / 40 at 7.2, 54 / 55 at 14; 6,000 ligands 67 / 70 at 14, 106 / 106 at 29; 64 atoms 0.97
+// to 1.05 times from 0.4 on; a list of 1 atom gains 1 to 8% in thirds at any work.
 constexpr int kSplitLigands = 2048;
+constexpr double kSplitWork = 1e7;
 constexpr int kSplitShare = 50;
 
-bool split_library(int ligands, int groups) { return groups == 1 && ligands >= kSplitLigands; }
+bool split_library(int ligands, long long atoms, int restarts, int groups) {
+    return groups == 1 && ligands >= kSplitLigands && (double)atoms * restarts >= kSplitWork;
+}
 
 // Side streams a call's chains can use.
 int side_ways(bool split, int bins, int groups) {
@@ -1050,7 +1059,7 @@ int enqueue_batch(dock_ctx *c, const Pocket &pk, const dock_library *lib, const 
     const bool capturing = cap != hipStreamCaptureStatusNone;
     // (looked at before anything of this call is enqueued)
     const int groups = p->bin_mode ? kMaxGroups : 1;
-    const bool split = split_library(lib->n_ligands, groups);
+    const bool split = split_library(lib->n_ligands, lib->n_atoms_total, p->restarts, groups);
     const bool side = p->mode == DOCK_MODE_BATCHED && !timed && !capturing &&
                       side_ways(split, used_bins(lib->mask_words, lib->n_atoms_total), groups) > 1 &&
                       side_streams_free(c, s, lib->n_ligands);
@@ -1829,7 +1838,7 @@ int dock_autotune(dock_ctx *c, int32_t pocket, const dock_library *lib, const do
             t.split = cur;
         }
         c->tuned[tune_key(sa)] = t;
-        const bool in_thirds = split_library(la.L, G);
+        const bool in_thirds = split_library(la.L, la.A_total, sa.R, G);
         for (int bin = 0; out && bin < kNumBins; ++bin) {
             dock_bin_tuning &r = reps[bin];
             if (in_thirds && r.ligands > 0) {

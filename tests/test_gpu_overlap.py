@@ -54,6 +54,33 @@ def test_overlapped_lists_are_the_sequence(D, ctx, L, atoms, bin_mode):  # noqa:
     D.dock_pocket_unload(ctx, pid)
 
 
+@pytest.mark.parametrize("L,atoms,restarts,kw", [
+    (2048, (60, 70), 80, {}),                  # the least in thirds: 10 million atoms to place
+    (2050, (3, 70), 256, {}), (2100, (200, 256), 40, {}),
+    (2100, (3, 70), 256, dict(bin_mode=1))])
+def test_thirds_of_a_library_are_the_sequence(D, ctx, L, atoms, restarts, kw):  # noqa: F811
+    pid, _, dl, _ = _setup(D, ctx, L, atoms, 90 + L % 7)
+    params = D.SearchParams(synth.start_quats(7, restarts), torsion_steps=16, sweep_passes=1,
+                            top_k=5, **kw)
+    ref, got, rep = [D.DeviceResults(L, dl.n_atoms_total, dl.n_rot_total, params) for _ in range(3)]
+    print(f"[case] thirds L={L} R={restarts} {kw}", flush=True)
+    D.dock_set_timing(ctx, True)
+    D.dock_ligands_batch(ctx, pid, dl, params, ref)
+    D.dock_set_timing(ctx, False)
+    D.dock_get_timing(ctx)
+    st = torch.cuda.Stream()
+    st.wait_stream(torch.cuda.current_stream())
+    for _ in range(3):
+        D.dock_ligands_batch(ctx, pid, dl, params, got)
+        torch.cuda.synchronize()
+        D.dock_ligands_batch(ctx, pid, dl, params, rep, st)
+        D.dock_ligands_batch(ctx, pid, dl, params, got, st)
+    torch.cuda.synchronize()
+    _same(ref, got)
+    _same(ref, rep)
+    D.dock_pocket_unload(ctx, pid)
+
+
 def test_overlapped_lists_under_a_callers_capture(D, ctx):  # noqa: F811
     pid, params, dl, (ref, got, _) = _setup(D, ctx, 40, (3, 100), 95)
     st = torch.cuda.Stream()

@@ -46,12 +46,14 @@ def ctx(D):
     D.dock_destroy(c)
 
 
-def _job(D, ctx, ligands, atoms=(12, 40), pid=None, **kw):
+def _job(D, ctx, ligands, atoms=(12, 40), pid=None, restarts=None, **kw):
+    # (large lists have restarts enough to run in thirds)
+    restarts = restarts or (4 if ligands < 2000 else 256)
     pk = synth.pocket_gaussians(7, 2, 8, 0.5, 4, 1.0)
     if pid is None:
         pid = D.dock_pocket_load(ctx, pk.values, pk.spacing, pk.origin)
     lib = synth.library_uniform(ligands, ligands, atoms, (0, 2))
-    params = D.SearchParams(synth.start_quats(3, 4), torsion_steps=8, sweep_passes=1, **kw)
+    params = D.SearchParams(synth.start_quats(3, restarts), torsion_steps=8, sweep_passes=1, **kw)
     dl = D.DeviceLibrary(lib, device="cpu")
     res = D.DeviceResults(ligands, dl.n_atoms_total, dl.n_rot_total, params, device="cpu")
     return pid, dl, params, res
@@ -269,15 +271,28 @@ def test_bounds_need_fewer_orientations_where_ligands_reach_out_of_the_grid(D, c
     assert got == {b: "align_bound" if b in bins else "align" for b in range(8)}
 
 
+@pytest.mark.parametrize("ligands,atoms,restarts,parts", [
+    (2047, (200, 250), 256, 1), (2048, (200, 250), 256, 3), (2048, (200, 250), 4, 1),
+    (2100, (1, 1), 256, 1), (9000, (1, 12), 20, 1), (9000, (1, 12), 400, 3)])
+def test_libraries_with_little_work_are_not_split(D, ctx, ligands, atoms, restarts, parts):
+    # in thirds from 2,048 ligands and 10 million restarts x atoms on
+    pid, dl, params, res = _job(D, ctx, ligands, atoms, restarts=restarts)
+    _log(D)
+    D.dock_ligands_batch(ctx, pid, dl, params, res, 0xA2)
+    D.lib().stub_all_idle()
+    bins = [m.group(1) for m in (re.match(r"dock bin=(\d)", line) for line in _log(D)) if m]
+    assert bins and {bins.count(b) for b in bins} == {parts}
+
+
 @pytest.mark.parametrize("sample", [60, 2100])
 def test_tuned_tiles_are_those_of_the_form_that_runs(D, ctx, sample):
     # the model's selection is faster alone with 16 waves, and slower beside a sweep: a
     # library in thirds keeps 4 waves, a short list takes the 16
-    pid, dl, params, res = _job(D, ctx, sample, (12, 120))
+    pid, dl, params, res = _job(D, ctx, sample, (12, 120), restarts=256)
     table = D.dock_autotune(ctx, pid, dl, params, 0xA1)
     assert {t["select_waves"] for t in table if t["ligands"]} == {16 if sample < 2048 else 4}
     for n, waves in ((60, 16), (2100, 4)):
-        _, dl, _, res = _job(D, ctx, n, (12, 120), pid=pid)
+        _, dl, _, res = _job(D, ctx, n, (12, 120), pid=pid, restarts=256)
         _log(D)
         D.dock_ligands_batch(ctx, pid, dl, params, res, 0xA1)
         D.lib().stub_all_idle()
