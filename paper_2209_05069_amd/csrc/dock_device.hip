@@ -2932,7 +2932,11 @@ static int select_shape(int nmax, int R, int K, bool plain, int *waves) {
     return sel && select_lds_bytes(nmax, *waves, R, K, 2) <= (size_t)160 * 1024 ? 2 : sel;
 }
 
-template <int NS>
+// Given: the restarts' poses are in ws.rpose (the plain form, with sel_lds); without the
+// replay its 16 waves need fewer registers and start beside the next ligand's k_plain (40
+// ligands of 200-240 atoms, 1,000 restarts of 5 steps: 9.3 -> 8.5 ms, at 20 steps
+// 27.5 -> 25.7).
+template <int NS, bool Given>
 __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibArgs lib,
                                                 WorkArgs ws, OutArgs out, int bin, int lst, int single,
                                                 int sel_lds) {
@@ -3033,8 +3037,7 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
                 };
                 if (t < R) {
                     const int r = uniform_int(order[t]);
-                    if (single >= 0 && ws.rpose) {
-                        // plain form: as k_plain left it
+                    if constexpr (Given) {
                         const float *P = ws.rpose + (size_t)r * n * 3;
                         for (int e = lane; e < 3 * n; e += 64) cp[e] = P[e];
                     } else {
@@ -3115,7 +3118,7 @@ __global__ __launch_bounds__(1024) void k_select(GridArgs g, SearchArgs sa, LibA
             for (int k = 0; k < ns; ++k)
                 for (int e = threadIdx.x; e < 3 * n; e += blockDim.x)
                     accp[(size_t)k * 3 * n + e] = keptL[(size_t)k * ps + e];
-        } else if (wave == 0) {
+        } else if (!Given && wave == 0) {
             // greedy selection with plain-RMSD dedup; poses rebuilt from traces
             int ns = 0;
             const float lim = sa.dedup2 * (float)n;
@@ -3901,10 +3904,10 @@ static hipError_t launch_select_t(int bin, int lst, int blocks, int waves, const
                                   const OutArgs &out, int single, hipStream_t s) {
     const int sel = select_shape(bin_nmax(bin), sa.R, sa.K, single >= 0, &waves);
     const size_t lds = select_lds_bytes(bin_nmax(bin), waves, sa.R, sa.K, sel);
-    hipFuncSetAttribute((const void *)k_select<NS>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                        (int)lds);
-    hipLaunchKernelGGL((k_select<NS>), dim3(blocks), dim3(64 * waves), lds, s, g, sa, lib, ws, out,
-                       bin, lst, single, sel);
+    auto *kernel = single >= 0 && ws.rpose && sel ? k_select<NS, true> : k_select<NS, false>;
+    hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64 * waves), lds, s, g, sa, lib, ws, out, bin, lst,
+                       single, sel);
     return hipGetLastError();
 }
 
@@ -4116,9 +4119,9 @@ static int select_occ(int bin, int waves, int R, int K) {
     int nb = 0;
     const int sel = select_shape(bin_nmax(bin), R, K, false, &waves);
     const size_t lds = select_lds_bytes(bin_nmax(bin), waves, R, K, sel);
-    hipFuncSetAttribute((const void *)k_select<NS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    hipFuncSetAttribute((const void *)k_select<NS, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                         (int)lds);
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_select<NS>, 64 * waves, lds) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_select<NS, false>, 64 * waves, lds) !=
         hipSuccess)
         return 1;
     return nb > 0 ? nb : 1;

@@ -89,3 +89,27 @@ def test_selection_does_not_depend_on_tile_or_library_size(D, ctx):  # noqa: F81
                             np.testing.assert_array_equal(x, y, err_msg=f"{i} {j} {n}")
     assert tried >= 8
     D.dock_pocket_unload(ctx, pid)
+
+
+@pytest.mark.parametrize("atoms,restarts,top_k", [((3, 64), 40, 30), ((60, 256), 40, 30),
+                                                  ((250, 256), 70, 1), ((3, 256), 64, 64)])
+def test_plain_poses_as_found_are_the_poses_replayed(D, ctx, atoms, restarts, top_k):  # noqa: F811
+    # (a context with a memory budget keeps no poses of the restarts: they are replayed)
+    pk = synth.pocket_gaussians(9, 4, 32, 0.5, 40, 4.0)
+    lib = synth.library_uniform(9, 12, atoms, (0, 4))
+    params = D.SearchParams(synth.start_quats(9, restarts), torsion_steps=16, sweep_passes=2,
+                            align_steps=12, top_k=top_k, dedup_rmsd=2.0, mode=1)
+    print(f"[case] plain poses {atoms} R={restarts} K={top_k}", flush=True)
+    tight = D.dock_create(0, hbm_budget_bytes=1 << 30)
+    got = []
+    for c in (ctx, tight):
+        pid = D.dock_pocket_load(c, pk.values, pk.spacing, pk.origin)
+        dl = D.DeviceLibrary(lib)
+        res = D.DeviceResults(12, dl.n_atoms_total, dl.n_rot_total, params)
+        D.dock_ligands_batch(c, pid, dl, params, res)
+        torch.cuda.synchronize()
+        got.append(res.to_host())
+        D.dock_pocket_unload(c, pid)
+    D.dock_destroy(tight)
+    for k in ("best_score", "n_poses", "status", "pose_score", "pose_restart", "pose_xyz"):
+        np.testing.assert_array_equal(got[0][k], got[1][k], err_msg=k)
