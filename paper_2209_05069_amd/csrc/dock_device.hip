@@ -2935,11 +2935,11 @@ static int select_shape(int nmax, int R, int K, bool plain, int *waves) {
 // Given: the restarts' poses are in ws.rpose (the plain form, with sel_lds); without the
 // replay its 16 waves need fewer registers and start beside the next ligand's k_plain (40
 // ligands of 200-240 atoms, 1,000 restarts of 5 steps: 9.3 -> 8.5 ms, at 20 steps
-// 27.5 -> 25.7).  At most 64 registers up to 64 atoms (65 otherwise), so that it leaves
+// 27.5 -> 25.7).  With the replay at most 64 registers up to 64 atoms (65 otherwise), which leaves
 // more room beside another third's sweep: 2,500 ligands of 20-80 atoms 42.8 -> 42.5 ms; with
 // as many up to 128 atoms, 42.1, but 4,096 of 12-150 atoms 63.6 -> 65.1.
 template <int NS, bool Given>
-__global__ __launch_bounds__(1024, NS == 1 ? 8 : 4) void k_select(GridArgs g, SearchArgs sa, LibArgs lib,
+__global__ __launch_bounds__(1024, NS == 1 && !Given ? 8 : 4) void k_select(GridArgs g, SearchArgs sa, LibArgs lib,
                                                 WorkArgs ws, OutArgs out, int bin, int lst, int single,
                                                 int sel_lds) {
     extern __shared__ __align__(16) unsigned char smem[];
