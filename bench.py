@@ -41,18 +41,18 @@ PEAK_FP32_NONPACKED_TFLOPS = 78.6  # one wave64 FMA per CU per clock (packed FP3
 TRAFFIC = {
     # large batched workload, T=256: rocprofv3 FETCH_SIZE / WRITE_SIZE of the alignment
     # (all bins), one step, scaled by the 256 MiB reference copy
-    (3, 256, 200000): ("k_align", "ec5705f94905e58f", 9.2182e+12),
+    (3, 256, 200000): ("k_align", "d8fc571d25f6f8a7", 9.2230e+12),
 }
 # The same of the torsion sweep, the dominant kernel since the alignment takes bounds.
 TRAFFIC_SWEEP = {
-    (3, 256, 200000): ("k_dock", "ec5705f94905e58f", 1.7708e+12),
+    (3, 256, 200000): ("k_dock", "d8fc571d25f6f8a7", 1.8171e+12),
 }
 
 # VALU wave-instructions per step of all docking kernels (rocprofv3 SQ_INSTS_VALU, one
 # step), for the VALU-instruction roofline: one wave64 VALU instruction per CU per
 # clock, 256 CUs at 2.4 GHz.  Same validity rule as TRAFFIC: (source sha, instructions).
 VALU_INSTR = {
-    (3, 256, 200000): ("ec5705f94905e58f", 1.7571e+12),
+    (3, 256, 200000): ("d8fc571d25f6f8a7", 1.7573e+12),
 }
 VALU_ROOF_PER_S = 256 * 2.4e9
 
